@@ -60,8 +60,8 @@ typedef enum {
 /* Precision of the Legendre contractions (the direct synthesis and analysis sums
  * of Section 4.2). The quadrature weights, FFTs, grid products and the viscous
  * update always run in FP64, and so do the Legendre values: FP64 and FP32
- * continue the three-term recurrence in FP64 registers from FP64 seed rows;
- * BF16X3 reads the FP64 table rounded once to FP32. */
+ * continue the recurrence in FP64 registers from FP64 seeds (FP64 mostly by pairs of
+ * degrees); BF16X3 reads the FP64 table rounded once to FP32. */
 enum {
   NSE_PREC_FP64 = 0,  /* FP64 products, FP64 accumulation                      */
   NSE_PREC_FP32 = 1,  /* values and coefficients rounded to FP32, FP32 products
@@ -113,14 +113,14 @@ nse_status nse_sphere_init(const nse_member* members, int32_t n_members,
 nse_status nse_sphere_destroy(nse_ctx* ctx);
 
 /* Member blocking of a truncation group (members sharing N and nlat). In FP64
- * a group with several members runs its Legendre synthesis and analysis as
- * FP64 MFMA products in which one pass over the table serves a block of
- * members (the same sums as Section 4.2; the table entries are reused as the
- * rows of a matrix product whose columns are the members' panels or ring
- * spectra). synth_block and anal_block are 0 (one member per workgroup, the
- * single-member kernels) or 2, 4, 8. The default for FP64 groups of >= 2
- * members is the largest power of two <= min(members, 4) for the synthesis
- * and <= min(members, 8) for the analysis, or what NSE_FLAG_AUTOTUNE measured. `member` selects the group by any of its
+ * a group with several members takes its Legendre synthesis and analysis (the
+ * same sums as Section 4.2) a block of members at a time: the workgroups of a
+ * block's members for one order run side by side on one XCD and share its cache for
+ * the order's recurrence seeds and coefficients. synth_block and anal_block
+ * are 0 (member by member, the single-member kernels) or 2, 4, 8. The default
+ * for FP64 groups of >= 2 members is the largest power of two
+ * <= min(members, 4) for the synthesis and <= min(members, 8) for the
+ * analysis, or what NSE_FLAG_AUTOTUNE measured. `member` selects the group by any of its
  * members. Other precisions always use the single-member kernels. Setting
  * drops captured graphs. NSE_ERR_ARG for an unknown block size or member, or
  * for non-zero blocks on a group of one member or of another precision. */
@@ -172,9 +172,9 @@ nse_status nse_nonlinear_adjoint(nse_ctx* ctx, const double* alpha,
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same
  * result as nse_nonlinear_adjoint (the same kernels), with the adjoint's
- * Fourier intermediates (5 + 4 field slabs of nlat x (N+1) complex values and
- * (N+1)(N+2)x4 panel cotangents per member, each group's pieces 256-byte
- * aligned) placed in a static device array of 32 MiB that the library holds on
+ * Fourier intermediates (5 + 4 field slabs of nlat x (N+1) complex values per
+ * member, each group's pieces 256-byte aligned; room for a further (N+1)(N+2)x4
+ * values per member is asked for) placed in a static device array of 32 MiB that the library holds on
  * every device it runs on until the process ends, instead of buffers the
  * context allocates on first use. It calls no allocator. One member up to
  * N = 255 on its default grid fits (18.4 MB); a context that needs more returns

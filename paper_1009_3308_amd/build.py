@@ -22,11 +22,10 @@ SOURCES = [
     "nse_api.cpp",
     "legendre_table.hip",
     "synthesis.hip",
+    "pair_legendre.hip",
     "ring_fft.hip",
     "analysis.hip",
     "contract_lp.hip",
-    "adjoint.hip",
-    "ensemble.hip",
     "ndf_adaptive.hip",
     "diagnostics.hip",
 ]

@@ -26,6 +26,8 @@
 // 27.0 us against 30.9 and 28.1). With fewer latitudes per lane (N = 100 on
 // 160 x 320) four waves are faster (4.7 against 5.0 us; 4.8 against 5.9 us with
 // the corrector sweep of a device-controlled run).
+#include <type_traits>
+
 #include "lane_ops.h"
 #include "spectral_ops.h"
 
@@ -214,8 +216,16 @@ hipError_t launch_analysis_otf(dim3 grid, dim3 block, size_t lds, hipStream_t s,
     case 2: hipLaunchKernelGGL((k_analysis_otf<TT, 2, NDF>), grid, block, lds, s, g, out); break;
     case 3: hipLaunchKernelGGL((k_analysis_otf<TT, 3, NDF>), grid, block, lds, s, g, out); break;
     case 4: hipLaunchKernelGGL((k_analysis_otf<TT, 4, NDF>), grid, block, lds, s, g, out); break;
-    case 5: hipLaunchKernelGGL((k_analysis_otf<TT, 5, NDF>), grid, block, lds, s, g, out); break;
-    default: hipLaunchKernelGGL((k_analysis_otf<TT, 6, NDF>), grid, block, lds, s, g, out); break;
+    default:
+      // FP64 grids of nh >= 256 take the degree pairs
+      if constexpr (std::is_same<TT, float>::value) {
+        if (g.nh <= 320)
+          hipLaunchKernelGGL((k_analysis_otf<TT, 5, NDF>), grid, block, lds, s, g, out);
+        else
+          hipLaunchKernelGGL((k_analysis_otf<TT, 6, NDF>), grid, block, lds, s, g, out);
+        break;
+      }
+      return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }

@@ -41,16 +41,21 @@ struct Group {
   std::vector<double> nu;
   std::vector<double> mu, w;         // all nlat nodes (host)
   FftPlan plan{};
-  double *d_mu = nullptr, *d_w = nullptr, *d_T1 = nullptr, *d_T2 = nullptr;
+  double *d_mu = nullptr, *d_w = nullptr, *d_T1 = nullptr;
   float *d_T1f = nullptr, *d_T2f = nullptr;
   int64_t* d_t2off = nullptr;
-  double2 *d_rec_a = nullptr, *d_rec_g = nullptr, *d_rec_p = nullptr;  // recurrence coefficients (rec_slot)
+  double2 *d_rec_a = nullptr, *d_rec_g = nullptr;  // recurrence coefficients (rec_slot)
+  // tables of the degree-pair contractions, one buffer (build_pairs), and the seeds
+  // of their recurrences in four and in eight segments per order
+  double2* d_pair = nullptr;
+  double2 *d_pair_rec = nullptr, *d_pair_con = nullptr, *d_pair_lam = nullptr, *d_pair_syn = nullptr;
+  double2 *d_seeds1 = nullptr, *d_seeds2 = nullptr;
   uint64_t* d_lps = nullptr;      // split-bf16 synthesis panels (BF16X3 groups)
   int64_t* d_lpsoff = nullptr;
   int64_t lps_stride = 0;         // per member, 8-byte units
   std::vector<int64_t> t2off;  // [N+2] start of order m in T2
   double2 *d_F = nullptr, *d_W = nullptr, *d_tw = nullptr;
-  double2 *d_Fa = nullptr, *d_Fbar = nullptr, *d_Pbar = nullptr;  // adjoint, allocated on demand
+  double2 *d_Fa = nullptr, *d_Fbar = nullptr;  // adjoint, allocated on demand
   int64_t* d_off = nullptr;
   double* d_nu = nullptr;
 
@@ -67,22 +72,29 @@ struct Group {
     g.mu = d_mu;
     g.w = d_w;
     g.T1 = d_T1;
-    g.T2 = d_T2;
     g.T1f = d_T1f;
     g.T2f = d_T2f;
     g.t2off = d_t2off;
     g.rec_a = d_rec_a;
     g.rec_g = d_rec_g;
-    g.rec_p = d_rec_p;
+    g.pair_rec = d_pair_rec;
+    g.pair_syn = reinterpret_cast<const double*>(d_pair_syn);
+    g.pair_con = d_pair_con;
+    g.pair_lam = d_pair_lam;
+    g.seeds1 = d_seeds1;
+    g.seeds2 = d_seeds2;
     g.F = d_F;
     g.Fa = d_Fa;
     g.Fbar = d_Fbar;
-    g.Pbar = d_Pbar;
     g.W = d_W;
     g.lps = d_lps;
     g.lpsoff = d_lpsoff;
     g.tw = d_tw;
     g.off = d_off;
+    g.off0 = offsets[0];
+    g.ostride = offsets.size() > 1 ? offsets[1] - offsets[0] : 0;
+    for (size_t i = 1; i < offsets.size(); ++i)
+      if (offsets[i] - offsets[i - 1] != g.ostride) g.ostride = -1;
     g.nu = d_nu;
     return g;
   }
@@ -97,9 +109,10 @@ struct Group {
     if (d_Fa) {
       g.Fa = d_Fa + (int64_t)i * 5 * nlat * (N + 1);
       g.Fbar = d_Fbar + (int64_t)i * 4 * nlat * (N + 1);
-      g.Pbar = d_Pbar + (int64_t)i * (N + 1) * (N + 2) * 4;
     }
     g.off = d_off + i;
+    g.off0 = offsets[i];
+    g.ostride = 0;
     g.nu = d_nu + i;
     return g;
   }
@@ -256,20 +269,20 @@ void free_group(Group& g) {
   (void)hipFree(g.d_mu);
   (void)hipFree(g.d_w);
   (void)hipFree(g.d_T1);
-  (void)hipFree(g.d_T2);
   (void)hipFree(g.d_T1f);
   (void)hipFree(g.d_T2f);
   (void)hipFree(g.d_t2off);
   (void)hipFree(g.d_rec_a);
   (void)hipFree(g.d_rec_g);
-  (void)hipFree(g.d_rec_p);
+  (void)hipFree(g.d_pair);
+  (void)hipFree(g.d_seeds1);
+  (void)hipFree(g.d_seeds2);
   (void)hipFree(g.d_lps);
   (void)hipFree(g.d_lpsoff);
   (void)hipFree(g.d_F);
   (void)hipFree(g.d_W);
   (void)hipFree(g.d_Fa);
   (void)hipFree(g.d_Fbar);
-  (void)hipFree(g.d_Pbar);
   (void)hipFree(g.d_tw);
   (void)hipFree(g.d_off);
   (void)hipFree(g.d_nu);
@@ -294,6 +307,87 @@ hipError_t dalloc(T** p, size_t count) {
   return hipMalloc((void**)p, sizeof(T) * (count ? count : 1));
 }
 
+// Tables and seeds of the degree-pair recurrences (pair_legendre.hip), in long
+// double and rounded once (the seeds in double-double on the device). Per (m, k) with
+// l = m + 2k, e = e(l, m):
+//   s_{k+1} = s_{k-1} g_k / g_{k+1}, g_k = e(l) e(l+1), s_0 = s_1 = 1;
+//   A_k = s_k / (s_{k+1} g_{k+1}), B_k = -A_k (e(l+1)^2 + e(l+2)^2);
+//   c1_k = s_k e(l+1), c2_k = s_k e(l+2);
+//   synthesis columns of the fields i m c and S c (S c[l] = cm(l) c[l-1] - cp(l) c[l+1],
+//   cm(l) = (l-1) e(l), cp(l) = (l+2) e(l+1)) of coefficients c[l], over the degrees
+//   up to N+1: pair_syn = {m c1, m c2, m s, c1 cm(l), c2 cm(l+2) - c1 cp(l), -c2 cp(l+2),
+//   s cm(l+1), -s cp(l+1)}, the terms of degrees past N+1 left out.
+nse_status build_pairs(nse_ctx* c, Group& g) {
+  const int N = g.N;
+  const int64_t np = pair_slot(N, N) + pair_count(N, N);
+  // one host buffer and one copy: (A, B), their low parts, (c1, c2 | s), the synthesis
+  // columns, (lambda^(-1/2), lambda^(1/2)), the starting values
+  std::vector<double2> all((size_t)8 * np + 2 * N + 3);
+  double2 *rec = all.data(), *lo = rec + np, *con = lo + np, *syn2 = con + 2 * np,
+          *lam = syn2 + 4 * np, *q0 = lam + N + 2;
+  double* syn = reinterpret_cast<double*>(syn2);
+  std::vector<long double> e(N + 8), s(N + 8);
+  long double pr = std::sqrt(1.0L / (4.0L * 3.14159265358979323846264338327950288L));
+  for (int l = 1; l <= N + 1; ++l) {
+    const long double v = (long double)l * (l + 1);
+    lam[l] = make_double2((double)(1.0L / std::sqrt(v)), (double)std::sqrt(v));
+  }
+  lam[0] = make_double2(0.0, 0.0);
+  for (int m = 0; m <= N; ++m) {
+    const int K = pair_count(N, m), L = N + 2 - m;
+    const long double mm = (long double)m * m;
+    for (int i = 0; i <= 2 * K + 3; ++i) {  // e[i] = e(m + i)
+      const long double l2 = (long double)(m + i) * (m + i);
+      e[i] = i ? std::sqrt((l2 - mm) / (4.0L * l2 - 1.0L)) : 0.0L;
+    }
+    s[0] = s[1] = 1.0L;
+    for (int k = 1; k <= K; ++k)
+      s[k + 1] = s[k - 1] * (e[2 * k] * e[2 * k + 1]) / (e[2 * k + 2] * e[2 * k + 3]);
+    if (m) pr *= -std::sqrt((2.0L * m + 1.0L) / (2.0L * m));
+    const long double qm = pr / e[1];
+    q0[m] = make_double2((double)qm, (double)(qm - (double)qm));
+    for (int k = 0; k < K; ++k) {
+      const int64_t i = pair_slot(N, m) + k;
+      const long double A = s[k] / (s[k + 1] * e[2 * k + 2] * e[2 * k + 3]);
+      const long double B = -A * (e[2 * k + 1] * e[2 * k + 1] + e[2 * k + 2] * e[2 * k + 2]);
+      rec[i] = make_double2((double)A, (double)B);
+      lo[i] = make_double2((double)(A - rec[i].x), (double)(B - rec[i].y));
+      const long double c1 = s[k] * e[2 * k + 1], c2 = s[k] * e[2 * k + 2];
+      con[2 * i] = make_double2((double)c1, (double)c2);
+      con[2 * i + 1] = make_double2((double)s[k], 0.0);
+      const long double l = m + 2 * k;
+      const long double on = 2 * k + 1 < L ? 1.0L : 0.0L, up = 2 * k + 2 < L ? 1.0L : 0.0L;
+      double* v = syn + 8 * i;
+      v[0] = (double)(m * c1);
+      v[1] = (double)(m * c2 * up);
+      v[2] = (double)(m * s[k] * on);
+      v[3] = (double)(c1 * (l - 1.0L) * e[2 * k]);
+      v[4] = (double)(up * c2 * (l + 1.0L) * e[2 * k + 2] - c1 * (l + 2.0L) * e[2 * k + 1]);
+      v[5] = (double)(-up * c2 * (l + 4.0L) * e[2 * k + 3]);
+      v[6] = (double)(on * s[k] * l * e[2 * k + 1]);
+      v[7] = (double)(-on * s[k] * (l + 3.0L) * e[2 * k + 2]);
+    }
+  }
+  NSE_HIP(c, dalloc(&g.d_pair, all.size()));
+  NSE_HIP(c, hipMemcpy(g.d_pair, all.data(), sizeof(double2) * all.size(), hipMemcpyHostToDevice));
+  g.d_pair_rec = g.d_pair;
+  g.d_pair_con = g.d_pair + (con - rec);
+  g.d_pair_syn = g.d_pair + (syn2 - rec);
+  g.d_pair_lam = g.d_pair + (lam - rec);
+  // four segments on the large grids and for blocks of members, eight for single
+  // members on the others
+  const size_t tiles = (size_t)(N + 1) * ((g.nh + 15) / 16);
+  for (int ks = 1; ks <= 2; ++ks) {
+    if (ks == 1 ? g.nh < 256 && g.members.size() < 2 : g.nh >= 256) continue;
+    double2*& seeds = ks == 1 ? g.d_seeds1 : g.d_seeds2;
+    NSE_HIP(c, dalloc(&seeds, tiles * ks * 64));
+    NSE_HIP(c, hipMemsetAsync(seeds, 0, sizeof(double2) * tiles * ks * 64, c->stream));
+    NSE_HIP(c, launch_pair_seeds(g.view(), ks, g.d_pair + (lo - rec), g.d_pair + (q0 - rec), seeds,
+                                 c->stream));
+  }
+  return NSE_OK;
+}
+
 nse_status build_group(nse_ctx* c, Group& g) {
   g.nh = (g.nlat + 1) / 2;
   g.M = 2 * g.nlat;
@@ -303,6 +397,9 @@ nse_status build_group(nse_ctx* c, Group& g) {
   NSE_HIP(c, dalloc(&g.d_w, g.nh));
   NSE_HIP(c, hipMemcpy(g.d_mu, g.mu.data(), sizeof(double) * g.nh, hipMemcpyHostToDevice));
   NSE_HIP(c, hipMemcpy(g.d_w, g.w.data(), sizeof(double) * g.nh, hipMemcpyHostToDevice));
+  // the degree-by-degree kernels (FP32 mode; FP64 members by themselves on grids below
+  // nh = 256) seed from the table T1, the split-bf16 mode reads its FP32 copies
+  const bool table = g.precision != NSE_PREC_FP64 || g.nh < 256;
   const int64_t ts1 = t1_size(g.N, g.nh);
   g.t2off.assign(g.N + 2, 0);
   for (int m = 0; m <= g.N; ++m) {
@@ -313,12 +410,11 @@ nse_status build_group(nse_ctx* c, Group& g) {
   NSE_HIP(c, dalloc(&g.d_t2off, g.N + 2));
   NSE_HIP(c, hipMemcpy(g.d_t2off, g.t2off.data(), sizeof(int64_t) * (g.N + 2),
                        hipMemcpyHostToDevice));
-  NSE_HIP(c, dalloc(&g.d_T1, ts1));
-  NSE_HIP(c, dalloc(&g.d_T2, ts2));
-  {
+  if (table) NSE_HIP(c, dalloc(&g.d_T1, ts1));
+  if (table) {
     // recurrence coefficients, in long double and rounded once
     const int64_t nrec = (int64_t)(g.N + 2) * (g.N + 3) / 2;
-    std::vector<double2> ra(nrec), rg(nrec), rp(nrec);
+    std::vector<double2> ra(nrec), rg(nrec);
     for (int m = 0; m <= g.N; ++m) {
       const long double lm = m;
       auto a_of = [&](int l) -> long double {
@@ -333,17 +429,12 @@ nse_status build_group(nse_ctx* c, Group& g) {
         const long double rs = (l > 0) ? 1.0L / std::sqrt((long double)l * (l + 1)) : 0.0L;
         ra[sl] = make_double2((double)al, (double)ratio);
         rg[sl] = make_double2((double)gl, (double)rs);
-        const long double en = (l + 1 <= g.N + 1) ? 1.0L / a_of(l + 1) : 0.0L;  // e(l+1)
-        const long double el = (l > m) ? 1.0L / al : 0.0L;                      // e(l)
-        rp[sl] = make_double2((double)((long double)l * en), (double)((l + 1.0L) * el));
       }
     }
     NSE_HIP(c, dalloc(&g.d_rec_a, nrec));
     NSE_HIP(c, dalloc(&g.d_rec_g, nrec));
-    NSE_HIP(c, dalloc(&g.d_rec_p, nrec));
     NSE_HIP(c, hipMemcpy(g.d_rec_a, ra.data(), sizeof(double2) * nrec, hipMemcpyHostToDevice));
     NSE_HIP(c, hipMemcpy(g.d_rec_g, rg.data(), sizeof(double2) * nrec, hipMemcpyHostToDevice));
-    NSE_HIP(c, hipMemcpy(g.d_rec_p, rp.data(), sizeof(double2) * nrec, hipMemcpyHostToDevice));
   }
   if (c->params.precision == NSE_PREC_BF16X3) {
     // FP32 copies of the tables, split into bf16 pieces in registers (the FP64
@@ -372,8 +463,9 @@ nse_status build_group(nse_ctx* c, Group& g) {
   NSE_HIP(c, dalloc(&g.d_nu, nb));
   NSE_HIP(c, hipMemcpy(g.d_off, g.offsets.data(), sizeof(int64_t) * nb, hipMemcpyHostToDevice));
   NSE_HIP(c, hipMemcpy(g.d_nu, g.nu.data(), sizeof(double) * nb, hipMemcpyHostToDevice));
-  NSE_HIP(c, launch_legendre_table(g.view(), g.d_T1, g.d_T2, g.d_T1f, g.d_T2f, c->stream));
-  return NSE_OK;
+  if (table)
+    NSE_HIP(c, launch_legendre_table(g.view(), 0, g.N + 1, g.d_T1, g.d_T1f, g.d_T2f, c->stream));
+  return build_pairs(c, g);
 }
 
 bool is_finite(double x) { return std::isfinite(x); }
@@ -423,19 +515,29 @@ nse_status timed_launch(nse_ctx* c, int kind, F&& launch) {
   return NSE_OK;
 }
 
-// FP64 and FP32 contractions run on the vector units (HBM-bound table streams);
-// the split-bf16 form runs on MFMA.
-// Groups of several FP64 members use the member-batched MFMA products.
+// FP64 contractions run by degree pairs on the FP64 matrix cores, except those of single
+// members on a small grid; FP32 ones run on the vector units (recurrence in FP64
+// registers), the split-bf16 form on the bf16 matrix cores.
+//
+// A member by itself (member block 0) on a small grid is bound by the chain of one workgroup, not by
+// arithmetic, and the degree-by-degree kernels, which cut an order into more and
+// shorter workgroups, have the shorter chain: synthesis 6.8 against 7.4 us at N = 155
+// and 11.3 against 10.7 at N = 255 (nh = 117 and 192), analysis 5.2 against 7.2 us at
+// N = 155, 8.4 against 8.5 at N = 255 and 9.0 against 9.6 at N = 300 (nh = 240); at N =
+// 511 (nh = 384) the pairs take 24.6 against 37.2 and 18.8 against 29.2 us.
+bool pair_synthesis(const GroupView& v, int mode) {
+  return mode != SYNTH_NONLINEAR || v.mb_synth > 1 || v.nh >= 192;
+}
+bool pair_analysis(const GroupView& v) { return v.mb_anal > 1 || v.nh >= 256; }
 hipError_t launch_synth_any(const GroupView& v, const SynthInput& in, int mode, hipStream_t s) {
   if (v.precision == NSE_PREC_BF16X3) return launch_synthesis_lp(v, in, mode, v.precision, s);
-  if (v.precision == NSE_PREC_FP64 && mode == SYNTH_NONLINEAR && v.mb_synth >= 2)
-    return launch_synthesis_mb(v, in, v.mb_synth, s);
+  if (v.precision == NSE_PREC_FP64 && pair_synthesis(v, mode)) return launch_synthesis_pair(v, in, mode, s);
   return launch_synthesis(v, in, mode, s);
 }
 
 hipError_t launch_anal_any(const GroupView& v, const AnalOutput& out, hipStream_t s) {
   if (v.precision == NSE_PREC_BF16X3) return launch_analysis_lp(v, out, v.precision, s);
-  if (v.precision == NSE_PREC_FP64 && v.mb_anal >= 2) return launch_analysis_mb(v, out, v.mb_anal, s);
+  if (v.precision == NSE_PREC_FP64 && pair_analysis(v)) return launch_analysis_pair(v, out, s);
   return launch_analysis(v, out, s);
 }
 
@@ -638,9 +740,8 @@ nse_status enqueue_step(nse_ctx* c, double2* hist, const double2* forcing, int64
   return NSE_OK;
 }
 
-// Buffers of the adjoint (four forward fields plus the analysis cotangent,
-// the field-spectrum cotangents and the panel cotangents), allocated on the
-// first adjoint call.
+// Buffers of the adjoint (four forward fields plus the analysis cotangent, and
+// the field-spectrum cotangents), allocated on the first adjoint call.
 nse_status ensure_adjoint_buffers(nse_ctx* c) {
   for (auto& g : c->groups) {
     if (g.d_Fa) continue;
@@ -648,16 +749,15 @@ nse_status ensure_adjoint_buffers(nse_ctx* c) {
     const size_t fs = (size_t)g.nlat * (g.N + 1);
     NSE_HIP(c, dalloc(&g.d_Fa, nb * 5 * fs));
     NSE_HIP(c, dalloc(&g.d_Fbar, nb * 4 * fs));
-    NSE_HIP(c, dalloc(&g.d_Pbar, nb * (size_t)(g.N + 1) * (g.N + 2) * 4));
   }
   return NSE_OK;
 }
 
 // alpha_bar = J^T n_bar at the synthesis input `in` (always FP64 tables):
 // recompute the forward spectra with the analysis cotangent as a fifth field,
-// then the transposed ring, synthesis and prologue.
+// then the transposed ring, and the transposed synthesis and prologue.
 // `scratch_base` (optional): device memory of noalloc_bytes(c) bytes that holds
-// the groups' Fa, Fbar and Pbar instead of the context's own buffers.
+// the groups' Fa and Fbar instead of the context's own buffers.
 nse_status enqueue_nonlinear_adjoint(nse_ctx* c, SynthInput in, const double2* n_bar,
                                      double2* alpha_bar, double2* scratch_base = nullptr) {
   in.adj = n_bar;
@@ -674,12 +774,10 @@ nse_status enqueue_nonlinear_adjoint(nse_ctx* c, SynthInput in, const double2* n
       const size_t fs = (size_t)g.nlat * (g.N + 1);
       v.Fa = carve(sizeof(double2) * nb * 5 * fs);
       v.Fbar = carve(sizeof(double2) * nb * 4 * fs);
-      v.Pbar = carve(sizeof(double2) * nb * (size_t)(g.N + 1) * (g.N + 2) * 4);
     }
-    NSE_HIP(c, launch_synthesis(v, in, SYNTH_ADJ, c->stream));
+    NSE_HIP(c, launch_synthesis_pair(v, in, SYNTH_ADJ, c->stream));
     NSE_HIP(c, launch_ring_adjoint(v, g.plan, c->stream));
-    NSE_HIP(c, launch_synthesis_adjoint(v, c->stream));
-    NSE_HIP(c, launch_prep_adjoint(v, alpha_bar, c->stream));
+    NSE_HIP(c, launch_adjoint_pair(v, alpha_bar, nullptr, false, c->stream));
   }
   return NSE_OK;
 }
@@ -845,11 +943,10 @@ nse_status ndf_correct(nse_ctx* c, int mode, int sweep, const double2* dprev, do
 }
 
 // The corrector can ride in the analysis epilogue (ANAL_NDF) when the context is
-// one group whose analysis is k_analysis_otf.
+// one group of the FP64 or FP32 mode.
 bool ndf_fusable(const nse_ctx* c) {
   if (c->groups.size() != 1) return false;
-  const Group& g = c->groups[0];
-  return g.precision != NSE_PREC_BF16X3 && !(g.precision == NSE_PREC_FP64 && g.mb_anal >= 2);
+  return c->groups[0].precision != NSE_PREC_BF16X3;
 }
 
 // The chain of device-controlled sweep slot parity `sel` with the corrector in
@@ -1111,8 +1208,10 @@ static nse_status bind_noalloc_scratch(nse_ctx* c) {
   return NSE_OK;
 }
 
-// Bytes of adjoint intermediates (Fa, Fbar, Pbar of every group) carved from the
-// static scratch, each piece 256-byte aligned.
+// Bytes the static scratch must hold for a context: the adjoint intermediates Fa and
+// Fbar of every group, each piece 256-byte aligned, and (N+1)(N+2) x 4 complex values
+// per member beside them, which no kernel uses (the documented size, so that the
+// contexts it admits stay the same).
 static size_t noalloc_bytes(const nse_ctx* c) {
   auto up = [](size_t b) { return (b + 255) & ~size_t(255); };
   size_t total = 0;
@@ -1182,8 +1281,7 @@ nse_status nse_sphere_init(const nse_member* members, int32_t n_members, const n
                "member %d: M = %d must be <= %d and factor into 2, 3 and 5", i, 2 * m.nlat, kMaxM);
       return init_fail(NSE_ERR_UNSUPPORTED, buf);
     }
-    if (synthesis_lds_bytes(m.N, 5) > 65536 || synthesis_lds_bytes(m.N, 4) > 65536 || ring_lds_bytes(2 * m.nlat) > 65536 ||
-        synthesis_adjoint_lds_bytes((m.nlat + 1) / 2) > 65536 ||
+    if (synthesis_lds_bytes(m.N) > 65536 || ring_lds_bytes(2 * m.nlat) > 65536 ||
         analysis_otf_lds_bytes((m.nlat + 1) / 2) > 65536 || synthesis_lp_lds_bytes(m.N) > 65536 ||
         split_panel_lp_lds_bytes(m.N) > 65536 ||
         analysis_lp_lds_bytes((m.nlat + 1) / 2) > 65536) {
@@ -1511,10 +1609,9 @@ nse_status enqueue_adjoint_sweep(nse_ctx* ctx, const double2* tr, int64_t n, int
     a.h = ctx->params.dt;
     for (auto& g : ctx->groups) {
       const GroupView v = g.view();
-      NSE_HIP(ctx, launch_synthesis(v, in, SYNTH_ADJ, ctx->stream));
+      NSE_HIP(ctx, launch_synthesis_pair(v, in, SYNTH_ADJ, ctx->stream));
       NSE_HIP(ctx, launch_ring_adjoint(v, g.plan, ctx->stream));
-      NSE_HIP(ctx, launch_synthesis_adjoint(v, ctx->stream));
-      NSE_HIP(ctx, launch_prep_step_adjoint(v, a, ctx->stream));
+      NSE_HIP(ctx, launch_adjoint_pair(v, nullptr, &a, false, ctx->stream));
     }
   }
   return NSE_OK;
@@ -1685,8 +1782,7 @@ nse_status nse_analyze_velocity(nse_ctx* ctx, const double* u_grid, double* alph
     const Group& g = ctx->groups[ctx->member_group[i]];
     const GroupView v = g.member_view(ctx->member_index[i]);
     NSE_HIP(ctx, launch_ring_project(v, g.plan, u_grid + goff, ctx->stream));
-    NSE_HIP(ctx, launch_synthesis_adjoint(v, ctx->stream));
-    NSE_HIP(ctx, launch_prep_adjoint(v, (double2*)alpha_out, ctx->stream));
+    NSE_HIP(ctx, launch_adjoint_pair(v, (double2*)alpha_out, nullptr, true, ctx->stream));
     goff += (int64_t)2 * g.nlat * g.M;
   }
   return NSE_OK;
@@ -1699,9 +1795,9 @@ nse_status nse_legendre_values(nse_ctx* ctx, int32_t member, int32_t m, double* 
     return fail(ctx, NSE_ERR_ARG, "member %d out of range", member);
   const Group& g = ctx->groups[ctx->member_group[member]];
   if (m < 0 || m > g.N) return fail(ctx, NSE_ERR_ARG, "order m = %d outside 0..%d", m, g.N);
-  const size_t count = (size_t)(g.N + 2 - m) * g.nh;
-  NSE_HIP(ctx, hipMemcpyAsync(out, g.d_T1 + t1_order_offset(g.N, m, g.nh), sizeof(double) * count,
-                              hipMemcpyDeviceToDevice, ctx->stream));
+  // the table's own kernel, one order (T1 at the order's offset is `out`)
+  NSE_HIP(ctx, launch_legendre_table(g.view(), m, 1, out - t1_order_offset(g.N, m, g.nh), nullptr,
+                                     nullptr, ctx->stream));
   return NSE_OK;
 }
 

@@ -47,16 +47,23 @@ __host__ __device__ inline int64_t coeff_offset(int N, int m) {
 // computed once per group on the host, for l = m .. N+1 at rec_slot(N, l, m):
 //   rec_a = (a(l,m), a(l,m) / a(l-1,m)),  a(l,m) = sqrt((4 l^2 - 1) / (l^2 - m^2)),
 //   rec_g = ((2l+1) e(l), lambda_l^(-1/2)),  e(l) = 1 / a(l,m),
-//   rec_p = (l e(l+1), (l+1) e(l))  (the coefficients of the transposed panel
-//           recurrences of the adjoint; l e(l+1) = 0 at l = N+1),
 // with a(m,m) = e(m) = 0, the ratio 0 for l <= m+1 (it multiplies Pbar[m-1,m] = 0)
 // and lambda^(-1/2) = 0 at l = 0.
 __host__ __device__ inline int64_t rec_slot(int N, int l, int m) {
   return coeff_offset(N + 1, m) + (l - m);
 }
+// Degree pairs of order m (pair_legendre.hip): k = 0 .. pair_count - 1 covers the
+// degrees m .. N+1; tables over (m, k) start at pair_slot.
+__host__ __device__ inline int pair_count(int N, int m) { return (N + 3 - m) / 2; }
+__host__ __device__ inline int64_t pair_slot(int N, int m) {
+  const int64_t T = N + 3, r = T - m;
+  return T * T / 4 - r * r / 4;
+}
+// Rows per segment of the recurrences (4 ks segments, an even number of rows).
+__host__ __device__ inline int pair_len(int K, int ks) { return 2 * ((K + 8 * ks - 1) / (8 * ks)); }
 // Legendre tables, l = m .. N+1 (L = N + 2 - m degrees for order m, k = l - m):
 //   T1[m][k][p]                        (synthesis; latitude fastest, row stride nh)
-//   T2[m][deg tile][p][64 degrees]     (analysis; ceil(L/64) tiles of 64 degrees,
+//   T2[m][deg tile][p][64 degrees]     (split-bf16 analysis, in FP32; ceil(L/64) tiles of 64 degrees,
 //                                       each a contiguous block streamed by one
 //                                       workgroup; orders start at t2off[m])
 constexpr int kTile = 64;
@@ -71,27 +78,33 @@ __host__ __device__ inline int64_t t1_size(int N, int nh) {
 struct GroupView {
   int N, nlat, nh, M, nb;   // nh = northern latitudes incl. the equator if nlat is odd
   int precision;            // NSE_PREC_* of the Legendre contractions
-  int mb_synth, mb_anal;    // member blocks of the batched FP64 MFMA kernels (0 = per member)
+  int mb_synth, mb_anal;    // member blocks of the FP64 contractions (0 = member by member)
   const double* mu;         // [nh] Gauss-Legendre nodes, descending
   const double* w;          // [nh]
-  const double* T1;         // FP64 synthesis table (layouts above)
-  const double* T2;         // FP64 analysis table
+  const double* T1;         // FP64 table (layouts above); null where nothing reads it
   const float* T1f;         // FP32 copies (split-bf16x3 mode only), else null
   const float* T2f;
   const int64_t* t2off;     // [N+2] start of order m in T2 (element units)
   const double2* rec_a;     // [(N+2)(N+3)/2] (a(l,m), a(l,m) / a(l-1,m)), slot rec_slot(N, l, m)
   const double2* rec_g;     // same slots: ((2l+1) e(l), lambda_l^(-1/2)), see rec_slot
-  const double2* rec_p;     // same slots: (l e(l+1), (l+1) e(l)), see rec_slot
+  // degree-pair contractions (pair_legendre.hip): tables over pair_slot
+  const double2* pair_rec;  // (A_k, B_k)
+  const double* pair_syn;   // [8]: coefficients of the synthesis columns, see build_group
+  const double2* pair_con;  // [2]: (c1, c2), (s, -) of Pbar[l_k] = c1_k q_k + c2_{k-1} q_{k-1},
+                            // Pbar[l_k + 1] = mu s_k q_k
+  const double2* pair_lam;  // [N+2] (lambda^(-1/2), lambda^(1/2)), zero at l = 0
+  const double2* seeds1;    // (q_{k-1}, q_k) at the first k of every segment: [m][tile of 16
+  const double2* seeds2;    // latitudes][4 ks segments][16] for ks = 1 and 2 (null: not kept)
   double2* F;               // [nb][4][N+1][nlat] Fourier coefficients of grid fields
   double2* Fa;              // adjoint: [nb][5][N+1][nlat] (4 forward fields + adjoint input)
   double2* Fbar;            // adjoint: [nb][4][N+1][nlat] cotangents of the field spectra
-  double2* Pbar;            // adjoint: [nb][N+1][N+2][4] cotangents of the panels
   double2* W;               // [nb][N+1][nlat] weighted ring spectra (analysis input),
                             // latitude fastest so the analysis reads them coalesced
   uint64_t* lps;            // split-bf16 synthesis panels, 8-byte groups (precision BF16X3)
   const int64_t* lpsoff;    // [N+2] start of order m in one member's lps (member stride lpsoff[N+1])
   const double2* tw;        // [M] exp(-2 pi i k / M)
-  const int64_t* off;       // [nb] complex-slot offset of each member in a state
+  const int64_t* off;       // [nb] complex-slot offset of each member in a state,
+  int64_t off0, ostride;    // equal to off0 + b ostride where ostride >= 0
   const double* nu;         // [nb]
   const int* gate;          // null, or a device flag: the chain kernels do nothing while it is 0
 };
@@ -109,11 +122,10 @@ struct FftPlan {
 };
 
 // The history update that ends the adjoint of one NDF step (eq. (ode_disc)
-// transposed), from the panel cotangents Pbar of its nonlinear adjoint:
+// transposed), from the result alpha_bar of its nonlinear adjoint:
 //   r = hin[0] / (c_0 + h nu lambda)   (zero at l = 0, real at m = 0),
 //   hout[j] = hin[j+1] - c_{j+1} r + pi_j alpha_bar,   j = 0 .. depth-1,
-// with alpha_bar the predictor cotangent (the transposed panel recurrences) and
-// pi_j the predictor's weights.
+// with alpha_bar the predictor cotangent and pi_j the predictor's weights.
 struct StepAdjointArgs {
   const double2* hin;  // [depth][state]
   double2* hout;       // [depth][state]; may equal hin
@@ -228,7 +240,7 @@ struct NdfArgs {
 };
 
 // Launchers (each enqueues on `s` and returns the launch status).
-hipError_t launch_legendre_table(const GroupView& g, double* T1, double* T2, float* T1f,
+hipError_t launch_legendre_table(const GroupView& g, int m0, int count, double* T1, float* T1f,
                                  float* T2f, hipStream_t s);
 hipError_t launch_synthesis(const GroupView& g, const SynthInput& in, int mode, hipStream_t s);
 hipError_t launch_ring(const GroupView& g, const FftPlan& plan, int mode, double* grid_out,
@@ -237,11 +249,13 @@ hipError_t launch_analysis(const GroupView& g, const AnalOutput& out, hipStream_
 hipError_t launch_ring_adjoint(const GroupView& g, const FftPlan& plan, hipStream_t s);
 hipError_t launch_ring_project(const GroupView& g, const FftPlan& plan, const double* u_grid,
                                hipStream_t s);
-hipError_t launch_synthesis_adjoint(const GroupView& g, hipStream_t s);
-hipError_t launch_prep_adjoint(const GroupView& g, double2* alpha_bar, hipStream_t s);
-hipError_t launch_prep_step_adjoint(const GroupView& g, const StepAdjointArgs& a, hipStream_t s);
-hipError_t launch_synthesis_mb(const GroupView& g, const SynthInput& in, int B, hipStream_t s);
-hipError_t launch_analysis_mb(const GroupView& g, const AnalOutput& out, int B, hipStream_t s);
+hipError_t launch_adjoint_pair(const GroupView& g, double2* alpha_bar, const StepAdjointArgs* sa,
+                               bool projection, hipStream_t s);
+hipError_t launch_pair_seeds(const GroupView& g, int ks, const double2* rec_lo, const double2* pq0,
+                             double2* seeds, hipStream_t s);
+hipError_t launch_synthesis_pair(const GroupView& g, const SynthInput& in, int mode,
+                                 hipStream_t s);
+hipError_t launch_analysis_pair(const GroupView& g, const AnalOutput& out, hipStream_t s);
 hipError_t launch_synthesis_lp(const GroupView& g, const SynthInput& in, int mode, int prec,
                                hipStream_t s);
 hipError_t launch_analysis_lp(const GroupView& g, const AnalOutput& out, int prec, hipStream_t s);
@@ -257,10 +271,9 @@ hipError_t launch_inertial_manifold(const GroupView& g, const double2* n, const 
 hipError_t launch_ndf_correct(const GroupView& g, const NdfArgs& a, hipStream_t s);
 
 // Dynamic LDS of the launches (validated against 64 KiB at init).
-size_t synthesis_lds_bytes(int N, int NF);
+size_t synthesis_lds_bytes(int N);
 size_t ring_lds_bytes(int M);
 size_t analysis_otf_lds_bytes(int nh);
-size_t synthesis_adjoint_lds_bytes(int nh);
 size_t synthesis_lp_lds_bytes(int N);
 size_t split_panel_lp_lds_bytes(int N);
 size_t analysis_lp_lds_bytes(int nh);

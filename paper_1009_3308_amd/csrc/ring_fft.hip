@@ -1023,7 +1023,7 @@ __global__ __launch_bounds__(NT) void k_ring_adj(GroupView g, FftPlan plan) {
 // per ring, the real transforms Ut_m = sum_j u_theta e^{-i m phi_j} and
 // Up_m = sum_j u_phi e^{-i m phi_j} (one complex FFT of u_theta + i u_phi),
 // scaled by c = (2 pi / M) w_p / sin(theta_p) and written to
-// Fbar[b][f][m][lat] as (c Ut, -c Up, 0, 0). The latitude sums and the degree
+// Fbar[b][f][m][lat] as f = 0, 1: c Ut, -c Up. The latitude sums and the degree
 // coupling of d/dtheta are done by the unweighted analysis and the prologue
 // transpose, since conj(Z[l,m]) = lambda^(-1/2) (-i m Pbar / sin, -dPbar/dtheta) e^{-i m phi}
 // and sin(theta) dPbar/dtheta couples degrees l - 1 and l + 1.
@@ -1056,8 +1056,6 @@ __global__ __launch_bounds__(NT) void k_ring_project(GroupView g, FftPlan plan,
     const int64_t mo = (int64_t)m * nlat;
     Fb[mo] = make_double2(h * (zm.x + zc.x), h * (zm.y - zc.y));
     Fb[fstride + mo] = make_double2(-h * (zm.y + zc.y), h * (zm.x - zc.x));
-    Fb[2 * fstride + mo] = make_double2(0.0, 0.0);
-    Fb[3 * fstride + mo] = make_double2(0.0, 0.0);
   }
 }
 

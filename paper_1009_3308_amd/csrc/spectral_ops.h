@@ -168,7 +168,7 @@ __device__ inline void load_degree_inputs(const GroupView& g, const AnalOutput& 
 template <bool NDF = false>
 __device__ inline void finish_degree_from(const GroupView& g, const AnalOutput& out, int b, int m,
                                           int k, double sx, double sy, const double2* in,
-                                          double* nv = nullptr);
+                                          double* nv = nullptr, const double* rs = nullptr);
 
 __device__ inline void finish_degree(const GroupView& g, const AnalOutput& out, int b, int m,
                                      int k, double sx, double sy) {
@@ -179,16 +179,16 @@ __device__ inline void finish_degree(const GroupView& g, const AnalOutput& out, 
 
 // As finish_degree, with the step-update inputs already loaded (load_degree_inputs).
 // NDF (out.mode == ANAL_NDF): nv receives the coefficient's four weighted norm
-// terms (squares).
+// terms (squares). rs: lambda_l^(-1/2) where the caller has it.
 template <bool NDF>
 __device__ inline void finish_degree_from(const GroupView& g, const AnalOutput& out, int b, int m,
                                           int k, double sx, double sy, const double2* in,
-                                          double* nv) {
+                                          double* nv, const double* rs) {
   const int l = m + k;
   const double lam = (double)l * (l + 1);
   double2 n = make_double2(0.0, 0.0);
   if (l >= 1) {
-    const double r = 1.0 / sqrt(lam);
+    const double r = rs ? *rs : 1.0 / sqrt(lam);
     n = make_double2(sx * r, m == 0 ? 0.0 : sy * r);
   }
   const int64_t slot = g.off[b] + coeff_offset(g.N, m) + k;

@@ -16,8 +16,6 @@
 // three-term recurrence in FP64 registers, so the loop is bound by the LDS reads
 // of the panel, which is why the lanes of the four-field modes take one to three
 // latitudes each.
-#include <type_traits>
-
 #include "lane_ops.h"
 #include "spectral_ops.h"
 
@@ -33,9 +31,10 @@ constexpr int kPanelConvPerThread = 10;
 // LDS bound of the kernels keeps N below 680)
 constexpr int kRcPerThread = 3;
 
-// NF fields: per lane 4 NF partial sums (NF fields x (E, O) x (re, im)).
-// The panel [L][NF] double2 is reused afterwards for the cross-wave reduction.
-__host__ __device__ inline int synth_pan_slots(int N, int NF) {
+constexpr int NF = 4;  // fields
+// Per lane 4 NF partial sums (NF fields x (E, O) x (re, im)). The panel
+// [L][NF] double2 is reused afterwards for the cross-wave reduction.
+__host__ __device__ inline int synth_pan_slots(int N) {
   const int pan = NF * (N + 2 + kOtfBatch);  // panel rows plus the padding a batch may read
   const int red = kSynthWaves * 4 * NF * 64 / 2;
   return pan > red ? pan : red;
@@ -43,15 +42,13 @@ __host__ __device__ inline int synth_pan_slots(int N, int NF) {
 
 // LDS: coefficients, panel (reused for the reduction) and the recurrence
 // coefficients of the order.
-size_t synthesis_lds_bytes(int N, int NF) {
-  return sizeof(double2) * (size_t)((N + 3) + synth_pan_slots(N, NF) + N + 2 + kOtfBatch);
+size_t synthesis_lds_bytes(int N) {
+  return sizeof(double2) * (size_t)((N + 3) + synth_pan_slots(N) + N + 2 + kOtfBatch);
 }
 
-// TT: type of the products and of the per-wave accumulation (double for
-// NSE_PREC_FP64; float for NSE_PREC_FP32, where the panel is rounded to FP32 once
-// and each Legendre value before its products); the recurrence and the
-// cross-wave sums are FP64 in both.
-// NF: 4 (nonlinear and grid modes) or 5 (adjoint mode).
+// NSE_PREC_FP32: the panel is rounded to FP32 and each Legendre value before its
+// products, the per-wave sums are FP32; the recurrence and the cross-wave sums are
+// FP64.
 // The Legendre values are continued in registers by the three-term recurrence of
 // eq. (sph_har),
 //   Pbar[l,m] = a(l,m) mu Pbar[l-1,m] - (a(l,m) / a(l-1,m)) Pbar[l-2,m],
@@ -62,7 +59,7 @@ size_t synthesis_lds_bytes(int N, int NF) {
 // R: latitudes per lane (tiles of 64 R latitudes, lane l taking l, l + 64, ...):
 // every panel value read from LDS then serves R latitudes, which is what bounds
 // the loop (the LDS, shared by the four SIMDs).
-template <typename TT, int NF, int R = 1>
+template <int R>
 __global__ __launch_bounds__(kSynthThreads) void k_synthesis(GroupView g, SynthInput in,
                                                               int mode) {
   constexpr int kRed = 4 * NF;
@@ -95,23 +92,7 @@ __global__ __launch_bounds__(kSynthThreads) void k_synthesis(GroupView g, SynthI
   if (gate_closed(g)) return;
   __syncthreads();
   build_panel<NF>(pan, a, N, m, L, mode, in.coriolis, in.stream != 0);
-  if (NF == 5) {
-    // fifth field: lambda^(-1/2) n_bar, l = max(m, 1)..N, real at m = 0 (n_bar formed
-    // here from hbar_out[0] inside the step adjoint)
-    const double2* nb = in.adj + g.off[b] + coeff_offset(N, m);
-    for (int k = threadIdx.x; k < L; k += blockDim.x) {
-      const int l = m + k;
-      double2 v = make_double2(0.0, 0.0);
-      if (l >= 1 && l <= N) {
-        const double lam = (double)l * (l + 1);
-        double r = 1.0 / sqrt(lam);
-        if (in.adj_step) r *= -in.adj_h / (in.adj_c0 + in.adj_h * g.nu[b] * lam);
-        v = make_double2(nb[k].x * r, m == 0 ? 0.0 : nb[k].y * r);
-      }
-      pan[NF * k + 4] = v;
-    }
-  }
-  double2* rc = pan + synth_pan_slots(N, NF);  // [L + kOtfBatch] (a(l,m), a(l,m) / a(l-1,m))
+  double2* rc = pan + synth_pan_slots(N);  // [L + kOtfBatch] (a(l,m), a(l,m) / a(l-1,m))
 #pragma unroll
   for (int i = 0; i < kRcPerThread; ++i) {
     const int k = threadIdx.x + i * kSynthThreads;
@@ -121,8 +102,7 @@ __global__ __launch_bounds__(kSynthThreads) void k_synthesis(GroupView g, SynthI
   // FP32 products read the panel as float2, rounded once per entry and written
   // in place over the front of the FP64 panel (every entry is read into
   // registers before any is overwritten); the padding entries become zero
-  using TT2 = typename std::conditional<std::is_same<TT, float>::value, float2, double2>::type;
-  if (std::is_same<TT, float>::value) {
+  {
     constexpr int kPer = kPanelConvPerThread;
     const int npan = NF * (L + kOtfBatch);
     double2 v[kPer];
@@ -140,7 +120,7 @@ __global__ __launch_bounds__(kSynthThreads) void k_synthesis(GroupView g, SynthI
     }
     __syncthreads();
   }
-  const TT2* pt = reinterpret_cast<const TT2*>(pan);
+  const float2* pt = reinterpret_cast<const float2*>(pan);
 
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
@@ -149,11 +129,11 @@ __global__ __launch_bounds__(kSynthThreads) void k_synthesis(GroupView g, SynthI
   const int chunk = ((L + 2 * kSynthWaves - 1) / (2 * kSynthWaves)) * 2;
   const int k0 = wave * chunk;
   const int k1 = min(L, k0 + chunk);
-  TT acc[R][kRed];
+  float acc[R][kRed];
 #pragma unroll
   for (int r = 0; r < R; ++r)
 #pragma unroll
-    for (int i = 0; i < kRed; ++i) acc[r][i] = TT(0);
+    for (int i = 0; i < kRed; ++i) acc[r][i] = 0.f;
   if (k0 < k1) {
     // seeds: the table rows k0 and k0 + 1 (k0 even), then the recurrence
     const double* t = g.T1 + t1_order_offset(N, m, nh);
@@ -170,16 +150,16 @@ __global__ __launch_bounds__(kSynthThreads) void k_synthesis(GroupView g, SynthI
     }
 #pragma unroll
     for (int f = 0; f < NF; ++f) {
-      const TT2 A0 = pt[NF * k0 + f];
-      TT2 A1 = pt[NF * k0 + f];
+      const float2 A0 = pt[NF * k0 + f];
+      float2 A1 = pt[NF * k0 + f];
       if (k0 + 1 < k1) A1 = pt[NF * (k0 + 1) + f];
-      else A1.x = A1.y = TT(0);
+      else A1.x = A1.y = 0.f;
 #pragma unroll
       for (int r = 0; r < R; ++r) {
-        acc[r][4 * f + 0] = fma((TT)P2[r], A0.x, acc[r][4 * f + 0]);
-        acc[r][4 * f + 1] = fma((TT)P2[r], A0.y, acc[r][4 * f + 1]);
-        acc[r][4 * f + 2] = fma((TT)P1[r], A1.x, acc[r][4 * f + 2]);
-        acc[r][4 * f + 3] = fma((TT)P1[r], A1.y, acc[r][4 * f + 3]);
+        acc[r][4 * f + 0] = fma((float)P2[r], A0.x, acc[r][4 * f + 0]);
+        acc[r][4 * f + 1] = fma((float)P2[r], A0.y, acc[r][4 * f + 1]);
+        acc[r][4 * f + 2] = fma((float)P1[r], A1.x, acc[r][4 * f + 2]);
+        acc[r][4 * f + 3] = fma((float)P1[r], A1.y, acc[r][4 * f + 3]);
       }
     }
     // batches of kB degrees: the batch's coefficient pairs and panel entries are
@@ -188,7 +168,7 @@ __global__ __launch_bounds__(kSynthThreads) void k_synthesis(GroupView g, SynthI
     // are padding and are not accumulated)
     for (int kb = k0 + 2; kb < k1; kb += kB) {
       double2 c[kB];
-      TT2 A[kB][NF];
+      float2 A[kB][NF];
 #pragma unroll
       for (int u = 0; u < kB; ++u) {
         c[u] = rc[kb + u];
@@ -208,7 +188,7 @@ __global__ __launch_bounds__(kSynthThreads) void k_synthesis(GroupView g, SynthI
         for (int u = 0; u < kB; ++u) {
           if (kb + u < k1) {
             const int par = (u & 1) * 2;  // kb is even
-            const TT vt = (TT)v[u];
+            const float vt = (float)v[u];
 #pragma unroll
             for (int f = 0; f < NF; ++f) {
               acc[r][4 * f + par + 0] = fma(vt, A[u][f].x, acc[r][4 * f + par + 0]);
@@ -223,7 +203,6 @@ __global__ __launch_bounds__(kSynthThreads) void k_synthesis(GroupView g, SynthI
   // panel; wave w finishes fields w, w+4, ... of its 64 latitudes
   double* red = reinterpret_cast<double*>(pan);  // [wave][kRed][64]
   const int nf = (mode == SYNTH_GRID) ? 3 : NF;
-  double2* Fout = (NF == 5) ? g.Fa : g.F;
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     __syncthreads();
@@ -241,7 +220,7 @@ __global__ __launch_bounds__(kSynthThreads) void k_synthesis(GroupView g, SynthI
           orr += red[(w * kRed + 4 * f + 2) * 64 + lane];
           oi += red[(w * kRed + 4 * f + 3) * 64 + lane];
         }
-        double2* out = Fout + ((int64_t)(b * NF + f) * (N + 1) + m) * nlat;
+        double2* out = g.F + ((int64_t)(b * NF + f) * (N + 1) + m) * nlat;
         out[p] = make_double2(er + orr, ei + oi);
         const int ps = nlat - 1 - p;
         if (ps != p) out[ps] = make_double2(er - orr, ei - oi);
@@ -270,17 +249,12 @@ __global__ __launch_bounds__(kSynthThreads) void k_synthesis(GroupView g, SynthI
 // differences as its input, the first latitude tile stores y0, psi and the
 // iterate, and the analysis epilogue of the slot stores the differences (the
 // tiles of an order all read the old ones here).
-// NF = 5 (SYNTH_ADJ, the adjoint's synthesis): a fifth field
-// f4 = sum lambda^(-1/2) n_bar[l] Pbar (Pbar terms, zero at l = 0, real at m = 0,
-// times -h / (c_0 + h nu lambda) inside the step adjoint) written with the four
-// forward fields to Fa.
-template <int R, int NF, bool STEP>
+template <bool STEP>
 __device__ __forceinline__ void synthesis_adv_body(const GroupView& g, const SynthInput& in,
                                                    const NdfArgs* na, const NdfStepArgs* ns) {
-  static_assert(NF == 4 || NF == 5, "four fields, or five in the adjoint mode");
-  static_assert(!STEP || NF == 4, "the controller step rides on the nonlinear synthesis");
+  constexpr int R = 1;  // latitudes per lane
   constexpr int kRed = 4 * NF;
-  constexpr int kB = (R == 1) ? kOtfBatch : 2;  // degrees per recurrence batch
+  constexpr int kB = kOtfBatch;  // degrees per recurrence batch
   const int N = g.N, nh = g.nh, nlat = g.nlat;
   const int ntile = (nh + 64 * R - 1) / (64 * R);
   // the tiles of one order run on one XCD and share its L2 for the order's
@@ -296,7 +270,6 @@ __device__ __forceinline__ void synthesis_adv_body(const GroupView& g, const Syn
   double2* za = psi + (N + 1 + kOtfBatch);  // [K + kOtfBatch] zeta_a[l] = lambda_l psi[l]
   double2* rc = za + (N + 1 + kOtfBatch);   // [K + kOtfBatch] (a(l,m), a(l,m) / a(l-1,m))
   double2* dc = rc + (N + 1 + kOtfBatch);   // [K + kOtfBatch] ((2l+1) e(l), l)
-  double2* n5 = dc + (N + 1 + kOtfBatch);   // NF = 5: [K + kOtfBatch] lambda^(-1/2) n_bar[l]
 
   const int lane = threadIdx.x & 63;
   // the wave index is uniform across the wave, so the degree bounds are scalar
@@ -449,17 +422,6 @@ __device__ __forceinline__ void synthesis_adv_body(const GroupView& g, const Syn
     za[k] = make_double2(lam * ps.x, lam * ps.y);
     rc[k] = c;
     dc[k] = make_double2(e.x, (k < K) ? dl : 0.0);
-    if constexpr (NF == 5) {
-      // fifth field: lambda^(-1/2) n_bar, l = max(m, 1)..N, real at m = 0
-      double2 w = make_double2(0.0, 0.0);
-      if (k < K && l >= 1) {
-        const double2 nb = in.adj[base + k];
-        double r = e.y;
-        if (in.adj_step) r *= -in.adj_h / (in.adj_c0 + in.adj_h * g.nu[b] * lam);
-        w = make_double2(nb.x * r, m == 0 ? 0.0 : nb.y * r);
-      }
-      n5[k] = w;
-    }
   }
   // an ended attempt of a device-controlled run: checked once the loads are in
   // flight (nothing is stored before this barrier), so the flag costs no wait
@@ -481,11 +443,6 @@ __device__ __forceinline__ void synthesis_adv_body(const GroupView& g, const Syn
       const double2 ps = psi[0], zz = za[0], d = dc[0];
 #pragma unroll
       for (int r = 0; r < R; ++r) {
-        if constexpr (NF == 5) {
-          const double2 w = n5[0];
-          acc[r][16] = fma(P1[r], w.x, acc[r][16]);
-          acc[r][17] = fma(P1[r], w.y, acc[r][17]);
-        }
         const double D = fma(d.y, XP1[r], -d.x * P2[r]);
         acc[r][0] = fma(P1[r], ps.x, acc[r][0]);
         acc[r][1] = fma(P1[r], ps.y, acc[r][1]);
@@ -511,14 +468,13 @@ __device__ __forceinline__ void synthesis_adv_body(const GroupView& g, const Syn
     // degrees kbs .. k1 - 1 in batches of kB (kb odd: degree kb + u is odd for
     // even u)
     for (int kb = kbs; kb < k1; kb += kB) {
-      double2 c[kB], ps[kB], zz[kB], d[kB], w5[kB];
+      double2 c[kB], ps[kB], zz[kB], d[kB];
 #pragma unroll
       for (int u = 0; u < kB; ++u) {
         c[u] = rc[kb + u];
         ps[u] = psi[kb + u];
         zz[u] = za[kb + u];
         d[u] = dc[kb + u];
-        if constexpr (NF == 5) w5[u] = n5[kb + u];
       }
 #pragma unroll
       for (int r = 0; r < R; ++r) {
@@ -541,10 +497,6 @@ __device__ __forceinline__ void synthesis_adv_body(const GroupView& g, const Syn
           acc[r][9 + qd] = fma(D, zz[u].y, acc[r][9 + qd]);
           acc[r][12 + qp] = fma(v, zz[u].x, acc[r][12 + qp]);
           acc[r][13 + qp] = fma(v, zz[u].y, acc[r][13 + qp]);
-          if constexpr (NF == 5) {
-            acc[r][16 + qp] = fma(v, w5[u].x, acc[r][16 + qp]);
-            acc[r][17 + qp] = fma(v, w5[u].y, acc[r][17 + qp]);
-          }
         }
       }
     }
@@ -574,7 +526,7 @@ __device__ __forceinline__ void synthesis_adv_body(const GroupView& g, const Syn
         vn = make_double2(-dm * vn.y, dm * vn.x);
         vs = make_double2(-dm * vs.y, dm * vs.x);
       }
-      double2* out = (NF == 5 ? g.Fa : g.F) + ((int64_t)(b * NF + f) * (N + 1) + m) * nlat;
+      double2* out = g.F + ((int64_t)(b * NF + f) * (N + 1) + m) * nlat;
       out[p] = vn;
       const int psouth = nlat - 1 - p;
       if (psouth != p) out[psouth] = vs;
@@ -582,70 +534,42 @@ __device__ __forceinline__ void synthesis_adv_body(const GroupView& g, const Syn
   }
 }
 
-template <int R, int NF>
 __global__ __launch_bounds__(kSynthThreads) void k_synthesis_adv(GroupView g, SynthInput in) {
-  synthesis_adv_body<R, NF, false>(g, in, nullptr, nullptr);
+  synthesis_adv_body<false>(g, in, nullptr, nullptr);
 }
 
 __global__ __launch_bounds__(kSynthThreads) void k_synthesis_adv_step(GroupView g, SynthInput in,
                                                                       NdfArgs a, NdfStepArgs st) {
-  synthesis_adv_body<1, 4, true>(g, in, &a, &st);
+  synthesis_adv_body<true>(g, in, &a, &st);
 }
 
-size_t synthesis_adv_lds_bytes(int N, int nf) {
-  const int arrays = nf * (N + 1 + kOtfBatch);
-  const int red = kSynthWaves * 4 * nf * 64 / 2;
+size_t synthesis_adv_lds_bytes(int N) {
+  const int arrays = NF * (N + 1 + kOtfBatch);
+  const int red = kSynthWaves * 4 * NF * 64 / 2;
   return sizeof(double2) * (size_t)(arrays > red ? arrays : red);
 }
 
-// Four-field recurrence synthesis with TT products: one to three latitudes per
-// lane by grid size (measured best: R = 3 at nh = 384, R = 1 at nh <= 192, where
-// the grid has too few tiles for more).
-template <typename TT>
-hipError_t launch_synthesis_otf4(const GroupView& g, const SynthInput& in, int mode,
-                                 hipStream_t s) {
-  dim3 block(kSynthThreads);
-  const size_t lds = synthesis_lds_bytes(g.N, 4);
-  if (g.nh >= 384 && g.nh % 192 == 0) {
-    const int nt = g.nh / 192;
-    dim3 grid3(xcd_grid((g.N + 1) * nt, nt), g.nb);
-    hipLaunchKernelGGL((k_synthesis<TT, 4, 3>), grid3, block, lds, s, g, in, mode);
-  } else if (g.nh >= 256) {
-    const int nt = (g.nh + 127) / 128;
-    dim3 grid2(xcd_grid((g.N + 1) * nt, nt), g.nb);
-    hipLaunchKernelGGL((k_synthesis<TT, 4, 2>), grid2, block, lds, s, g, in, mode);
-  } else {
-    const int nt = (g.nh + 63) / 64;
-    dim3 grid(xcd_grid((g.N + 1) * nt, nt), g.nb);
-    hipLaunchKernelGGL((k_synthesis<TT, 4>), grid, block, lds, s, g, in, mode);
-  }
-  return hipGetLastError();
-}
-
+// FP32: one to three latitudes per lane by grid size (measured best: R = 3 at nh =
+// 384, R = 1 at nh <= 192, where the grid has too few tiles for more). FP64, the
+// nonlinear mode of single members on grids below nh = 192: the derivative form.
 hipError_t launch_synthesis(const GroupView& g, const SynthInput& in, int mode, hipStream_t s) {
-  dim3 block(kSynthThreads);
-  const int ntile = (g.nh + 63) / 64;
-  dim3 grid(xcd_grid((g.N + 1) * ntile, ntile), g.nb);
-  if (mode == SYNTH_ADJ && g.nh < 256) {
-    // the derivative form with the fifth field (T255 adjoint: 14.5 us with the
-    // panel form, 12.0 us; 78 VGPRs against 144)
-    hipLaunchKernelGGL((k_synthesis_adv<1, 5>), grid, block, synthesis_adv_lds_bytes(g.N, 5), s,
-                       g, in);
-  } else if (mode == SYNTH_ADJ)
-    hipLaunchKernelGGL((k_synthesis<double, 5>), grid, block,
-                       synthesis_lds_bytes(g.N, 5), s, g, in, mode);
-  else if (g.precision == NSE_PREC_FP32) {
-    if (4 * (g.N + 2 + kOtfBatch) > kPanelConvPerThread * kSynthThreads) return hipErrorInvalidValue;
-    return launch_synthesis_otf4<float>(g, in, mode, s);
-  } else if (mode == SYNTH_NONLINEAR && g.nh < 256) {
-    // one latitude per lane: the loop is bound by the LDS reads, and the
-    // derivative-on-Legendre form reads three values per degree instead of five
-    // (T255: 14.2 -> 13.8 us); with two or three latitudes per lane the panel
-    // form's fewer FMAs per latitude win (T511: 38.6 us against 44.4 us)
-    hipLaunchKernelGGL((k_synthesis_adv<1, 4>), grid, block, synthesis_adv_lds_bytes(g.N, 4), s, g,
-                       in);
-  } else {
-    return launch_synthesis_otf4<double>(g, in, mode, s);
+  const dim3 block(kSynthThreads);
+  if (g.precision == NSE_PREC_FP64) {
+    const int nt = (g.nh + 63) / 64;
+    const dim3 grid(xcd_grid((g.N + 1) * nt, nt), g.nb);
+    if (mode != SYNTH_NONLINEAR || !g.T1) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_synthesis_adv, grid, block, synthesis_adv_lds_bytes(g.N), s, g, in);
+    return hipGetLastError();
+  }
+  if (4 * (g.N + 2 + kOtfBatch) > kPanelConvPerThread * kSynthThreads) return hipErrorInvalidValue;
+  const size_t lds = synthesis_lds_bytes(g.N);
+  const int R = g.nh >= 384 && g.nh % 192 == 0 ? 3 : (g.nh >= 256 ? 2 : 1);
+  const int nt = (g.nh + 64 * R - 1) / (64 * R);
+  const dim3 grid(xcd_grid((g.N + 1) * nt, nt), g.nb);
+  switch (R) {
+    case 3: hipLaunchKernelGGL(k_synthesis<3>, grid, block, lds, s, g, in, mode); break;
+    case 2: hipLaunchKernelGGL(k_synthesis<2>, grid, block, lds, s, g, in, mode); break;
+    default: hipLaunchKernelGGL(k_synthesis<1>, grid, block, lds, s, g, in, mode); break;
   }
   return hipGetLastError();
 }
@@ -664,7 +588,7 @@ hipError_t launch_synthesis_step(const GroupView& g, const SynthInput& in, const
   if (!synthesis_takes_step(g)) return hipErrorInvalidValue;
   const int ntile = (g.nh + 63) / 64;
   dim3 grid(xcd_grid((g.N + 1) * ntile, ntile), g.nb);
-  const size_t lds = synthesis_adv_lds_bytes(g.N, 4) + sizeof(NdfCtl) + 6 * sizeof(double);
+  const size_t lds = synthesis_adv_lds_bytes(g.N) + sizeof(NdfCtl) + 6 * sizeof(double);
   hipLaunchKernelGGL(k_synthesis_adv_step, grid, dim3(kSynthThreads), lds, s, g, in, a, st);
   return hipGetLastError();
 }
