@@ -130,6 +130,11 @@ struct GraphEntry {
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
   uint64_t used = 0;  // last use, for least-recently-used eviction
+
+  bool same(const GraphEntry& o) const {
+    return kind == o.kind && hist == o.hist && forcing == o.forcing && aux == o.aux && n == o.n &&
+           i0 == o.i0 && i1 == o.i1;
+  }
 };
 
 }  // namespace
@@ -153,6 +158,8 @@ struct nse_ctx {
   // captured step chunks, at most kGraphCache (history, forcing) pairs
   std::vector<GraphEntry> graphs;
   uint64_t graph_clock = 0;
+  // the last sequences run without a graph (worth_capture)
+  std::vector<GraphEntry> seen;
   // per-kernel timing: every launch is issued `profile_repeat` times between
   // one pair of events (0 = timing off)
   bool profiling = false;
@@ -300,6 +307,7 @@ void drop_graphs(nse_ctx* c) {
   if (!c->graphs.empty() && c->stream) (void)hipStreamSynchronize(c->stream);
   for (auto& g : c->graphs) destroy_graph(g);
   c->graphs.clear();
+  c->seen.clear();
 }
 
 template <typename T>
@@ -788,6 +796,7 @@ nse_status enqueue_nonlinear_adjoint(nse_ctx* c, SynthInput in, const double2* n
 
 constexpr int kSlotsPerGraph = 16;       // sweep slots in one captured sequence (even)
 constexpr int kMaxGraphsPerBatch = 32;   // sequences enqueued between two waits
+constexpr int kFirstBatch = 2;           // and before the first of a call
 static_assert(kSlotsPerGraph % 2 == 0, "slots alternate between two state buffers");
 
 void drop_attempt_graph(nse_ctx* c);
@@ -1118,6 +1127,7 @@ nse_status advance_device(nse_ctx* c) {
   *c->h_ctl = k;
   NSE_HIP(c, hipMemcpyAsync(c->d_ctl, c->h_ctl, sizeof(NdfCtl), hipMemcpyHostToDevice, c->stream));
   long long read = k.nlog;
+  int run = 0;  // sequences enqueued by this call
   std::vector<nse_adaptive_record> recs;
   for (;;) {
     // enough sweeps for the remaining interval at the current step and the mean
@@ -1126,8 +1136,12 @@ nse_status advance_device(nse_ctx* c) {
     const double attempts = std::max<double>(1.0, (double)(k.nlog > 0 ? k.nlog : 1));
     const double per = k.nlog > 0 ? (double)(k.evaluations - 1) / attempts : (double)k.K;
     const double need = ((k.t_end - k.t) / k.h * 1.1 + 1.0) * std::max(1.0, per);
+    // `need` counts on the current step, which grows by orders of magnitude over the
+    // first attempts: a batch is at most half of what has run so far (an idle slot
+    // costs about a quarter of a working one, a wait as much as two)
     int graphs = (int)std::min<double>(kMaxGraphsPerBatch, std::ceil(need / kSlotsPerGraph));
-    graphs = std::max(graphs, 1);
+    graphs = std::max(1, std::min(graphs, std::max(kFirstBatch, run / 2)));
+    run += graphs;
     for (int i = 0; i < graphs; ++i) NSE_HIP(c, hipGraphLaunch(c->ad_exec, c->stream));
     NSE_HIP(c, hipMemcpyAsync(c->h_ctl, c->d_ctl, sizeof(NdfCtl), hipMemcpyDeviceToHost,
                               c->stream));
@@ -1453,18 +1467,40 @@ nse_status nse_nonlinear(nse_ctx* ctx, const double* alpha, double* n_out) {
 
 namespace {
 
+// The graph kept for the sequence `key`, or null.
+static GraphEntry* find_graph(nse_ctx* ctx, const GraphEntry& key) {
+  for (auto& g : ctx->graphs)
+    if (g.same(key)) {
+      g.used = ++ctx->graph_clock;
+      return &g;
+    }
+  return nullptr;
+}
+
+// Whether a sequence that has no graph yet should be captured: capturing and
+// instantiating takes longer than launching the same kernels one by one (20 steps of
+// the T255 adjoint: about 0.5 against 0.25 ms of host time), so it pays only for a
+// sequence on the same buffers as a recent one. Callers that hand in new buffers
+// every time (a gradient's trajectory) run without graphs.
+static bool worth_capture(nse_ctx* ctx, const GraphEntry& key) {
+  for (auto it = ctx->seen.begin(); it != ctx->seen.end(); ++it)
+    if (it->same(key)) {
+      ctx->seen.erase(it);
+      return true;
+    }
+  if (ctx->seen.size() >= kGraphCache) ctx->seen.erase(ctx->seen.begin());
+  ctx->seen.push_back(key);
+  return false;
+}
+
 // The executable graph of kGraphChunk fixed-coefficient steps (global index
-// k > order) on (h, f), captured on first use; the least recently used entry is
-// dropped once kGraphCache pairs are held.
+// k > order) on (h, f), captured; the least recently used entry is dropped once
+// kGraphCache are held.
 static nse_status step_graph(nse_ctx* ctx, double2* h, const double2* f, int64_t k,
                              hipGraphExec_t* out) {
-  for (auto& g : ctx->graphs) {
-    if (g.kind == 0 && g.hist == (const void*)h && g.forcing == (const void*)f) {
-      g.used = ++ctx->graph_clock;
-      *out = g.exec;
-      return NSE_OK;
-    }
-  }
+  GraphEntry ge;
+  ge.hist = h;
+  ge.forcing = f;
   if (ctx->graphs.size() >= kGraphCache) {
     auto lru = std::min_element(ctx->graphs.begin(), ctx->graphs.end(),
                                 [](const GraphEntry& a, const GraphEntry& b) { return a.used < b.used; });
@@ -1473,9 +1509,6 @@ static nse_status step_graph(nse_ctx* ctx, double2* h, const double2* f, int64_t
     destroy_graph(*lru);
     ctx->graphs.erase(lru);
   }
-  GraphEntry ge;
-  ge.hist = h;
-  ge.forcing = f;
   NSE_HIP(ctx, hipStreamBeginCapture(ctx->stream, hipStreamCaptureModeThreadLocal));
   nse_status s = NSE_OK;
   for (int i = 0; i < kGraphChunk && s == NSE_OK; ++i) s = enqueue_step(ctx, h, f, k + i);
@@ -1518,14 +1551,18 @@ nse_status nse_step(nse_ctx* ctx, double* hist, const double* forcing, int64_t s
   }
   const bool graph =
       (ctx->params.flags & NSE_FLAG_GRAPH) && ctx->stream != nullptr && !ctx->profiling;
-  if (graph && k < end) {
-    // the first call that reaches the fixed-coefficient steps captures the chunk
-    // graph even when fewer than a chunk of steps remain, so that the capture
-    // cost falls on that call and not on the later calls that replay it
+  if (graph && end - k >= kGraphChunk) {
+    GraphEntry key;
+    key.hist = h;
+    key.forcing = f;
     hipGraphExec_t exec = nullptr;
-    nse_status s = step_graph(ctx, h, f, k, &exec);
-    if (s != NSE_OK) return s;
-    for (; end - k >= kGraphChunk; k += kGraphChunk)
+    if (GraphEntry* g = find_graph(ctx, key))
+      exec = g->exec;
+    else if (end - k >= 4 * kGraphChunk || worth_capture(ctx, key)) {
+      nse_status s = step_graph(ctx, h, f, k, &exec);
+      if (s != NSE_OK) return s;
+    }
+    for (; exec && end - k >= kGraphChunk; k += kGraphChunk)
       NSE_HIP(ctx, hipGraphLaunch(exec, ctx->stream));
   }
   for (; k < end; ++k) {
@@ -1617,21 +1654,27 @@ nse_status enqueue_adjoint_sweep(nse_ctx* ctx, const double2* tr, int64_t n, int
   return NSE_OK;
 }
 
-// Runs `enqueue` (the steps i0 .. i1 - 1 of a trajectory sequence) from a
-// captured graph kept under (kind, traj, aux, forcing, n, i0, i1); captured on
-// the context's private stream (the context stream may be the null stream).
+// Runs `enqueue` (the steps i0 .. i1 - 1 of a trajectory sequence), from a captured
+// graph kept under (kind, traj, aux, forcing, n, i0, i1) once the same sequence has
+// come before; captured on the context's private stream (the context stream may be
+// the null stream).
 template <typename F>
 nse_status run_sequence_graph(nse_ctx* ctx, int kind, const void* traj, const void* aux,
                                      const void* forcing, int64_t n, int64_t i0, int64_t i1,
                                      F&& enqueue) {
-  for (auto& g : ctx->graphs) {
-    if (g.kind == kind && g.hist == traj && g.aux == aux && g.forcing == forcing && g.n == n &&
-        g.i0 == i0 && g.i1 == i1) {
-      g.used = ++ctx->graph_clock;
-      NSE_HIP(ctx, hipGraphLaunch(g.exec, ctx->stream));
-      return NSE_OK;
-    }
+  GraphEntry ge;
+  ge.kind = kind;
+  ge.hist = traj;
+  ge.aux = aux;
+  ge.forcing = forcing;
+  ge.n = n;
+  ge.i0 = i0;
+  ge.i1 = i1;
+  if (GraphEntry* g = find_graph(ctx, ge)) {
+    NSE_HIP(ctx, hipGraphLaunch(g->exec, ctx->stream));
+    return NSE_OK;
   }
+  if (!worth_capture(ctx, ge)) return enqueue();
   if (ctx->graphs.size() >= kGraphCache) {
     auto lru = std::min_element(ctx->graphs.begin(), ctx->graphs.end(),
                                 [](const GraphEntry& a, const GraphEntry& b) { return a.used < b.used; });
@@ -1641,14 +1684,6 @@ nse_status run_sequence_graph(nse_ctx* ctx, int kind, const void* traj, const vo
   }
   if (!ctx->cap_stream)
     NSE_HIP(ctx, hipStreamCreateWithFlags(&ctx->cap_stream, hipStreamNonBlocking));
-  GraphEntry ge;
-  ge.kind = kind;
-  ge.hist = traj;
-  ge.aux = aux;
-  ge.forcing = forcing;
-  ge.n = n;
-  ge.i0 = i0;
-  ge.i1 = i1;
   const hipStream_t user_stream = ctx->stream;
   ctx->stream = ctx->cap_stream;
   nse_status s = NSE_OK;
