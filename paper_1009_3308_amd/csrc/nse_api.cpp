@@ -1279,10 +1279,9 @@ nse_status nse_sphere_init(const nse_member* members, int32_t n_members, const n
       snprintf(buf, sizeof buf, "member %d: nlat must be >= 0", i);
       return init_fail(NSE_ERR_ARG, buf);
     }
-    FftPlan plan{};
     if (m.nlat == 0) {
       int nl = min_nlat(m.N);
-      while (2 * nl <= kMaxM && !fft_factor(2 * nl, plan)) ++nl;
+      while (2 * nl <= kMaxM && !fft_length(2 * nl)) ++nl;
       m.nlat = nl;
     } else if (2 * (int64_t)m.nlat < 3 * (int64_t)m.N + 2) {
       snprintf(buf, sizeof buf,
@@ -1290,12 +1289,12 @@ nse_status nse_sphere_init(const nse_member* members, int32_t n_members, const n
                2 * m.nlat, 3 * m.N + 2);
       return init_fail(NSE_ERR_ARG, buf);
     }
-    if (2 * (int64_t)m.nlat > kMaxM || !fft_factor(2 * m.nlat, plan)) {
+    if (2 * (int64_t)m.nlat > kMaxM || !fft_length(2 * m.nlat)) {
       snprintf(buf, sizeof buf,
                "member %d: M = %d must be <= %d and factor into 2, 3 and 5", i, 2 * m.nlat, kMaxM);
       return init_fail(NSE_ERR_UNSUPPORTED, buf);
     }
-    if (synthesis_lds_bytes(m.N) > 65536 || ring_lds_bytes(2 * m.nlat) > 65536 ||
+    if (synthesis_lds_bytes(m.N) > 65536 ||
         analysis_otf_lds_bytes((m.nlat + 1) / 2) > 65536 || synthesis_lp_lds_bytes(m.N) > 65536 ||
         split_panel_lp_lds_bytes(m.N) > 65536 ||
         analysis_lp_lds_bytes((m.nlat + 1) / 2) > 65536) {
@@ -1325,7 +1324,7 @@ nse_status nse_sphere_init(const nse_member* members, int32_t n_members, const n
       g.precision = P.precision;
       g.N = mem[i].N;
       g.nlat = mem[i].nlat;
-      fft_factor(2 * g.nlat, g.plan);
+      g.plan = fft_plan(2 * g.nlat);
       c->groups.push_back(g);
       gi = (int)c->groups.size() - 1;
     }

@@ -14,7 +14,6 @@ namespace nse {
 
 constexpr int kMaxSources = 6;   // predictor terms of NDF_5 (q + 1 <= 6)
 constexpr int kMaxStepCoef = 7;  // c_0 .. c_{q+1} of NDF_5
-constexpr int kMaxRadices = 16;
 constexpr int kMaxM = 1536;      // largest supported longitude count (ring LDS <= 64 KiB)
 
 // Linear work item of block `bid` such that the blocks the dispatcher places on one
@@ -115,11 +114,42 @@ __device__ inline bool gate_closed(const GroupView& g) {
   return g.gate && __hip_atomic_load(g.gate, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0;
 }
 
+// In-place mixed-radix transform of length M: stage s works on blocks of radix[s] J[s]
+// positions (J[-1] = M, J[last] = 1). In LDS, pad0 free slots follow every J[0]
+// positions and pad1 every J[1].
+constexpr int kMaxStages = 4;
+constexpr int kMaxLastRadix = 6;
 struct FftPlan {
   int nstages;
-  int radix[kMaxRadices];
-  int ns_log2[kMaxRadices];  // log2 of the stride Ns before each stage, -1 if not a power of 2
+  int pad0, pad1;
+  int len;                       // LDS slots of one array
+  int radix[kMaxStages], J[kMaxStages];
+  int per[kMaxStages];           // butterflies M / radix
+  int step[kMaxStages];          // twiddle step M / (radix J)
+  unsigned mj[kMaxStages], mper[kMaxStages], mr[kMaxStages];  // 2^21 / (J, per, radix) + 1
 };
+struct FftRadices {
+  int r[kMaxStages];
+};
+__host__ __device__ constexpr FftPlan make_plan(int M, FftRadices f, int n, int pad0, int pad1) {
+  FftPlan p{};
+  p.nstages = n;
+  p.pad0 = pad0;
+  p.pad1 = pad1;
+  for (int s = 0, L = M; s < n; ++s) {
+    const int R = f.r[s];
+    p.radix[s] = R;
+    p.J[s] = L / R;
+    p.per[s] = M / R;
+    p.step[s] = M / L;
+    p.mj[s] = (1u << 21) / (L / R) + 1;
+    p.mper[s] = (1u << 21) / (M / R) + 1;
+    p.mr[s] = (1u << 21) / R + 1;
+    L /= R;
+  }
+  p.len = M + pad0 * p.radix[0] + pad1 * (M / p.J[1]);
+  return p;
+}
 
 // The history update that ends the adjoint of one NDF step (eq. (ode_disc)
 // transposed), from the result alpha_bar of its nonlinear adjoint:
@@ -272,7 +302,6 @@ hipError_t launch_ndf_correct(const GroupView& g, const NdfArgs& a, hipStream_t 
 
 // Dynamic LDS of the launches (validated against 64 KiB at init).
 size_t synthesis_lds_bytes(int N);
-size_t ring_lds_bytes(int M);
 size_t analysis_otf_lds_bytes(int nh);
 size_t synthesis_lp_lds_bytes(int N);
 size_t split_panel_lp_lds_bytes(int N);
@@ -280,6 +309,7 @@ size_t analysis_lp_lds_bytes(int nh);
 
 // Host numerics.
 void gauss_legendre(int n, std::vector<double>& mu, std::vector<double>& w);
-bool fft_factor(int M, FftPlan& plan);
+bool fft_length(int M);
+FftPlan fft_plan(int M);
 
 }  // namespace nse

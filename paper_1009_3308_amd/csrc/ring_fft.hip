@@ -1,9 +1,8 @@
 // Longitude transforms and the grid product (Section 4.2: FFT in the
 // azimuthal direction at the M equispaced longitudes of eq. (quadrule)).
 //
-// One workgroup per latitude ring. Two real fields share one complex FFT: for
-// fields a, b with Fourier coefficients G^a_m, G^b_m, m = 0..N, the length-M
-// sequence
+// Two real fields share one complex FFT: for fields a, b with Fourier coefficients
+// G^a_m, G^b_m, m = 0..N, the length-M sequence
 //   x_m = G^a_m + i G^b_m,  x_{M-m} = conj(G^a_m) + i conj(G^b_m)
 // has the inverse DFT g^a_j + i g^b_j. The pairs are (f0, f1), the two
 // components of the stream-function gradient, and (f2, f3), the two of the
@@ -15,19 +14,21 @@
 // the vorticity gradient is larger than the stream-function gradient by about
 // the degree squared for a spectrum with weight at high degree, so each
 // transform holds two fields of one kind.
-// One forward FFT of q gives its spectrum Q_m; the quadrature factor
+// A forward FFT of q gives its spectrum Q_m; the quadrature factor
 // (2 pi / M) w_p of eq. (quadrule) is applied and Q_m, m = 0..N, is written for
 // the ring (W[m][lat], latitude fastest); the analysis folds the two rings of
 // each latitude pair.
 //
-// The FFT is a mixed-radix (8, 4, 2, 5, 3) Stockham transform done in place in
-// LDS: each stage reads R values at stride M/R into registers, applies
-// twiddles from a half table exp(-2 pi i e / M), e < M/2 (an LDS copy, or the
-// global table through L1 where the LDS is better spent on more rings per CU),
-// performs a radix-R butterfly and writes back in autosort order after a
-// barrier. The two inverse transforms run in the same stages. With the odd
-// radices last, the stage strides are powers of two and the index arithmetic
-// is shifts.
+// A workgroup holds one or two neighbouring rings in LDS. The transforms are
+// mixed-radix and in place, decimated in frequency on the way to the grid and in
+// time on the way back, the second the mirror image of the first: every butterfly
+// reads and writes the same positions, so a stage needs one barrier, and the grid
+// values lie in digit-reversed order, which the product does not mind. The last
+// inverse stage, the product and the first forward stage work on the same R
+// consecutive positions and are one pass in registers. With two rings the two real
+// products go through one forward transform, q_a + i q_b.
+// The plan (radices up to 16, three stages for most M, FftPlan) is chosen on the
+// host for the fewest stages and then for LDS accesses without bank conflicts.
 #include <type_traits>
 
 #include "nse_internal.h"
@@ -41,34 +42,75 @@ __device__ __forceinline__ double2 csub(double2 a, double2 b) { return make_doub
 __device__ __forceinline__ double2 cmul(double2 a, double2 b) {
   return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
 }
-// s * i * a for s = +-1
-__device__ __forceinline__ double2 cmul_si(double2 a, double s) { return make_double2(-s * a.y, s * a.x); }
+// S i a for S = +-1
+template <int S>
+__device__ __forceinline__ double2 cmul_si(double2 a) {
+  return S > 0 ? make_double2(-a.y, a.x) : make_double2(a.y, -a.x);
+}
 
 // cos/sin of 2 pi / 3, 2 pi / 5 and 4 pi / 5 in closed form:
-// sqrt(3)/2, (sqrt(5)-1)/4, -(sqrt(5)+1)/4, sqrt(10+2 sqrt(5))/4, sqrt(10-2 sqrt(5))/4.
+// sqrt(3)/2, (sqrt(5)-1)/4, -(sqrt(5)+1)/4, sqrt(10+2 sqrt(5))/4, sqrt(10-2 sqrt(5))/4;
+// of pi / 4, pi / 8 and 2 pi / 9, 4 pi / 9, 8 pi / 9.
 constexpr double kS3 = 0.86602540378443864676;
 constexpr double kC1 = 0.30901699437494742410;
 constexpr double kC2 = -0.80901699437494742410;
 constexpr double kS1 = 0.95105651629515357212;
 constexpr double kS2 = 0.58778525229247312917;
+constexpr double kH = 0.70710678118654752440;
+constexpr double kC16 = 0.92387953251128675613, kS16 = 0.38268343236508977173;
+constexpr double kC9a = 0.76604444311897803520, kS9a = 0.64278760968653932632;
+constexpr double kC9b = 0.17364817766693034885, kS9b = 0.98480775301220805937;
+constexpr double kC9d = -0.93969262078590838405, kS9d = 0.34202014332566873304;
 
-// DFT of length R with kernel exp(s 2 pi i j k / R), in place.
-template <int R>
-__device__ __forceinline__ void butterfly(double2* v, double s) {
+constexpr int inverse_mod(int a, int m) {
+  for (int x = 1; x < m; ++x)
+    if (a * x % m == 1) return x;
+  return 0;
+}
+
+// DFT of length R with kernel exp(S 2 pi i j k / R), in place.
+template <int R, int S>
+__device__ __forceinline__ void butterfly(double2* v);
+
+// R = A B, A and B coprime (prime-factor map: no twiddles in between).
+template <int A, int B, int S>
+__device__ __forceinline__ void butterfly_coprime(double2* v) {
+  constexpr int R = A * B, ia = B * inverse_mod(B % A, A), ib = A * inverse_mod(A % B, B);
+  double2 w[A][B];
+#pragma unroll
+  for (int b = 0; b < B; ++b) {
+    double2 t[A];
+#pragma unroll
+    for (int a = 0; a < A; ++a) t[a] = v[(B * a + A * b) % R];
+    butterfly<A, S>(t);
+#pragma unroll
+    for (int a = 0; a < A; ++a) w[a][b] = t[a];
+  }
+#pragma unroll
+  for (int a = 0; a < A; ++a) {
+    butterfly<B, S>(w[a]);
+#pragma unroll
+    for (int b = 0; b < B; ++b) v[(ia * a + ib * b) % R] = w[a][b];
+  }
+}
+
+template <int R, int S>
+__device__ __forceinline__ void butterfly(double2* v) {
   if constexpr (R == 2) {
     const double2 a = v[0], b = v[1];
     v[0] = cadd(a, b);
     v[1] = csub(a, b);
   } else if constexpr (R == 3) {
     const double2 t = cadd(v[1], v[2]);
-    const double2 d = cmul_si(csub(v[1], v[2]), s * kS3);
+    const double2 u = csub(v[1], v[2]);
+    const double2 d = cmul_si<S>(make_double2(kS3 * u.x, kS3 * u.y));
     const double2 c = make_double2(v[0].x - 0.5 * t.x, v[0].y - 0.5 * t.y);
     v[0] = cadd(v[0], t);
     v[1] = cadd(c, d);
     v[2] = csub(c, d);
   } else if constexpr (R == 4) {
     const double2 a0 = cadd(v[0], v[2]), a1 = csub(v[0], v[2]);
-    const double2 b0 = cadd(v[1], v[3]), b1 = cmul_si(csub(v[1], v[3]), s);
+    const double2 b0 = cadd(v[1], v[3]), b1 = cmul_si<S>(csub(v[1], v[3]));
     v[0] = cadd(a0, b0);
     v[2] = csub(a0, b0);
     v[1] = cadd(a1, b1);
@@ -79,23 +121,24 @@ __device__ __forceinline__ void butterfly(double2* v, double s) {
     const double2 x0 = v[0];
     const double2 c1 = make_double2(x0.x + kC1 * t1.x + kC2 * t2.x, x0.y + kC1 * t1.y + kC2 * t2.y);
     const double2 c2 = make_double2(x0.x + kC2 * t1.x + kC1 * t2.x, x0.y + kC2 * t1.y + kC1 * t2.y);
-    const double2 s1 = cmul_si(make_double2(kS1 * d1.x + kS2 * d2.x, kS1 * d1.y + kS2 * d2.y), s);
-    const double2 s2 = cmul_si(make_double2(kS2 * d1.x - kS1 * d2.x, kS2 * d1.y - kS1 * d2.y), s);
+    const double2 s1 = cmul_si<S>(make_double2(kS1 * d1.x + kS2 * d2.x, kS1 * d1.y + kS2 * d2.y));
+    const double2 s2 = cmul_si<S>(make_double2(kS2 * d1.x - kS1 * d2.x, kS2 * d1.y - kS1 * d2.y));
     v[0] = cadd(x0, cadd(t1, t2));
     v[1] = cadd(c1, s1);
     v[4] = csub(c1, s1);
     v[2] = cadd(c2, s2);
     v[3] = csub(c2, s2);
+  } else if constexpr (R == 6) {
+    butterfly_coprime<2, 3, S>(v);
   } else if constexpr (R == 8) {
     // radix 8 from two radix-4 transforms of the even and odd samples
     double2 e[4] = {v[0], v[2], v[4], v[6]};
     double2 o[4] = {v[1], v[3], v[5], v[7]};
-    butterfly<4>(e, s);
-    butterfly<4>(o, s);
-    constexpr double h = 0.70710678118654752440;  // 1 / sqrt(2)
-    const double2 o1 = make_double2(h * (o[1].x - s * o[1].y), h * (o[1].y + s * o[1].x));
-    const double2 o2 = cmul_si(o[2], s);
-    const double2 o3 = make_double2(h * (-o[3].x - s * o[3].y), h * (-o[3].y + s * o[3].x));
+    butterfly<4, S>(e);
+    butterfly<4, S>(o);
+    const double2 o1 = make_double2(kH * (o[1].x - S * o[1].y), kH * (o[1].y + S * o[1].x));
+    const double2 o2 = cmul_si<S>(o[2]);
+    const double2 o3 = make_double2(kH * (-o[3].x - S * o[3].y), kH * (-o[3].y + S * o[3].x));
     v[0] = cadd(e[0], o[0]);
     v[4] = csub(e[0], o[0]);
     v[1] = cadd(e[1], o1);
@@ -104,810 +147,409 @@ __device__ __forceinline__ void butterfly(double2* v, double s) {
     v[6] = csub(e[2], o2);
     v[3] = cadd(e[3], o3);
     v[7] = csub(e[3], o3);
-  }
-}
-
-// LDS rows are padded by one slot every 16 complex values so that the strided
-// accesses of the Stockham stages spread over the LDS banks.
-__device__ __forceinline__ int pad(int i) { return i + (i >> 4); }
-__host__ __device__ inline int padded_len(int M) { return M + (M >> 4) + 1; }
-
-// exp(-2 pi i e / M) from the half table tw[0 .. M/2) in LDS.
-__device__ __forceinline__ double2 twiddle(const double2* tw, int e, int half) {
-  if (e < half) return tw[e];
-  const double2 t = tw[e - half];
-  return make_double2(-t.x, -t.y);
-}
-
-// q = j / Ns, k = j mod Ns (shifts when Ns is a power of two).
-__device__ __forceinline__ void split(int j, int Ns, int lg, int& q, int& k) {
-  if (lg >= 0) {
-    q = j >> lg;
-    k = j & (Ns - 1);
+  } else if constexpr (R == 9) {
+    // n = 3 n1 + n2, k = k1 + 3 k2, twiddles exp(S 2 pi i n2 k1 / 9)
+    double2 w[3][3];  // [n2][k1]
+#pragma unroll
+    for (int n2 = 0; n2 < 3; ++n2) {
+      double2 t[3] = {v[n2], v[3 + n2], v[6 + n2]};
+      butterfly<3, S>(t);
+#pragma unroll
+      for (int k = 0; k < 3; ++k) w[n2][k] = t[k];
+    }
+    w[1][1] = cmul(w[1][1], make_double2(kC9a, S * kS9a));
+    w[1][2] = cmul(w[1][2], make_double2(kC9b, S * kS9b));
+    w[2][1] = cmul(w[2][1], make_double2(kC9b, S * kS9b));
+    w[2][2] = cmul(w[2][2], make_double2(kC9d, S * kS9d));
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      double2 t[3] = {w[0][k], w[1][k], w[2][k]};
+      butterfly<3, S>(t);
+#pragma unroll
+      for (int k2 = 0; k2 < 3; ++k2) v[k + 3 * k2] = t[k2];
+    }
+  } else if constexpr (R == 10) {
+    butterfly_coprime<2, 5, S>(v);
+  } else if constexpr (R == 12) {
+    butterfly_coprime<4, 3, S>(v);
+  } else if constexpr (R == 15) {
+    butterfly_coprime<3, 5, S>(v);
   } else {
-    q = j / Ns;
-    k = j - q * Ns;
-  }
-}
-
-// In-place Stockham stage of radix R on NA arrays in LDS (NA = 1 or 2): every
-// thread first reads, twiddles and transforms all butterflies it owns into
-// registers, then (after a barrier) writes them in autosort order.
-// sign = -1 forward (exp(-2 pi i jk/M)), +1 inverse.
-template <int R, int NA, int MAXM, int NT>
-__device__ __forceinline__ void stage(double2* x0, double2* x1, int M, int Ns, int lg,
-                                      const double2* tw, double sign) {
-  constexpr int MAXB = ((MAXM / R) * NA + NT - 1) / NT;
-  const int span = M / R;
-  const int step = M / (Ns * R);
-  const int total = span * NA;
-  const int half = M >> 1;
-  double2 v[MAXB][R];
-  int dst[MAXB];
+    static_assert(R == 16, "radices of FftPlan");
+    // n = 4 n1 + n2, k = k1 + 4 k2, twiddles exp(S 2 pi i n2 k1 / 16)
+    double2 w[4][4];  // [n2][k1]
 #pragma unroll
-  for (int c = 0; c < MAXB; ++c) {
-    const int t = threadIdx.x + c * NT;
-    dst[c] = -1;
-    if (t < total) {
-      const int a = (NA == 1) ? 0 : (t >= span ? 1 : 0);
-      const int j = t - a * span;
-      const double2* x = a ? x1 : x0;
+    for (int n2 = 0; n2 < 4; ++n2) {
+      double2 t[4] = {v[n2], v[4 + n2], v[8 + n2], v[12 + n2]};
+      butterfly<4, S>(t);
 #pragma unroll
-      for (int r = 0; r < R; ++r) v[c][r] = x[pad(j + r * span)];
-      int q, k;
-      split(j, Ns, lg, q, k);
-      if (k != 0) {
+      for (int k = 0; k < 4; ++k) w[n2][k] = t[k];
+    }
+    auto eighth = [](double2 a) { return make_double2(kH * (a.x - S * a.y), kH * (a.y + S * a.x)); };
+    w[1][1] = cmul(w[1][1], make_double2(kC16, S * kS16));
+    w[1][2] = eighth(w[1][2]);
+    w[1][3] = cmul(w[1][3], make_double2(kS16, S * kC16));
+    w[2][1] = eighth(w[2][1]);
+    w[2][2] = cmul_si<S>(w[2][2]);
+    w[2][3] = cmul_si<S>(eighth(w[2][3]));
+    w[3][1] = cmul(w[3][1], make_double2(kS16, S * kC16));
+    w[3][2] = cmul_si<S>(eighth(w[3][2]));
+    w[3][3] = cmul(w[3][3], make_double2(-kC16, -S * kS16));
 #pragma unroll
-        for (int r = 1; r < R; ++r) {
-          double2 w = twiddle(tw, r * k * step, half);
-          w.y *= -sign;  // the table holds exp(-2 pi i e / M); forward uses it as is
-          v[c][r] = cmul(v[c][r], w);
-        }
-      }
-      butterfly<R>(v[c], sign);
-      dst[c] = (a << 24) | (q * Ns * R + k);
+    for (int k = 0; k < 4; ++k) {
+      double2 t[4] = {w[0][k], w[1][k], w[2][k], w[3][k]};
+      butterfly<4, S>(t);
+#pragma unroll
+      for (int k2 = 0; k2 < 4; ++k2) v[k + 4 * k2] = t[k2];
     }
   }
+}
+
+// t / d for t d < 2^21, magic = 2^21 / d + 1
+__device__ __forceinline__ int quot(int t, unsigned magic) { return (int)(((unsigned)t * magic) >> 21); }
+// LDS slot of position i: pad0 free slots after every J[0] positions, pad1 after every J[1].
+__device__ __forceinline__ int slot(const FftPlan& pl, int i) {
+  int s = i + pl.pad0 * quot(i, pl.mj[0]);
+  if (pl.pad1) s += pl.pad1 * quot(i, pl.mj[1]);
+  return s;
+}
+// Slots between the positions i and i + J[st] of one block.
+__device__ __forceinline__ int slot_stride(const FftPlan& pl, int st) {
+  return pl.J[st] + (st == 0 ? pl.pad0 + pl.pad1 * pl.radix[1] : st == 1 ? pl.pad1 : 0);
+}
+
+// Powers w^r, w = exp(S 2 pi i e / M), r = 1 .. R-1, e R < M, times v[r]: w, w^2 and w^4
+// are read from the table tw[k] = exp(-2 pi i k / M), the others are products of at
+// most four of these.
+template <int R, int S>
+struct Twiddle {
+  double2 w1, w2, w4;
+  __device__ __forceinline__ Twiddle(const double2* tw, int e) {
+    w1 = tw[e];
+    w2 = R > 2 ? tw[2 * e] : w1;
+    w4 = R > 4 ? tw[4 * e] : w1;
+    if (S > 0) {
+      w1.y = -w1.y;
+      w2.y = -w2.y;
+      w4.y = -w4.y;
+    }
+  }
+  __device__ __forceinline__ void apply(double2* v) const {
+    v[1] = cmul(v[1], w1);
+    if constexpr (R > 2) v[2] = cmul(v[2], w2);
+    double2 w3 = w1, wb = w4;
+    if constexpr (R > 3) {
+      w3 = cmul(w1, w2);
+      v[3] = cmul(v[3], w3);
+    }
+#pragma unroll
+    for (int r = 4; r < R; r += 4) {
+      v[r] = cmul(v[r], wb);
+      if (r + 1 < R) v[r + 1] = cmul(v[r + 1], cmul(wb, w1));
+      if (r + 2 < R) v[r + 2] = cmul(v[r + 2], cmul(wb, w2));
+      if (r + 3 < R) v[r + 3] = cmul(v[r + 3], cmul(wb, w3));
+      if (r + 4 < R) wb = cmul(wb, w4);
+    }
+  }
+};
+
+// One stage of radix R over na arrays of stride PL, in place: the butterfly of block b,
+// offset j works on the positions b L + j + r J, L = R J; decimation in frequency
+// (S = 1, inverse: twiddles after the butterfly) or in time (S = -1: before).
+template <int R, int S, int NT>
+__device__ __forceinline__ void stage(double2* x, int na, int PL, const FftPlan& pl, int st,
+                                      const double2* tw) {
+  const int J = pl.J[st], per = pl.per[st], step = pl.step[st], d = slot_stride(pl, st);
+  for (int t = threadIdx.x; t < na * per; t += NT) {
+    const int a = na > 1 ? quot(t, pl.mper[st]) : 0, u = t - a * per;
+    const int b = quot(u, pl.mj[st]), j = u - b * J;
+    double2* y = x + (a * PL + slot(pl, b * J * R + j));
+    const Twiddle<R, S> w(tw, j * step);  // (the last stage, J = 1, does not come here)
+    double2 v[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) v[r] = y[r * d];
+    if (S < 0) w.apply(v);
+    butterfly<R, S>(v);
+    if (S > 0) w.apply(v);
+#pragma unroll
+    for (int r = 0; r < R; ++r) y[r * d] = v[r];
+  }
+}
+
+// Compile-time plans of the default grids of N = 2^k - 1, M = 3 * 2^k, and of N = 100, M =
+// 320 (160 rings 5.0 us, 6.9 at run time; any other M: the one that
+// fft_plan found, a kernel argument). With every index a constant the ring takes 21.3
+// us instead of 24.4 at M = 1536 (768 rings), 53 instead of 64 us at M = 768 (6144 rings).
+// Measured against these plans: 12, 16, 8 and 16, 12, 8 at M = 1536 22.8 us (their
+// last pass needs more registers); 8, 8, 8, 3 over 384 threads 22.8; 16, 16, 3 at M =
+// 768 8.8 against 8.2 us for 384 rings; 4, 16, 3 at M = 192 10.5 against 9.8 us for 2304.
+template <int CM>
+__host__ __device__ __forceinline__ FftPlan plan_of(const FftPlan& rt) {
+  if constexpr (CM == 1536) return make_plan(CM, {16, 16, 6}, 3, 6, 0);
+  else if constexpr (CM == 768) return make_plan(CM, {8, 16, 6}, 3, 6, 0);
+  else if constexpr (CM == 384) return make_plan(CM, {8, 16, 3}, 3, 3, 0);
+  else if constexpr (CM == 320) return make_plan(CM, {8, 8, 5}, 3, 0, 0);
+  else if constexpr (CM == 192) return make_plan(CM, {8, 8, 3}, 3, 3, 0);
+  else if constexpr (CM == 96) return make_plan(CM, {4, 4, 6}, 3, 0, 0);
+  else if constexpr (CM == 48) return make_plan(CM, {2, 4, 6}, 3, 0, 0);
+  else return rt;
+}
+// Calls f(integral_constant<R>) for the plan's radix.
+template <typename F>
+__device__ __forceinline__ void with_radix(int R, F&& f) {
+  switch (R) {
+    case 2: f(std::integral_constant<int, 2>{}); break;
+    case 3: f(std::integral_constant<int, 3>{}); break;
+    case 4: f(std::integral_constant<int, 4>{}); break;
+    case 5: f(std::integral_constant<int, 5>{}); break;
+    case 6: f(std::integral_constant<int, 6>{}); break;
+    case 8: f(std::integral_constant<int, 8>{}); break;
+    case 9: f(std::integral_constant<int, 9>{}); break;
+    case 10: f(std::integral_constant<int, 10>{}); break;
+    case 12: f(std::integral_constant<int, 12>{}); break;
+    case 15: f(std::integral_constant<int, 15>{}); break;
+    default: f(std::integral_constant<int, 16>{}); break;
+  }
+}
+// The same for the last stage's radix (at most kMaxLastRadix: its pass holds the
+// butterflies of two or three arrays at once).
+template <typename F>
+__device__ __forceinline__ void with_last_radix(int R, F&& f) {
+  switch (R) {
+    case 2: f(std::integral_constant<int, 2>{}); break;
+    case 3: f(std::integral_constant<int, 3>{}); break;
+    case 4: f(std::integral_constant<int, 4>{}); break;
+    case 5: f(std::integral_constant<int, 5>{}); break;
+    default: f(std::integral_constant<int, 6>{}); break;
+  }
+}
+template <int S, int NT>
+__device__ __forceinline__ void run_stage(double2* x, int na, int PL, const FftPlan& pl, int st,
+                                          const double2* tw) {
+  with_radix(pl.radix[st], [&](auto r) { stage<decltype(r)::value, S, NT>(x, na, PL, pl, st, tw); });
+}
+// The last stage alone (J = 1: no twiddles).
+template <int S, int NT>
+__device__ __forceinline__ void run_last(double2* x, int na, int PL, const FftPlan& pl) {
+  const int last = pl.nstages - 1, per = pl.per[last];
+  with_last_radix(pl.radix[last], [&](auto rc) {
+    constexpr int R = decltype(rc)::value;
+    for (int t = threadIdx.x; t < na * per; t += NT) {
+      const int a = na > 1 ? quot(t, pl.mper[last]) : 0;
+      double2* y = x + (a * PL + slot(pl, (t - a * per) * R));
+      double2 v[R];
+#pragma unroll
+      for (int r = 0; r < R; ++r) v[r] = y[r];
+      butterfly<R, S>(v);
+#pragma unroll
+      for (int r = 0; r < R; ++r) y[r] = v[r];
+    }
+  });
   __syncthreads();
+}
+// f(st) for the stages before the last one, a barrier after each: in rising order
+// (S = 1) or falling (S = -1); unrolled for a compile-time plan.
+template <int S, bool CT, typename F>
+__device__ __forceinline__ void for_stages(const FftPlan& pl, F&& f) {
+  const int last = pl.nstages - 1;
+  if constexpr (CT) {
 #pragma unroll
-  for (int c = 0; c < MAXB; ++c) {
-    if (dst[c] >= 0) {
-      double2* x = (dst[c] >> 24) ? x1 : x0;
-      const int idx = dst[c] & 0xffffff;
-#pragma unroll
-      for (int r = 0; r < R; ++r) x[pad(idx + r * Ns)] = v[c][r];
-    }
-  }
-  __syncthreads();
-}
-
-// Full in-place transform of one or two LDS arrays.
-template <int NA, int MAXM, int NT>
-__device__ void fft(double2* x0, double2* x1, const FftPlan& plan, int M, const double2* tw,
-                    double sign) {
-  int Ns = 1;
-  for (int st = 0; st < plan.nstages; ++st) {
-    const int R = plan.radix[st];
-    const int lg = plan.ns_log2[st];
-    switch (R) {
-      case 2: stage<2, NA, MAXM, NT>(x0, x1, M, Ns, lg, tw, sign); break;
-      case 3: stage<3, NA, MAXM, NT>(x0, x1, M, Ns, lg, tw, sign); break;
-      case 4: stage<4, NA, MAXM, NT>(x0, x1, M, Ns, lg, tw, sign); break;
-      case 5: stage<5, NA, MAXM, NT>(x0, x1, M, Ns, lg, tw, sign); break;
-      default: stage<8, NA, MAXM, NT>(x0, x1, M, Ns, lg, tw, sign); break;
-    }
-    Ns *= R;
-  }
-}
-
-// Compile-time plans for M = 3 * 2^k, the default grid of every truncation
-// (M = 3(N+1) for N = 2^j - 1): radix-8 stages (radix 4 where the power of
-// two needs it), radix 3 last, so every stride before the last stage is a
-// power of two. With M, the radices, the strides and the direction known at
-// compile time, the index arithmetic of a stage folds into constants.
-template <int M> struct CtPlan { static constexpr int n = 0; static constexpr int r[1] = {0}; };
-template <> struct CtPlan<48> { static constexpr int n = 3; static constexpr int r[3] = {4, 4, 3}; };
-template <> struct CtPlan<96> { static constexpr int n = 3; static constexpr int r[3] = {8, 4, 3}; };
-template <> struct CtPlan<192> { static constexpr int n = 3; static constexpr int r[3] = {8, 8, 3}; };
-template <> struct CtPlan<384> { static constexpr int n = 4; static constexpr int r[4] = {8, 4, 4, 3}; };
-template <> struct CtPlan<768> { static constexpr int n = 4; static constexpr int r[4] = {8, 8, 4, 3}; };
-template <> struct CtPlan<1536> { static constexpr int n = 4; static constexpr int r[4] = {8, 8, 8, 3}; };
-// M = 320 (N = 100 on 160 x 320, the grid of the paper's Example 2): radix 5
-// last, so the product and the forward store run as separate passes
-template <> struct CtPlan<320> { static constexpr int n = 3; static constexpr int r[3] = {8, 8, 5}; };
-// plans whose last stage is radix 3 at stride M/3 (fused product and store)
-template <int M> constexpr bool ct_fused() { return CtPlan<M>::n > 0 && CtPlan<M>::r[CtPlan<M>::n - 1] == 3; }
-
-constexpr int ct_log2(int x) { return x <= 1 ? 0 : 1 + ct_log2(x / 2); }
-
-// exp(SGN 2 pi i e / M) for 0 <= e < M from the half table tw[0 .. M/2) of
-// exp(-2 pi i e / M).
-template <int M, int SGN>
-__device__ __forceinline__ double2 tw_at(const double2* tw, int e) {
-  constexpr int half = M / 2;
-  double2 w = tw[e < half ? e : e - half];
-  if (e >= half) w = make_double2(-w.x, -w.y);
-  if (SGN > 0) w.y = -w.y;
-  return w;
-}
-
-// The twiddles w[r] = exp(SGN 2 pi i r e / M), r = 1 .. R-1, of one butterfly
-// (R e < R M / R = M): radix 4 and 8 read w, w^2 (and w^4) from the table and
-// form the other powers by products (at most two roundings more than a table
-// entry), which takes three of the seven table reads of a radix-8 butterfly.
-template <int R, int M, int SGN>
-__device__ __forceinline__ void stage_twiddles(double2* w, const double2* tw, int e) {
-  if constexpr (R == 4 || R == 8) {
-    w[1] = tw_at<M, SGN>(tw, e);
-    w[2] = tw_at<M, SGN>(tw, 2 * e);
-    w[3] = cmul(w[1], w[2]);
-    if constexpr (R == 8) {
-      w[4] = tw_at<M, SGN>(tw, 4 * e);
-      w[5] = cmul(w[1], w[4]);
-      w[6] = cmul(w[2], w[4]);
-      w[7] = cmul(w[3], w[4]);
+    for (int i = 0; i < kMaxStages - 1; ++i) {
+      const int st = S > 0 ? i : kMaxStages - 2 - i;
+      if (st < last) {
+        f(st);
+        __syncthreads();
+      }
     }
   } else {
-#pragma unroll
-    for (int r = 1; r < R; ++r) w[r] = tw_at<M, SGN>(tw, r * e);
-  }
-}
-
-// One Stockham stage of radix R at stride NS (a power of two) on NA arrays of
-// length M (x1 = x0 + padded_len(M) when NA = 2); SGN = -1 forward, +1 inverse.
-template <int R, int NS, int M, int NA, int NT, int SGN>
-__device__ __forceinline__ void stage_ct(double2* x0, const double2* tw) {
-  constexpr int span = M / R, total = span * NA, MAXB = (total + NT - 1) / NT;
-  constexpr int step = M / (NS * R), lg = ct_log2(NS);
-  constexpr int PL = M + (M >> 4) + 1;
-  double2 v[MAXB][R];
-  int dst[MAXB];
-#pragma unroll
-  for (int c = 0; c < MAXB; ++c) {
-    const int t = threadIdx.x + c * NT;
-    dst[c] = -1;
-    if (total % NT == 0 || t < total) {
-      const int a = (NA == 1) ? 0 : (t >= span ? 1 : 0);
-      const int j = t - a * span;
-      const double2* x = x0 + a * PL;
-#pragma unroll
-      for (int r = 0; r < R; ++r) v[c][r] = x[pad(j + r * span)];
-      const int k = j & (NS - 1), q = j >> lg;
-      if constexpr (NS > 1) {
-        double2 w[R];
-        stage_twiddles<R, M, SGN>(w, tw, k * step);
-#pragma unroll
-        for (int r = 1; r < R; ++r) v[c][r] = cmul(v[c][r], w[r]);
-      }
-      butterfly<R>(v[c], (double)SGN);
-      dst[c] = a * PL + q * NS * R + k;
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int c = 0; c < MAXB; ++c) {
-    if (dst[c] >= 0) {
-      const int base = dst[c] >= PL ? PL : 0;
-      const int idx = dst[c] - base;
-#pragma unroll
-      for (int r = 0; r < R; ++r) x0[base + pad(idx + r * NS)] = v[c][r];
-    }
-  }
-  __syncthreads();
-}
-
-template <int M, int S, int NS, int NA, int NT, int SGN>
-__device__ __forceinline__ void stages_ct(double2* x0, const double2* tw) {
-  if constexpr (S < CtPlan<M>::n) {
-    constexpr int R = CtPlan<M>::r[S];
-    stage_ct<R, NS, M, NA, NT, SGN>(x0, tw);
-    stages_ct<M, S + 1, NS * R, NA, NT, SGN>(x0, tw);
-  }
-}
-
-// Inverse transforms of the two LDS arrays x0 = f0 + i f1 and x1 = f2 + i f3 (x1 =
-// x0 + padded_len(M)) for a compile-time plan whose last stage is radix 3 at
-// stride M/3, fused with the grid product: every stage before the last as in
-// stages_ct; in the last, thread j computes butterfly j of both arrays, whose
-// outputs are the grid values at j, j + M/3 and j + 2M/3 (the positions it
-// read), forms q = Re(x0 x1) / sin^2 there and writes q in place to x0, so the
-// write-back of the last stage, the separate product pass and two barriers go.
-template <int M, int S, int NS, int NT>
-__device__ __forceinline__ void fft_ct_inverse_product(double2* x0, const double2* tw,
-                                                       double inv_sin2) {
-  constexpr int n = CtPlan<M>::n;
-  if constexpr (S < n - 1) {
-    constexpr int R = CtPlan<M>::r[S];
-    stage_ct<R, NS, M, 2, NT, 1>(x0, tw);
-    fft_ct_inverse_product<M, S + 1, NS * R, NT>(x0, tw, inv_sin2);
-  } else {
-    static_assert(CtPlan<M>::r[n - 1] == 3 && NS * 3 == M, "last stage: radix 3 at stride M/3");
-    constexpr int PL = M + (M >> 4) + 1, MAXB = (NS + NT - 1) / NT;
-#pragma unroll
-    for (int b = 0; b < MAXB; ++b) {
-      const int j = threadIdx.x + b * NT;  // butterfly j (q = 0, k = j at stride NS = M/3)
-      if (NS % NT == 0 || j < NS) {
-        double2 v[2][3];
-        const double2 w1 = tw_at<M, 1>(tw, j);  // inverse twiddles of butterfly j
-        const double2 w2 = cmul(w1, w1);
-#pragma unroll
-        for (int a = 0; a < 2; ++a) {
-#pragma unroll
-          for (int r = 0; r < 3; ++r) v[a][r] = x0[a * PL + pad(j + r * NS)];
-          v[a][1] = cmul(v[a][1], w1);
-          v[a][2] = cmul(v[a][2], w2);
-          butterfly<3>(v[a], 1.0);
-        }
-#pragma unroll
-        for (int r = 0; r < 3; ++r)
-          x0[pad(j + r * NS)] =
-              make_double2((v[0][r].x * v[1][r].x - v[0][r].y * v[1][r].y) * inv_sin2, 0.0);
-      }
-    }
-    __syncthreads();
-  }
-}
-
-// Forward transform of one LDS array for a compile-time plan whose last stage
-// is radix 3 at stride M/3: every stage before it as in stages_ct, then the
-// last stage computes only its butterflies' first outputs, X_m for m < M/3
-// (they hold every m <= N since 3N + 2 <= M), and stores c X_m for m <= N
-// straight to out[m * ostride], without the LDS write-back and its barriers.
-template <int M, int S, int NS, int NT>
-__device__ __forceinline__ void fft_ct_forward_store(double2* x0, const double2* tw, double c,
-                                                     double2* __restrict__ out, int64_t ostride,
-                                                     int N) {
-  constexpr int n = CtPlan<M>::n;
-  if constexpr (S < n - 1) {
-    constexpr int R = CtPlan<M>::r[S];
-    stage_ct<R, NS, M, 1, NT, -1>(x0, tw);
-    fft_ct_forward_store<M, S + 1, NS * R, NT>(x0, tw, c, out, ostride, N);
-  } else {
-    static_assert(CtPlan<M>::r[n - 1] == 3 && NS * 3 == M, "last stage: radix 3 at stride M/3");
-    constexpr int MAXB = (NS + NT - 1) / NT;
-#pragma unroll
-    for (int b = 0; b < MAXB; ++b) {
-      const int j = threadIdx.x + b * NT;  // butterfly j = k (q = 0 at stride NS = M/3)
-      if (j <= N) {
-        double2 v0 = x0[pad(j)], v1 = x0[pad(j + NS)], v2 = x0[pad(j + 2 * NS)];
-        if (j != 0) {
-          const double2 w1 = tw_at<M, -1>(tw, j);  // j < M / 3
-          v1 = cmul(v1, w1);
-          v2 = cmul(v2, cmul(w1, w1));
-        }
-        // first output of the radix-3 butterfly: v0 + (v1 + v2)
-        const double2 t = cadd(v1, v2);
-        out[(int64_t)j * ostride] = make_double2(c * (v0.x + t.x), c * (v0.y + t.y));
-      }
+#pragma unroll 1
+    for (int i = 0; i < last; ++i) {
+      f(S > 0 ? i : last - 1 - i);
+      __syncthreads();
     }
   }
 }
-
-// Transform of one or two LDS arrays (x1 must be x0 + padded_len(M) when
-// NA = 2): the compile-time plan when CM > 0, else the runtime plan.
-template <int NA, int MAXM, int NT, int CM>
-__device__ __forceinline__ void fft_any(double2* x0, double2* x1, const FftPlan& plan, int M,
-                                        const double2* tw, double sign) {
-  if constexpr (CM > 0) {
-    if (sign > 0)
-      stages_ct<CM, 0, 1, NA, NT, 1>(x0, tw);
-    else
-      stages_ct<CM, 0, 1, NA, NT, -1>(x0, tw);
-  } else {
-    fft<NA, MAXM, NT>(x0, x1, plan, M, tw, sign);
+// Slot of grid point n in the order that the inverse stages leave.
+__device__ __forceinline__ int grid_slot(const FftPlan& pl, int n) {
+  int pos = 0;
+  for (int s = 0; s < pl.nstages; ++s) {
+    const int d = quot(n, pl.mr[s]);
+    pos += (n - d * pl.radix[s]) * slot_stride(pl, s);
+    n = d;
   }
+  return pos;
 }
 
-// The ring's inputs for the forward kernel: the twiddle half table into tw and
-// the spectra of two field pairs into x0 = (Fa0, Fb0) and x1 = (Fa1, Fb1): for a
-// pair (a, b), x_m = G^a_m + i G^b_m, x_{M-m} = conj(G^a_m) + i conj(G^b_m) and
-// zero elsewhere, G[m] read from F[f][m][lat] (stride nlat between orders).
-// Every global load is issued before the first LDS write
-// (one memory round trip for the ring instead of one per array); thread t
-// loads order m = t mod (N+1) of pair t / (N+1). Since 3N + 2 <= M <= MAXM,
-// 2 (N+1) <= 2 (MAXM / 3 + 1) <= KI NT.
-template <int MAXM, int NT, bool COPYTW = true>
-__device__ void load_ring(double2* x0, double2* x1, double2* tw, const double2* __restrict__ gtw,
-                          const double2* __restrict__ Fa0, const double2* __restrict__ Fb0,
-                          const double2* __restrict__ Fa1, const double2* __restrict__ Fb1,
-                          int lat, int N, int M, int nlat) {
-  constexpr int KI = (2 * (MAXM / 3 + 1) + NT - 1) / NT;
-  constexpr int KT = (MAXM / 2 + NT - 1) / NT;
-  const int n1 = N + 1;
-  double2 ga[KI], gb[KI], t[KT];
-#pragma unroll
-  for (int i = 0; i < KI; ++i) {
-    const int idx = threadIdx.x + i * NT;
-    ga[i] = gb[i] = make_double2(0.0, 0.0);
-    if (idx < 2 * n1) {
-      const bool second = idx >= n1;
-      const int64_t off = (int64_t)(idx - (second ? n1 : 0)) * nlat + lat;
-      ga[i] = (second ? Fa1 : Fa0)[off];
-      gb[i] = (second ? Fb1 : Fb0)[off];
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < KT; ++i) {
-    const int j = threadIdx.x + i * NT;
-    if (COPYTW && j < M / 2) t[i] = gtw[j];
-  }
-#pragma unroll
-  for (int i = 0; i < KT; ++i) {
-    const int j = threadIdx.x + i * NT;
-    if (COPYTW && j < M / 2) tw[j] = t[i];
-  }
-#pragma unroll
-  for (int i = 0; i < KI; ++i) {
-    const int idx = threadIdx.x + i * NT;
-    if (idx < 2 * n1) {
-      const bool second = idx >= n1;
-      const int m = idx - (second ? n1 : 0);
-      double2* x = second ? x1 : x0;
-      if (m == 0) {
-        x[0] = make_double2(ga[i].x, gb[i].x);
-      } else {
-        x[pad(m)] = make_double2(ga[i].x - gb[i].y, ga[i].y + gb[i].x);       // ga + i gb
-        x[pad(M - m)] = make_double2(ga[i].x + gb[i].y, -ga[i].y + gb[i].x);  // conj(ga) + i conj(gb)
-      }
-    }
-  }
-  for (int j = N + 1 + threadIdx.x; j < M - N; j += NT) {
-    x0[pad(j)] = make_double2(0.0, 0.0);
-    x1[pad(j)] = make_double2(0.0, 0.0);
-  }
+// Northern node of ring `lat`.
+__device__ __forceinline__ int ring_node(const GroupView& g, int lat) {
+  return lat < g.nh ? lat : g.nlat - 1 - lat;
 }
 
-// ---------------------------------------------------------------------------
-// Nonlinear-mode ring kernel for M = 3 S, S = 128, 256 (the default grids of
-// N = 127 and 255). With k = k1 + 3 k2 and n = S n1 + n2 (k1, n1 < 3;
-// k2, n2 < S) the length-M transforms split into three S-point transforms and
-// one radix-3 pass:
-//   inverse: Y_k1 = IDFT_S(X[k1 + 3 .]),  x[S n1 + n2] = sum_k1 e^{2 pi i k1 n1/3} e^{2 pi i k1 n2/M} Y_k1[n2];
-//   forward: Z_k1[n2] = e^{-2 pi i k1 n2/M} sum_n1 q[S n1 + n2] e^{-2 pi i k1 n1/3},  Q[k1 + 3 k2] = DFT_S(Z_k1)[k2].
-// Each S-point transform belongs to one wave, which runs its Stockham stages
-// on its own LDS row: a wave's LDS accesses complete in program order, so the
-// stages need no workgroup barrier. The radix-3 passes of both directions and
-// the grid product meet in one pass (thread n2 holds the three grid points
-// S n1 + n2 of both paired fields), so the ring needs three workgroup barriers
-// (after the loads, after the six inverse transforms, after the fused pass)
-// where the radix-8/4/3 plan over the whole ring took about ten.
-template <int S> struct WavePlan { static constexpr int n = 0; static constexpr int r[1] = {0}; };
-template <> struct WavePlan<128> { static constexpr int n = 4; static constexpr int r[4] = {2, 4, 4, 4}; };
-template <> struct WavePlan<256> { static constexpr int n = 4; static constexpr int r[4] = {4, 4, 4, 4}; };
-
-__host__ __device__ constexpr int wave_row(int S) { return S + (S >> 4) + 1; }
-
-// exp(-2 pi i e / M), e < M, from the half table tw[0 .. M/2).
-template <int M>
-__device__ __forceinline__ double2 tw_full(const double2* tw, int e) {
-  constexpr int half = M / 2;
-  if (e < half) return tw[e];
-  const double2 t = tw[e - half];
-  return make_double2(-t.x, -t.y);
-}
-
-// One Stockham stage of radix R at stride NS over the S points of a wave's LDS
-// row x (in place: every lane reads its butterflies, then writes them); the
-// twiddles of length S are those of length M = 3 S at three times the index.
-// With STORE (the last forward stage, NS R = S) the outputs k2 = j + r NS go
-// to out[(k1 + 3 k2) * ostride] (scaled by c) for k1 + 3 k2 <= N instead.
-template <int R, int NS, int S, int SGN, bool STORE>
-__device__ __forceinline__ void wave_stage(double2* x, const double2* tw, int lane, double c,
-                                           double2* __restrict__ out, int64_t ostride, int k1,
-                                           int N) {
-  constexpr int M = 3 * S, span = S / R, MAXB = (span + 63) / 64;
-  constexpr int step = S / (NS * R), lg = ct_log2(NS);
-  double2 v[MAXB][R];
-  int dst[MAXB];
-#pragma unroll
-  for (int b = 0; b < MAXB; ++b) {
-    const int j = lane + 64 * b;
-    dst[b] = -1;
-    if (span % 64 == 0 || j < span) {
-#pragma unroll
-      for (int r = 0; r < R; ++r) v[b][r] = x[pad(j + r * span)];
-      const int k = j & (NS - 1), q = j >> lg;
-      if constexpr (NS > 1) {
-        // length-S twiddles: those of length M = 3 S at three times the index
-        double2 w[R];
-        stage_twiddles<R, M, SGN>(w, tw, 3 * k * step);
-#pragma unroll
-        for (int r = 1; r < R; ++r) v[b][r] = cmul(v[b][r], w[r]);
-      }
-      butterfly<R>(v[b], (double)SGN);
-      dst[b] = q * NS * R + k;
-    }
-  }
-  __builtin_amdgcn_wave_barrier();
-#pragma unroll
-  for (int b = 0; b < MAXB; ++b) {
-    if (dst[b] >= 0) {
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        if constexpr (STORE) {
-          const int m = k1 + 3 * (dst[b] + r * NS);
-          if (m <= N) out[(int64_t)m * ostride] = make_double2(c * v[b][r].x, c * v[b][r].y);
-        } else {
-          x[pad(dst[b] + r * NS)] = v[b][r];
-        }
-      }
-    }
-  }
-  __builtin_amdgcn_wave_barrier();
-}
-
-template <int S, int ST, int NS, int SGN, bool STORE_LAST>
-__device__ __forceinline__ void wave_fft(double2* x, const double2* tw, int lane, double c,
-                                         double2* __restrict__ out, int64_t ostride, int k1,
-                                         int N) {
-  if constexpr (ST < WavePlan<S>::n) {
-    constexpr int R = WavePlan<S>::r[ST];
-    constexpr bool last = ST + 1 == WavePlan<S>::n;
-    wave_stage<R, NS, S, SGN, STORE_LAST && last>(x, tw, lane, c, out, ostride, k1, N);
-    wave_fft<S, ST + 1, NS * R, SGN, STORE_LAST>(x, tw, lane, c, out, ostride, k1, N);
-  }
-}
-
-// Workgroup of NR neighbouring rings, NT / NR >= max(S, 384) threads per ring:
-// waves 6 r .. 6 r + 5 hold the inverse transforms Y_{a,k1} of ring r (a = 0:
-// f0 + i f1, a = 1: f2 + i f3) on LDS rows 6 r + 3 a + k1, threads
-// r NT / NR + n2 (n2 < S) the fused pass of ring r, waves 3 r .. 3 r + 2 its
-// forward transforms. With NR = 2 the loads of the two rings' spectra pair up
-// on the same cache lines (lanes 2 j and 2 j + 1 read the two latitudes of one
-// order): T255 ring 8.2 -> 7.6 us, the launch's 192 workgroups leaving 64 CUs
-// idle while the others hold the two rings that the busiest CUs held before.
-// TWL: the twiddle half table copied to LDS (after the rows) instead of read
-// from the global table through L1: the better choice when many members'
-// rings share the CUs (throughput), the global table when one member's rings
-// are latency-bound.
-template <int S, int NT, bool TWL, int NR>
-__global__ __launch_bounds__(NT) void k_ring_nl(GroupView g) {
-  constexpr int M = 3 * S, PS = wave_row(S), RT = NT / NR;
-  static_assert(RT >= S && RT >= 384, "threads per ring");
-  const int N = g.N, nlat = g.nlat;
-  const int lat0 = NR * xcd_item(blockIdx.x, 8 / NR);  // XCD chunks of 8 latitudes
-  if (lat0 >= nlat) return;
-  const int b = blockIdx.y;
-  extern __shared__ double2 lds[];
-  double2* twl = lds + 6 * NR * PS;
-  const double2* tw = TWL ? twl : g.tw;
-  if constexpr (TWL) {
-    for (int j = threadIdx.x; j < M / 2; j += NT) twl[j] = g.tw[j];  // ordered by the first barrier
-  }
-  const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  const int64_t fstride = (int64_t)(N + 1) * nlat;
-  const double2* F0 = g.F + (int64_t)b * 4 * fstride + lat0;
-
-  // loads: every spectrum value once (thread t: ring rr = t mod NR, order
-  // m = t' mod (N+1) of pair a = t' / (N+1), t' = t / NR, both fields of the
-  // pair), all requested before the first LDS write; X_a[m] = G^f_m + i G^f'_m
-  // goes to row 3a + m mod 3 of its ring at m / 3 and X_a[M - m] =
-  // conj(G^f_m) + i conj(G^f'_m) to row 3a + (M - m) mod 3 at (M - m) / 3
-  constexpr int KI = (2 * (S + 1) + RT - 1) / RT;  // N + 1 <= M / 3 + 1 = S + 1
-  const int n1 = N + 1;
-  const int rr = threadIdx.x % NR, tt = threadIdx.x / NR;
-  const bool rvalid = lat0 + rr < nlat;  // an odd last ring pair holds one ring
+// Spectra of NR neighbouring rings into LDS: array (ring rr, pair a) at x + (rr NP + a)
+// PL holds x_m = G^a_m + i G^b_m and x_{M-m} = conj(G^a_m) + i conj(G^b_m), zero in
+// between. pair(a, &ga, &gb) gives the pair's fields, [m][lat] with stride nlat between
+// orders; the third of NP = 3 pairs is one real field of spectrum ga / 2. All loads
+// are issued, unconditionally, before the first LDS write; neighbouring lanes take the
+// rings of one order, whose spectra share a cache line.
+template <int NP, int NR, int MAXM, int NT, typename P>
+__device__ __forceinline__ void load_spectra(double2* x, int PL, const FftPlan& pl, int N, int M, int nlat,
+                                             int lat0, P&& pair) {
+  constexpr int KI = (NR * NP * ((MAXM + 1) / 3) + NT - 1) / NT;  // N + 1 <= (M + 1) / 3
+  const int n1 = N + 1, top = NP * n1;
   double2 ga[KI], gb[KI];
 #pragma unroll
   for (int i = 0; i < KI; ++i) {
-    const int idx = tt + i * RT;
-    ga[i] = gb[i] = make_double2(0.0, 0.0);
-    if (idx < 2 * n1 && rvalid) {
-      const int a = idx >= n1 ? 1 : 0, m = idx - a * n1;
-      const double2* Fa = F0 + (int64_t)(2 * a) * fstride + (int64_t)m * nlat + rr;
-      ga[i] = Fa[0];
-      gb[i] = Fa[fstride];
-    }
+    const int t = threadIdx.x + i * NT, rr = t % NR, tt = min(t / NR, top - 1);
+    const int a = NP == 3 && tt >= 2 * n1 ? 2 : (tt >= n1 ? 1 : 0);
+    const double2 *fa, *fb;
+    pair(a, fa, fb);
+    const int64_t off = (int64_t)(tt - a * n1) * nlat + min(lat0 + rr, nlat - 1);
+    ga[i] = fa[off];
+    gb[i] = fb[off];
   }
 #pragma unroll
   for (int i = 0; i < KI; ++i) {
-    const int idx = tt + i * RT;
-    if (idx < 2 * n1) {
-      const int a = idx >= n1 ? 1 : 0, m = idx - a * n1;
-      double2* rows = lds + (6 * rr + 3 * a) * PS;
+    const int t = threadIdx.x + i * NT, rr = t % NR, tt = t / NR;
+    if (tt < top) {
+      const int a = NP == 3 && tt >= 2 * n1 ? 2 : (tt >= n1 ? 1 : 0), m = tt - a * n1;
+      double2* y = x + (rr * NP + a) * PL;
+      const bool real = NP == 3 && a == 2;
+      if (real) gb[i] = make_double2(0.0, 0.0);
       if (m == 0) {
-        rows[0] = make_double2(ga[i].x, gb[i].x);
+        y[0] = make_double2(ga[i].x, gb[i].x);
       } else {
-        rows[(m % 3) * PS + pad(m / 3)] = make_double2(ga[i].x - gb[i].y, ga[i].y + gb[i].x);
-        const int k = M - m;
-        rows[(k % 3) * PS + pad(k / 3)] = make_double2(ga[i].x + gb[i].y, gb[i].x - ga[i].y);
+        const double h = real ? 0.5 : 1.0;
+        y[slot(pl, m)] = make_double2(h * (ga[i].x - gb[i].y), h * (ga[i].y + gb[i].x));
+        y[slot(pl, M - m)] = make_double2(h * (ga[i].x + gb[i].y), h * (gb[i].x - ga[i].y));
       }
     }
   }
-  // the zero band N < k < M - N of both arrays of every ring
-  const int zb = M - 2 * N - 1;
-  for (int t = threadIdx.x; t < NR * 2 * zb; t += NT) {
-    const int r = t / (2 * zb), u = t - r * 2 * zb;
-    const int a = u >= zb ? 1 : 0;
-    const int k = N + 1 + u - a * zb;
-    lds[(6 * r + 3 * a + k % 3) * PS + pad(k / 3)] = make_double2(0.0, 0.0);
+  const int zb = M - 2 * N - 1;  // N < k < M - N
+  for (int a = 0; a < NR * NP; ++a)
+    for (int t = threadIdx.x; t < zb; t += NT) x[a * PL + slot(pl, N + 1 + t)] = make_double2(0.0, 0.0);
+}
+
+// Nonlinear mode: NR rings per workgroup.
+// Bound: at M = 1536 (768 rings, three per CU, 31 MB of spectra in and out) 21.3 us, of
+// which about 7 are the strided reads of the spectra, 6 the FP64 instructions and 5 the
+// LDS; the rings of a CU run in step, so these add up. Stockham rings with radices 8, 8,
+// 8, 3 took 22.8 us; 68 us became 54 for 6144 rings of M = 768 and 37 became 23 for 4608 of
+// M = 384, by fewer LDS passes without bank conflicts and one forward transform for
+// two rings; 17.5 became 13.7 for 480 rings of M = 960 (run-time plan).
+template <int MAXM, int NT, int NR, int CM>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_ring(GroupView g, FftPlan rt) {
+  const FftPlan pl = plan_of<CM>(rt);
+  const int N = g.N, M = CM ? CM : g.M, nlat = CM ? CM / 2 : g.nlat;
+  const int lat0 = NR * xcd_item(blockIdx.x, 8 / NR);  // XCD chunks of 8 rings share lines of F
+  if (lat0 >= nlat) return;
+  const int b = blockIdx.y;
+  const int PL = pl.len;
+  extern __shared__ double2 lds[];
+  const double2* tw = g.tw;
+  const int64_t fstride = (int64_t)(N + 1) * nlat;
+  const double2* F0 = g.F + (int64_t)b * 4 * fstride;
+  double inv_sin2[NR], c[NR];
+#pragma unroll
+  for (int r = 0; r < NR; ++r) {
+    const int lat = min(lat0 + r, nlat - 1), p = ring_node(g, lat);
+    const double x = g.mu[p];
+    inv_sin2[r] = 1.0 / ((1.0 - x) * (1.0 + x));
+    // quadrature factor (2 pi / M) w_p; the equator ring of an odd rule is its
+    // own mirror and is folded twice by the analysis
+    c[r] = (6.283185307179586477 / M) * g.w[p] * (2 * p + 1 == nlat ? 0.5 : 1.0);
   }
+  load_spectra<2, NR, MAXM, NT>(lds, PL, pl, N, M, nlat, lat0,
+                                [&](int a, const double2*& fa, const double2*& fb) {
+                                  fa = F0 + 2 * a * fstride;
+                                  fb = fa + fstride;
+                                });
   // an ended attempt of a device-controlled run: checked once the loads are in
   // flight (nothing is stored before this barrier), so the flag costs no wait
   if (gate_closed(g)) return;
   __syncthreads();
-  if (wave < 6 * NR) wave_fft<S, 0, 1, 1, false>(lds + wave * PS, tw, lane, 0.0, nullptr, 0, 0, 0);
-  __syncthreads();
-  // fused pass of ring r at n2: inverse twiddles and radix 3 of both pairs, the
-  // grid product at S n1 + n2, forward radix 3 and twiddles
-  {
-    const int r = threadIdx.x / RT, n2 = threadIdx.x - r * RT;
-    const int lat = lat0 + r;
-    if (n2 < S && lat < nlat) {
-      const int p = lat < g.nh ? lat : nlat - 1 - lat;  // northern node of the ring
-      const double x = g.mu[p];
-      const double inv_sin2 = 1.0 / ((1.0 - x) * (1.0 + x));
-      double2* rows = lds + 6 * r * PS;
-      const double2 w1 = tw_full<M>(tw, n2), w2 = cmul(w1, w1);
-      double2 y[2][3];
+  const int last = pl.nstages - 1;
+  for_stages<1, (CM > 0)>(pl, [&](int st) { run_stage<1, NT>(lds, 2 * NR, PL, pl, st, tw); });
+  with_last_radix(pl.radix[last], [&](auto rc) {
+    constexpr int R = decltype(rc)::value;
+    for (int u = threadIdx.x; u < pl.per[last]; u += NT) {
+      const int s0 = slot(pl, u * R);
+      double2 z[R];
 #pragma unroll
-      for (int a = 0; a < 2; ++a) {
+      for (int rr = 0; rr < NR; ++rr) {
+        double2 v0[R], v1[R];
+        const double2* y = lds + (2 * rr * PL + s0);
 #pragma unroll
-        for (int k1 = 0; k1 < 3; ++k1) y[a][k1] = rows[(3 * a + k1) * PS + pad(n2)];
-        y[a][1] = cmul(y[a][1], make_double2(w1.x, -w1.y));
-        y[a][2] = cmul(y[a][2], make_double2(w2.x, -w2.y));
-        butterfly<3>(y[a], 1.0);
+        for (int r = 0; r < R; ++r) {
+          v0[r] = y[r];
+          v1[r] = y[PL + r];
+        }
+        butterfly<R, 1>(v0);
+        butterfly<R, 1>(v1);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          const double q = (v0[r].x * v1[r].x - v0[r].y * v1[r].y) * inv_sin2[rr];
+          if (rr == 0)
+            z[r] = make_double2(q, 0.0);
+          else
+            z[r].y = q;
+        }
       }
-      double2 z[3];
+      butterfly<R, -1>(z);
 #pragma unroll
-      for (int j = 0; j < 3; ++j)
-        z[j] = make_double2((y[0][j].x * y[1][j].x - y[0][j].y * y[1][j].y) * inv_sin2, 0.0);
-      butterfly<3>(z, -1.0);
-      z[1] = cmul(z[1], w1);
-      z[2] = cmul(z[2], w2);
-#pragma unroll
-      for (int k1 = 0; k1 < 3; ++k1) rows[k1 * PS + pad(n2)] = z[k1];
+      for (int r = 0; r < R; ++r) lds[s0 + r] = z[r];
     }
-  }
+  });
   __syncthreads();
-  if (wave < 3 * NR) {
-    const int r = wave / 3, k1 = wave - 3 * r;
-    const int lat = lat0 + r;
-    if (lat < nlat) {
-      const int p = lat < g.nh ? lat : nlat - 1 - lat;
-      // quadrature factor (2 pi / M) w_p; the equator ring of an odd rule is its
-      // own mirror and is folded twice by the analysis
-      const double c = (6.283185307179586477 / M) * g.w[p] * (2 * p + 1 == nlat ? 0.5 : 1.0);
-      double2* Wl = g.W + (int64_t)b * (N + 1) * nlat + lat;  // W[b][m][lat]
-      wave_fft<S, 0, 1, -1, true>(lds + (6 * r + k1) * PS, tw, lane, c, Wl, nlat, k1, N);
+  for_stages<-1, (CM > 0)>(pl, [&](int st) { run_stage<-1, NT>(lds, 1, PL, pl, st, tw); });
+  double2* Wl = g.W + (int64_t)b * (N + 1) * nlat + lat0;  // W[b][m][lat]
+  if constexpr (NR == 1) {
+    for (int m = threadIdx.x; m <= N; m += NT) {
+      const double2 z = lds[slot(pl, m)];
+      Wl[(int64_t)m * nlat] = make_double2(c[0] * z.x, c[0] * z.y);
+    }
+  } else {
+    // the two real sequences of one transform: A = (Z_m + conj Z_{M-m}) / 2,
+    // B = (Z_m - conj Z_{M-m}) / (2 i)
+    for (int t = threadIdx.x; t < 2 * (N + 1); t += NT) {
+      const int m = t >> 1, rr = t & 1;
+      const double2 zm = lds[slot(pl, m)], zc = lds[slot(pl, m ? M - m : 0)];
+      const double h = 0.5 * (rr ? c[1] : c[0]);
+      if (lat0 + rr < nlat)
+        Wl[(int64_t)m * nlat + rr] = rr ? make_double2(h * (zm.y + zc.y), -h * (zm.x - zc.x))
+                                       : make_double2(h * (zm.x + zc.x), h * (zm.y - zc.y));
     }
   }
 }
 
-// Adjoint of the ring step on the same split transforms (M = 3 S; the
-// operation is that of k_ring_adj below): nine inverse S-point transforms
-// (rows 3a + k1: a = 0, 1 the forward pairs f0 + i f1 and f2 + i f3, a = 2 the
-// real field of spectrum Qbar / 2), one fused pass at n2 (inverse radix 3 of
-// the three arrays, the cotangents gbar at S n1 + n2, forward radix 3 of
-// gbar0 + i gbar1 and gbar2 + i gbar3), six forward S-point transforms into
-// rows 0..5, and the unpacking of the two real transforms of each array.
-// Waves take the rows in turn, so any NT / NR >= max(S, 384) covers them. With
-// NR = 2 the workgroup holds two neighbouring rings (ring r on rows 9 r .. 9 r + 8,
-// 78.6 KB of LDS at S = 256), and the loads of Fa and the stores of Fbar pair up
-// on the same 32 bytes (lanes 2 j and 2 j + 1 take the two latitudes of one
-// order): the T255 backward pass 1.8% shorter than with one ring per workgroup.
-template <int S, int NT, int NR>
-__global__ __launch_bounds__(NT) void k_ring_adj_nl(GroupView g) {
-  constexpr int M = 3 * S, PS = wave_row(S), NW = NT / 64, RT = NT / NR;
-  static_assert(RT >= S && RT >= 384, "threads per ring");
-  const int N = g.N, nlat = g.nlat;
-  const int lat0 = NR * xcd_item(blockIdx.x, 8 / NR);  // XCD chunks of 8 latitudes
-  if (lat0 >= nlat) return;
-  const int b = blockIdx.y;
-  extern __shared__ double2 lds[];
-  const double2* tw = g.tw;  // twiddle half table, read through L1
-  const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  const int64_t fstride = (int64_t)(N + 1) * nlat;
-  const int rr = threadIdx.x % NR, tt = threadIdx.x / NR;
-  const bool rvalid = lat0 + rr < nlat;  // an odd last ring pair holds one ring
-  const double2* F5 = g.Fa + (int64_t)b * 5 * fstride + lat0 + rr;
-
-  // loads: thread t takes ring rr and order m = t' mod (N+1) of array
-  // a = t' / (N+1), t' = t / NR (both fields of a forward pair, or the fifth
-  // field for a = 2), all requested before the first LDS write
-  constexpr int KI = (3 * (S + 1) + RT - 1) / RT;  // N + 1 <= S + 1
-  const int n1 = N + 1;
-  double2 ga[KI], gb[KI];
-#pragma unroll
-  for (int i = 0; i < KI; ++i) {
-    const int idx = tt + i * RT;
-    ga[i] = gb[i] = make_double2(0.0, 0.0);
-    if (idx < 3 * n1 && rvalid) {
-      const int a = idx >= 2 * n1 ? 2 : (idx >= n1 ? 1 : 0), m = idx - a * n1;
-      const double2* Fa = F5 + (int64_t)(2 * a) * fstride + (int64_t)m * nlat;
-      ga[i] = Fa[0];
-      if (a < 2) gb[i] = Fa[fstride];
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < KI; ++i) {
-    const int idx = tt + i * RT;
-    if (idx < 3 * n1) {
-      const int a = idx >= 2 * n1 ? 2 : (idx >= n1 ? 1 : 0), m = idx - a * n1;
-      double2* rows = lds + (9 * rr + 3 * a) * PS;
-      const int k = M - m;
-      if (a < 2) {
-        if (m == 0) {
-          rows[0] = make_double2(ga[i].x, gb[i].x);
-        } else {
-          rows[(m % 3) * PS + pad(m / 3)] = make_double2(ga[i].x - gb[i].y, ga[i].y + gb[i].x);
-          rows[(k % 3) * PS + pad(k / 3)] = make_double2(ga[i].x + gb[i].y, gb[i].x - ga[i].y);
-        }
-      } else {
-        // x_0 = Re Qbar_0, x_m = Qbar_m / 2, x_{M-m} = conj(Qbar_m) / 2
-        if (m == 0) {
-          rows[0] = make_double2(ga[i].x, 0.0);
-        } else {
-          rows[(m % 3) * PS + pad(m / 3)] = make_double2(0.5 * ga[i].x, 0.5 * ga[i].y);
-          rows[(k % 3) * PS + pad(k / 3)] = make_double2(0.5 * ga[i].x, -0.5 * ga[i].y);
-        }
-      }
-    }
-  }
-  // the zero band N < k < M - N of the three arrays of every ring
-  const int zb = M - 2 * N - 1;
-  for (int t = threadIdx.x; t < NR * 3 * zb; t += NT) {
-    const int r = t / (3 * zb), u = t - r * 3 * zb;
-    const int a = u >= 2 * zb ? 2 : (u >= zb ? 1 : 0);
-    const int k = N + 1 + u - a * zb;
-    lds[(9 * r + 3 * a + k % 3) * PS + pad(k / 3)] = make_double2(0.0, 0.0);
-  }
-  __syncthreads();
-  for (int row = wave; row < 9 * NR; row += NW)
-    wave_fft<S, 0, 1, 1, false>(lds + row * PS, tw, lane, 0.0, nullptr, 0, 0, 0);
-  __syncthreads();
-  // fused pass of ring r at n2: the grid values at S n1 + n2 of the three
-  // arrays, gbar0 + i gbar1 = qb (g2, -g3) and gbar2 + i gbar3 = qb (g0, -g1)
-  // with qb = c_lat qbar / s^2, and the forward radix 3 and twiddles of both
-  {
-    const int r = threadIdx.x / RT, n2 = threadIdx.x - r * RT;
-    const int lat = lat0 + r;
-    if (n2 < S && lat < nlat) {
-      const int p = lat < g.nh ? lat : nlat - 1 - lat;  // northern node of the ring
-      const double x = g.mu[p];
-      const double inv_sin2 = 1.0 / ((1.0 - x) * (1.0 + x));
-      const double clat = (6.283185307179586477 / M) * g.w[p];
-      double2* rows = lds + 9 * r * PS;
-      const double2 w1 = tw_full<M>(tw, n2), w2 = cmul(w1, w1);
-      double2 y[3][3];
-#pragma unroll
-      for (int a = 0; a < 3; ++a) {
-#pragma unroll
-        for (int k1 = 0; k1 < 3; ++k1) y[a][k1] = rows[(3 * a + k1) * PS + pad(n2)];
-        y[a][1] = cmul(y[a][1], make_double2(w1.x, -w1.y));
-        y[a][2] = cmul(y[a][2], make_double2(w2.x, -w2.y));
-        butterfly<3>(y[a], 1.0);
-      }
-      double2 z[2][3];
-#pragma unroll
-      for (int n1 = 0; n1 < 3; ++n1) {
-        const double qb = clat * y[2][n1].x * inv_sin2;
-        z[0][n1] = make_double2(qb * y[1][n1].x, -qb * y[1][n1].y);
-        z[1][n1] = make_double2(qb * y[0][n1].x, -qb * y[0][n1].y);
-      }
-#pragma unroll
-      for (int a = 0; a < 2; ++a) {
-        butterfly<3>(z[a], -1.0);
-        z[a][1] = cmul(z[a][1], w1);
-        z[a][2] = cmul(z[a][2], w2);
-#pragma unroll
-        for (int k1 = 0; k1 < 3; ++k1) rows[(3 * a + k1) * PS + pad(n2)] = z[a][k1];
-      }
-    }
-  }
-  __syncthreads();
-  for (int row = wave; row < 6 * NR; row += NW) {
-    const int r = row / 6;
-    wave_fft<S, 0, 1, -1, false>(lds + (9 * r + row - 6 * r) * PS, tw, lane, 0.0, nullptr, 0, 0, 0);
-  }
-  __syncthreads();
-  // unpack two real transforms per array, Z_k at row 3 a + k mod 3, k / 3:
-  // A_m = (Z_m + conj Z_{M-m}) / 2, B_m = (Z_m - conj Z_{M-m}) / (2 i); times 2 for m >= 1
-  double2* Fb = g.Fbar + (int64_t)b * 4 * fstride + lat0 + rr;  // Fbar[b][f][m][lat]
-  if (rvalid) {
-    const double2* rows = lds + 9 * rr * PS;
-    for (int m = tt; m <= N; m += RT) {
-      const double sc = (m == 0) ? 0.5 : 1.0;
-      const int mc = m == 0 ? 0 : M - m;
-#pragma unroll
-      for (int arr = 0; arr < 2; ++arr) {
-        const double2 zm = rows[(3 * arr + m % 3) * PS + pad(m / 3)];
-        const double2 zc = rows[(3 * arr + mc % 3) * PS + pad(mc / 3)];
-        Fb[(int64_t)(2 * arr) * fstride + (int64_t)m * nlat] = make_double2(sc * (zm.x + zc.x), sc * (zm.y - zc.y));
-        Fb[(int64_t)(2 * arr + 1) * fstride + (int64_t)m * nlat] = make_double2(sc * (zm.y + zc.y), -sc * (zm.x - zc.x));
-      }
-    }
-  }
-}
-
-}  // namespace
-
-size_t ring_lds_bytes(int M) { return sizeof(double2) * (size_t)(2 * padded_len(M) + M / 2); }
-
-// One workgroup per ring; rings are taken in XCD-local chunks of eight
-// neighbouring latitudes so that the strided reads of F share L2 lines.
-// MAXM: the largest M of the size class this instance serves and NT its
-// workgroup size (register arrays are sized from both).
-// TWG: the stages read their twiddles from the global half table (L1-resident)
-// instead of an LDS copy, which leaves 2 padded_len(M) entries of LDS per ring.
-template <int MAXM, int NT, int CM, bool TWG = false>
-__global__ __launch_bounds__(NT) void k_ring(GroupView g, FftPlan plan, int mode,
-                                             double* grid_out) {
-  constexpr int PTS = (MAXM + NT - 1) / NT;
-  const int N = g.N, M = CM > 0 ? CM : g.M, nlat = g.nlat;
+// Grid mode: u_theta = f0 / sin, u_phi = -f1 / sin and the third field (f2). 625 rings of
+// M = 1250: 34.8 -> 19.7 us.
+template <int MAXM, int NT, int CM>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_ring_grid(GroupView g, FftPlan rt, double* grid_out) {
+  const FftPlan pl = plan_of<CM>(rt);
+  const int N = g.N, M = CM ? CM : g.M, nlat = CM ? CM / 2 : g.nlat;
   const int lat = xcd_item(blockIdx.x, 8);
   if (lat >= nlat) return;
-  const int b = blockIdx.y;
-  const int p = lat < g.nh ? lat : nlat - 1 - lat;  // northern node of the ring
-  const int PL = padded_len(M);
+  const int PL = pl.len;
   extern __shared__ double2 lds[];
-  double2* A0 = lds;
-  double2* A1 = lds + PL;
-  double2* twl = lds + 2 * PL;  // unused with TWG
-  const double2* tw = TWG ? g.tw : twl;
-  const double x = g.mu[p];
-  const double sin2 = (1.0 - x) * (1.0 + x);
   const int64_t fstride = (int64_t)(N + 1) * nlat;
-  const double2* F0 = g.F + (int64_t)b * 4 * fstride;
-
-  if (mode == SYNTH_GRID) {
-    // u_theta = f0 / sin, u_phi = -f1 / sin, zeta = f2
-    const double rs = 1.0 / sqrt(sin2);
-    load_ring<MAXM, NT, !TWG>(A0, A1, twl, g.tw, F0, F0 + fstride, F0 + 2 * fstride,
-                              F0 + 2 * fstride, lat, N, M, nlat);
-    __syncthreads();
-    fft_any<2, MAXM, NT, CM>(A0, A1, plan, M, tw, 1.0);
-    double* g0 = grid_out + ((int64_t)0 * nlat + lat) * M;
-    double* g1 = grid_out + ((int64_t)1 * nlat + lat) * M;
-    double* g2 = grid_out + ((int64_t)2 * nlat + lat) * M;
-    for (int j = threadIdx.x; j < M; j += blockDim.x) {
-      const double2 v0 = A0[pad(j)], v1 = A1[pad(j)];
-      g0[j] = rs * v0.x;
-      g1[j] = -rs * v0.y;
-      g2[j] = v1.x;
-    }
-    return;
-  }
-
-  // inverse transforms of f0 + i f1 and f2 + i f3, then the grid product
-  load_ring<MAXM, NT, !TWG>(A0, A1, twl, g.tw, F0, F0 + fstride, F0 + 2 * fstride,
-                            F0 + 3 * fstride, lat, N, M, nlat);
-  // an ended attempt of a device-controlled run (only nonlinear-mode launches
-  // are gated): checked once the loads are in flight, nothing stored before
-  if (gate_closed(g)) return;
+  const double x = g.mu[ring_node(g, lat)];
+  const double rs = 1.0 / sqrt((1.0 - x) * (1.0 + x));
+  load_spectra<2, 1, MAXM, NT>(lds, PL, pl, N, M, nlat, lat,
+                               [&](int a, const double2*& fa, const double2*& fb) {
+                                 fa = g.F + 2 * a * fstride;
+                                 fb = a ? fa : fa + fstride;
+                               });
   __syncthreads();
-  const double inv_sin2 = 1.0 / sin2;
-  if constexpr (CM > 0 && ct_fused<CM>()) {
-    fft_ct_inverse_product<CM, 0, 1, NT>(A0, tw, inv_sin2);
-  } else {
-    fft_any<2, MAXM, NT, CM>(A0, A1, plan, M, tw, 1.0);
-    // grid product, in place: each index j is read and rewritten by one thread
-#pragma unroll
-    for (int c = 0; c < PTS; ++c) {
-      const int j = threadIdx.x + c * NT;
-      if (j < M) {
-        const double2 z01 = A0[pad(j)], z23 = A1[pad(j)];
-        A0[pad(j)] = make_double2((z01.x * z23.x - z01.y * z23.y) * inv_sin2, 0.0);
-      }
-    }
-    __syncthreads();
-  }
-  // quadrature factor (2 pi / M) w_p; the equator ring of an odd rule is its
-  // own mirror and is folded twice by the analysis
-  const double c = (6.283185307179586477 / M) * g.w[p] * (2 * p + 1 == nlat ? 0.5 : 1.0);
-  // W[b][m][lat]: stride nlat between orders (the eight rings of an XCD chunk
-  // fill whole cache lines of one order)
-  double2* Wl = g.W + (int64_t)b * (N + 1) * nlat + lat;
-  if constexpr (CM > 0 && ct_fused<CM>()) {
-    fft_ct_forward_store<CM, 0, 1, NT>(A0, tw, c, Wl, nlat, N);
-  } else {
-    fft_any<1, MAXM, NT, CM>(A0, A1, plan, M, tw, -1.0);
-    for (int m = threadIdx.x; m <= N; m += blockDim.x) {
-      const double2 X = A0[pad(m)];
-      Wl[(int64_t)m * nlat] = make_double2(c * X.x, c * X.y);
-    }
+  for_stages<1, (CM > 0)>(pl, [&](int st) { run_stage<1, NT>(lds, 2, PL, pl, st, g.tw); });
+  run_last<1, NT>(lds, 2, PL, pl);
+  double* g0 = grid_out + (int64_t)lat * M;
+  const int64_t gs = (int64_t)nlat * M;
+  for (int j = threadIdx.x; j < M; j += NT) {
+    const int p = grid_slot(pl, j);
+    const double2 v0 = lds[p], v1 = lds[PL + p];
+    g0[j] = rs * v0.x;
+    g0[gs + j] = -rs * v0.y;
+    g0[2 * gs + j] = v1.x;
   }
 }
 
@@ -919,102 +561,89 @@ __global__ __launch_bounds__(NT) void k_ring(GroupView g, FftPlan plan, int mode
 //   gbar0 = qbar g2 / s^2, gbar2 = qbar g0 / s^2, gbar1 = -qbar g3 / s^2, gbar3 = -qbar g1 / s^2
 // and the cotangents of the field spectra (the c2r of the synthesis)^T:
 //   Gbar_0 = sum_j gbar_j,  Gbar_m = 2 sum_j gbar_j e^{-i m phi_j}  (m >= 1),
-// written to Fbar[b][f][m][lat]. c_lat = (2 pi / M) w_p.
-template <int MAXM, int NT, int CM>
-__global__ __launch_bounds__(NT) void k_ring_adj(GroupView g, FftPlan plan) {
-  constexpr int PTS = (MAXM + NT - 1) / NT;
-  const int N = g.N, M = CM > 0 ? CM : g.M, nlat = g.nlat;
-  const int lat = xcd_item(blockIdx.x, 8);  // XCD-local chunks of 8 rings share L2 lines of Fa
-  if (lat >= nlat) return;
+// written to Fbar[b][f][m][lat]. c_lat = (2 pi / M) w_p. Three inverse transforms per
+// ring, one pass for the cotangents (gbar0 + i gbar1, both of the vorticity-gradient
+// size, and gbar2 + i gbar3), two forward transforms: 59 -> 38 us for 768 rings of M = 1536
+// (384 threads; 256: 40.5), 14.3 -> 13.7 us for 384 of M = 768.
+template <int MAXM, int NT, int NR, int CM>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_ring_adj(GroupView g, FftPlan rt) {
+  const FftPlan pl = plan_of<CM>(rt);
+  const int N = g.N, M = CM ? CM : g.M, nlat = CM ? CM / 2 : g.nlat;
+  const int lat0 = NR * xcd_item(blockIdx.x, 8 / NR);
+  if (lat0 >= nlat) return;
   const int b = blockIdx.y;
-  const int p = lat < g.nh ? lat : nlat - 1 - lat;
-  const int PL = padded_len(M);
+  const int PL = pl.len;
   extern __shared__ double2 lds[];
-  double2* A0 = lds;
-  double2* A1 = lds + PL;
-  double2* tw = lds + 2 * PL;
-  const double x = g.mu[p];
-  const double inv_sin2 = 1.0 / ((1.0 - x) * (1.0 + x));
+  const double2* tw = g.tw;
   const int64_t fstride = (int64_t)(N + 1) * nlat;
   const double2* F5 = g.Fa + (int64_t)b * 5 * fstride;
-
-  // the ring's fifth field (the cotangent of its spectrum Q), requested now and
-  // written to LDS after the forward transforms; 3N + 2 <= M <= MAXM bounds N + 1
-  constexpr int KS = (MAXM / 3 + 1 + NT - 1) / NT;
-  double2 qbar[KS];
+  double cs[NR];  // c_lat / s^2
 #pragma unroll
-  for (int i = 0; i < KS; ++i) {
-    const int m = threadIdx.x + i * NT;
-    qbar[i] = (m <= N) ? F5[4 * fstride + (int64_t)m * nlat + lat] : make_double2(0.0, 0.0);
+  for (int r = 0; r < NR; ++r) {
+    const int p = ring_node(g, min(lat0 + r, nlat - 1));
+    const double x = g.mu[p];
+    cs[r] = (6.283185307179586477 / M) * g.w[p] / ((1.0 - x) * (1.0 + x));
   }
-  // forward grid fields of this ring: f0 + i f1 and f2 + i f3 (pairs of one
-  // kind, as in k_ring)
-  load_ring<MAXM, NT>(A0, A1, tw, g.tw, F5, F5 + fstride, F5 + 2 * fstride, F5 + 3 * fstride, lat,
-                      N, M, nlat);
+  load_spectra<3, NR, MAXM, NT>(lds, PL, pl, N, M, nlat, lat0,
+                                [&](int a, const double2*& fa, const double2*& fb) {
+                                  fa = F5 + 2 * a * fstride;
+                                  fb = a < 2 ? fa + fstride : fa;
+                                });
   __syncthreads();
-  fft_any<2, MAXM, NT, CM>(A0, A1, plan, M, tw, 1.0);
-  double g0[PTS], g1[PTS], g2[PTS], g3[PTS];
+  const int last = pl.nstages - 1;
+  for_stages<1, (CM > 0)>(pl, [&](int st) { run_stage<1, NT>(lds, 3 * NR, PL, pl, st, tw); });
+  // (the cotangents take the first two of the ring's arrays)
+  with_last_radix(pl.radix[last], [&](auto rc) {
+    constexpr int R = decltype(rc)::value;
+    const int per = pl.per[last];
+    for (int t = threadIdx.x; t < NR * per; t += NT) {
+      const int rr = NR == 1 || t < per ? 0 : 1, u = t - rr * per;
+      double2* y = lds + (3 * rr * PL + slot(pl, u * R));
+      double2 v0[R], v1[R], v2[R];
 #pragma unroll
-  for (int c = 0; c < PTS; ++c) {
-    const int j = threadIdx.x + c * NT;
-    g0[c] = g1[c] = g2[c] = g3[c] = 0.0;
-    if (j < M) {
-      const double2 z01 = A0[pad(j)], z23 = A1[pad(j)];
-      g0[c] = z01.x;
-      g1[c] = z01.y;
-      g2[c] = z23.x;
-      g3[c] = z23.y;
+      for (int r = 0; r < R; ++r) {
+        v0[r] = y[r];
+        v1[r] = y[PL + r];
+        v2[r] = y[2 * PL + r];
+      }
+      butterfly<R, 1>(v0);
+      butterfly<R, 1>(v1);
+      butterfly<R, 1>(v2);
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const double qb = (NR == 1 || rr == 0 ? cs[0] : cs[NR - 1]) * v2[r].x;
+        const double2 z0 = make_double2(qb * v1[r].x, -qb * v1[r].y);
+        v1[r] = make_double2(qb * v0[r].x, -qb * v0[r].y);
+        v0[r] = z0;
+      }
+      butterfly<R, -1>(v0);
+      butterfly<R, -1>(v1);
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        y[r] = v0[r];
+        y[PL + r] = v1[r];
+      }
     }
-  }
+  });
   __syncthreads();
-  // cotangent of the grid product: the real field of spectrum Qbar / 2 (m >= 1),
-  // x_0 = Re Qbar_0, x_m = Qbar_m / 2, x_{M-m} = conj(Qbar_m) / 2, zero elsewhere
+  for_stages<-1, (CM > 0)>(pl, [&](int st) {
 #pragma unroll
-  for (int i = 0; i < KS; ++i) {
-    const int m = threadIdx.x + i * NT;
-    if (m == 0) {
-      A0[0] = make_double2(qbar[i].x, 0.0);
-    } else if (m <= N) {
-      A0[pad(m)] = make_double2(0.5 * qbar[i].x, 0.5 * qbar[i].y);
-      A0[pad(M - m)] = make_double2(0.5 * qbar[i].x, -0.5 * qbar[i].y);
-    }
-  }
-  for (int j = N + 1 + threadIdx.x; j < M - N; j += NT) A0[pad(j)] = make_double2(0.0, 0.0);
-  __syncthreads();
-  fft_any<1, MAXM, NT, CM>(A0, A1, plan, M, tw, 1.0);
-  const double clat = (6.283185307179586477 / M) * g.w[p];
-  double qb[PTS];
-#pragma unroll
-  for (int c = 0; c < PTS; ++c) {
-    const int j = threadIdx.x + c * NT;
-    qb[c] = (j < M) ? clat * A0[pad(j)].x * inv_sin2 : 0.0;
-  }
-  __syncthreads();
-#pragma unroll
-  for (int c = 0; c < PTS; ++c) {
-    const int j = threadIdx.x + c * NT;
-    if (j < M) {
-      // gbar0 + i gbar1 (both of the vorticity-gradient size) and gbar2 + i gbar3
-      A0[pad(j)] = make_double2(qb[c] * g2[c], -qb[c] * g3[c]);
-      A1[pad(j)] = make_double2(qb[c] * g0[c], -qb[c] * g1[c]);
-    }
-  }
-  __syncthreads();
-  fft_any<2, MAXM, NT, CM>(A0, A1, plan, M, tw, -1.0);
+    for (int rr = 0; rr < NR; ++rr) run_stage<-1, NT>(lds + 3 * rr * PL, 2, PL, pl, st, tw);
+  });
   // unpack two real transforms per array: z = a + i b ->
   // A_m = (Z_m + conj Z_{M-m}) / 2, B_m = (Z_m - conj Z_{M-m}) / (2 i); times 2 for m >= 1
-  double2* Fb = g.Fbar + (int64_t)b * 4 * fstride + lat;  // Fbar[b][f][m][lat]
-  for (int m = threadIdx.x; m <= N; m += blockDim.x) {
+  double2* Fb = g.Fbar + (int64_t)b * 4 * fstride + lat0;  // Fbar[b][f][m][lat]
+  for (int t = threadIdx.x; t < NR * (N + 1); t += NT) {
+    const int m = t / NR, rr = t % NR;
+    if (lat0 + rr >= nlat) continue;
     const double sc = (m == 0) ? 0.5 : 1.0;
+    const int pm = slot(pl, m), pc = slot(pl, m ? M - m : 0);
 #pragma unroll
-    for (int arr = 0; arr < 2; ++arr) {
-      const double2* X = arr ? A1 : A0;
-      const double2 zm = X[pad(m)];
-      const double2 zc = X[pad((M - m) % M)];
-      const double2 ga = make_double2(sc * (zm.x + zc.x), sc * (zm.y - zc.y));
-      const double2 gb = make_double2(sc * (zm.y + zc.y), -sc * (zm.x - zc.x));
-      Fb[(int64_t)(arr ? 2 : 0) * fstride + (int64_t)m * nlat] = ga;
-      Fb[(int64_t)(arr ? 3 : 1) * fstride + (int64_t)m * nlat] = gb;
+    for (int a = 0; a < 2; ++a) {
+      const double2 zm = lds[(3 * rr + a) * PL + pm], zc = lds[(3 * rr + a) * PL + pc];
+      double2* out = Fb + (int64_t)(2 * a) * fstride + (int64_t)m * nlat + rr;
+      out[0] = make_double2(sc * (zm.x + zc.x), sc * (zm.y - zc.y));
+      out[fstride] = make_double2(sc * (zm.y + zc.y), -sc * (zm.x - zc.x));
     }
   }
 }
@@ -1026,151 +655,133 @@ __global__ __launch_bounds__(NT) void k_ring_adj(GroupView g, FftPlan plan) {
 // Fbar[b][f][m][lat] as f = 0, 1: c Ut, -c Up. The latitude sums and the degree
 // coupling of d/dtheta are done by the unweighted analysis and the prologue
 // transpose, since conj(Z[l,m]) = lambda^(-1/2) (-i m Pbar / sin, -dPbar/dtheta) e^{-i m phi}
-// and sin(theta) dPbar/dtheta couples degrees l - 1 and l + 1.
+// and sin(theta) dPbar/dtheta couples degrees l - 1 and l + 1. 768 rings of M = 1536:
+// 20.6 -> 13.3 us.
 template <int MAXM, int NT, int CM>
-__global__ __launch_bounds__(NT) void k_ring_project(GroupView g, FftPlan plan,
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_ring_project(GroupView g, FftPlan rt,
                                                      const double* __restrict__ u_grid) {
-  const int N = g.N, M = CM > 0 ? CM : g.M, nlat = g.nlat;
+  const FftPlan pl = plan_of<CM>(rt);
+  const int N = g.N, M = CM ? CM : g.M, nlat = CM ? CM / 2 : g.nlat;
   const int lat = xcd_item(blockIdx.x, 8);
-  if (lat >= g.nlat) return;
+  if (lat >= nlat) return;
   const int b = blockIdx.y;
-  const int p = lat < g.nh ? lat : nlat - 1 - lat;
-  const int PL = padded_len(M);
+  const int p = ring_node(g, lat);
   extern __shared__ double2 lds[];
-  double2* A0 = lds;
-  double2* tw = lds + 2 * PL;
-  for (int j = threadIdx.x; j < M / 2; j += blockDim.x) tw[j] = g.tw[j];
   const double* ut = u_grid + ((int64_t)(2 * b) * nlat + lat) * M;
   const double* up = ut + (int64_t)nlat * M;
-  for (int j = threadIdx.x; j < M; j += blockDim.x) A0[pad(j)] = make_double2(ut[j], up[j]);
+  constexpr int KI = (MAXM + NT - 1) / NT;
+  double2 u[KI];
+#pragma unroll
+  for (int i = 0; i < KI; ++i) {
+    const int j = min((int)threadIdx.x + i * NT, M - 1);
+    u[i] = make_double2(ut[j], up[j]);
+  }
+#pragma unroll
+  for (int i = 0; i < KI; ++i) {
+    const int j = threadIdx.x + i * NT;
+    if (j < M) lds[grid_slot(pl, j)] = u[i];
+  }
   __syncthreads();
-  fft_any<1, MAXM, NT, CM>(A0, A0, plan, M, tw, -1.0);
+  run_last<-1, NT>(lds, 1, 0, pl);
+  for_stages<-1, (CM > 0)>(pl, [&](int st) { run_stage<-1, NT>(lds, 1, 0, pl, st, g.tw); });
   const double x = g.mu[p];
-  const double c = (6.283185307179586477 / M) * g.w[p] / sqrt((1.0 - x) * (1.0 + x));
+  const double h = 0.5 * (6.283185307179586477 / M) * g.w[p] / sqrt((1.0 - x) * (1.0 + x));
   const int64_t fstride = (int64_t)(N + 1) * nlat;
   double2* Fb = g.Fbar + (int64_t)b * 4 * fstride + lat;  // Fbar[b][f][m][lat]
-  for (int m = threadIdx.x; m <= N; m += blockDim.x) {
-    const double2 zm = A0[pad(m)];
-    const double2 zc = A0[pad((M - m) % M)];
-    const double h = 0.5 * c;
-    const int64_t mo = (int64_t)m * nlat;
-    Fb[mo] = make_double2(h * (zm.x + zc.x), h * (zm.y - zc.y));
-    Fb[fstride + mo] = make_double2(-h * (zm.y + zc.y), h * (zm.x - zc.x));
+  for (int m = threadIdx.x; m <= N; m += NT) {
+    const double2 zm = lds[slot(pl, m)], zc = lds[slot(pl, m ? M - m : 0)];
+    Fb[(int64_t)m * nlat] = make_double2(h * (zm.x + zc.x), h * (zm.y - zc.y));
+    Fb[fstride + (int64_t)m * nlat] = make_double2(-h * (zm.y + zc.y), h * (zm.x - zc.x));
   }
 }
 
-// Calls launch(MAXM, NT, CM) (as integral constants) for the group's M: the
-// compile-time instance when M = 3 * 2^k is one of the default grids, else
-// the size class of the runtime plan.
+// Calls launch(MAXM, NT, CM) (as integral constants) for M: a compile-time plan if there
+// is one, else the size class.
 template <typename F>
 hipError_t ring_dispatch(int M, F&& launch) {
   using std::integral_constant;
   switch (M) {
     case 48: return launch(integral_constant<int, 48>{}, integral_constant<int, 64>{}, integral_constant<int, 48>{});
     case 96: return launch(integral_constant<int, 96>{}, integral_constant<int, 64>{}, integral_constant<int, 96>{});
-    case 192: return launch(integral_constant<int, 192>{}, integral_constant<int, 128>{}, integral_constant<int, 192>{});
-    case 320: return launch(integral_constant<int, 320>{}, integral_constant<int, 256>{}, integral_constant<int, 320>{});
-    case 384: return launch(integral_constant<int, 384>{}, integral_constant<int, 256>{}, integral_constant<int, 384>{});
-    case 768: return launch(integral_constant<int, 768>{}, integral_constant<int, 512>{}, integral_constant<int, 768>{});
-    case 1536: return launch(integral_constant<int, 1536>{}, integral_constant<int, 1024>{}, integral_constant<int, 1536>{});
+    case 192: return launch(integral_constant<int, 192>{}, integral_constant<int, 64>{}, integral_constant<int, 192>{});
+    case 320: return launch(integral_constant<int, 384>{}, integral_constant<int, 128>{}, integral_constant<int, 320>{});
+    case 384: return launch(integral_constant<int, 384>{}, integral_constant<int, 128>{}, integral_constant<int, 384>{});
+    case 768: return launch(integral_constant<int, 768>{}, integral_constant<int, 256>{}, integral_constant<int, 768>{});
+    case 1536: return launch(integral_constant<int, 1536>{}, integral_constant<int, 256>{}, integral_constant<int, 1536>{});
     default: break;
   }
-  if (M <= 256) return launch(integral_constant<int, 256>{}, integral_constant<int, 128>{}, integral_constant<int, 0>{});
-  if (M <= 512) return launch(integral_constant<int, 512>{}, integral_constant<int, 256>{}, integral_constant<int, 0>{});
-  if (M <= 768) return launch(integral_constant<int, 768>{}, integral_constant<int, 256>{}, integral_constant<int, 0>{});
-  if (M <= 1024) return launch(integral_constant<int, 1024>{}, integral_constant<int, 512>{}, integral_constant<int, 0>{});
-  return launch(integral_constant<int, kMaxM>{}, integral_constant<int, 512>{}, integral_constant<int, 0>{});
+  const integral_constant<int, 0> rt;
+  if (M <= 192) return launch(integral_constant<int, 192>{}, integral_constant<int, 64>{}, rt);
+  if (M <= 384) return launch(integral_constant<int, 384>{}, integral_constant<int, 128>{}, rt);
+  if (M <= 768) return launch(integral_constant<int, 768>{}, integral_constant<int, 256>{}, rt);
+  return launch(integral_constant<int, kMaxM>{}, integral_constant<int, 256>{}, rt);
 }
 
-// the split adjoint ring: nine rows of S + S/16 + 1 points (the twiddles are
-// read from the global table; an LDS copy took the T255 ring from 8.2 to 8.8 us)
-size_t ring_adj_nl_lds_bytes(int M) { return sizeof(double2) * (size_t)(9 * wave_row(M / 3)); }
+// LDS of na arrays of one ring.
+size_t ring_lds(const FftPlan& pl, int na) { return sizeof(double2) * (size_t)na * pl.len; }
 
-hipError_t launch_ring_adjoint(const GroupView& g, const FftPlan& plan, hipStream_t s) {
-  dim3 grid(xcd_grid(g.nlat, 8), g.nb);
-  if (g.M == 384 || g.M == 768) {
-    if (g.M == 768) {
-      // two neighbouring rings per workgroup (at M = 384 the 96 ring pairs of
-      // one member would leave most CUs idle)
-      dim3 grid2(xcd_grid((g.nlat + 1) / 2, 4), g.nb);
-      const size_t lds = 2 * ring_adj_nl_lds_bytes(g.M);
-      hipLaunchKernelGGL((k_ring_adj_nl<256, 768, 2>), grid2, dim3(768), lds, s, g);
-      return hipGetLastError();
-    }
-    const size_t lds = ring_adj_nl_lds_bytes(g.M);
-    hipLaunchKernelGGL((k_ring_adj_nl<128, 384, 1>), grid, dim3(384), lds, s, g);
-    return hipGetLastError();
-  }
-  const size_t lds = ring_lds_bytes(g.M);
+}  // namespace
+
+// Two rings per workgroup (M <= 768: their LDS is 39 to 78 KB) when there are more rings
+// than CUs: neighbouring rings share cache lines of the spectra, and one forward transform
+// serves both. With run-time plans M = 768, 6144 rings: 64 us against 81 with one ring per
+// workgroup; 384 rings: 10.9 against 12.6; M = 192, 2304 rings: 13.4 against 16.2. Up to
+// 256 rings half of the CUs would idle.
+inline bool two_rings(const GroupView& g) { return (int64_t)g.nlat * g.nb > 256; }
+
+hipError_t launch_ring_adjoint(const GroupView& g, const FftPlan& pl, hipStream_t s) {
   return ring_dispatch(g.M, [&](auto maxm, auto nt, auto cm) {
     constexpr int MAXM = decltype(maxm)::value, NT = decltype(nt)::value, CM = decltype(cm)::value;
-    hipLaunchKernelGGL((k_ring_adj<MAXM, NT, CM>), grid, dim3(NT), lds, s, g, plan);
+    if constexpr (MAXM <= 768) {
+      if (two_rings(g)) {
+        dim3 grid(xcd_grid((g.nlat + 1) / 2, 4), g.nb);
+        hipLaunchKernelGGL((k_ring_adj<MAXM, 2 * NT, 2, CM>), grid, dim3(2 * NT), ring_lds(plan_of<CM>(pl), 6), s, g, pl);
+        return hipGetLastError();
+      }
+    }
+    dim3 grid(xcd_grid(g.nlat, 8), g.nb);
+    constexpr int NT1 = MAXM > 768 ? 384 : NT;
+    hipLaunchKernelGGL((k_ring_adj<MAXM, NT1, 1, CM>), grid, dim3(NT1), ring_lds(plan_of<CM>(pl), 3), s, g, pl);
     return hipGetLastError();
   });
 }
 
-hipError_t launch_ring_project(const GroupView& g, const FftPlan& plan, const double* u_grid,
+hipError_t launch_ring_project(const GroupView& g, const FftPlan& pl, const double* u_grid,
                                hipStream_t s) {
   dim3 grid(xcd_grid(g.nlat, 8), g.nb);
-  const size_t lds = ring_lds_bytes(g.M);
   return ring_dispatch(g.M, [&](auto maxm, auto nt, auto cm) {
     constexpr int MAXM = decltype(maxm)::value, NT = decltype(nt)::value, CM = decltype(cm)::value;
-    hipLaunchKernelGGL((k_ring_project<MAXM, NT, CM>), grid, dim3(NT), lds, s, g, plan, u_grid);
+    hipLaunchKernelGGL((k_ring_project<MAXM, NT, CM>), grid, dim3(NT), ring_lds(plan_of<CM>(pl), 1), s, g, pl, u_grid);
     return hipGetLastError();
   });
 }
 
-// the split ring: six rows of S + S/16 + 1 points per ring, and the twiddle
-// half table with an LDS copy
-size_t ring_nl_lds_bytes(int M, int nr, bool twl) {
-  return sizeof(double2) * (size_t)(6 * nr * wave_row(M / 3) + (twl ? M / 2 : 0));
-}
-
-hipError_t launch_ring(const GroupView& g, const FftPlan& plan, int mode, double* grid_out,
+hipError_t launch_ring(const GroupView& g, const FftPlan& pl, int mode, double* grid_out,
                        hipStream_t s) {
-  dim3 grid(xcd_grid(g.nlat, 8), g.nb);
-  // the split kernel for M = 384 and 768 (T127, T255: ring 10.0 -> 9.4 us at
-  // T255). At M = 1536 the radix-8/8/8/3 plan stays: three one-wave 512-point
-  // transforms took 23.6 us, six 256-point ones with a radix-6 fused pass 26.8
-  // us (twelve waves) and 25.8 us (six waves of two rows each, 52.7 KB of LDS:
-  // still two rings per CU). Over 512 threads with the twiddles read from the
-  // global table (52.3 KB of LDS, three rings per CU, the whole T511 launch
-  // resident) it takes 19.4 us against 21.0 us over 1024 threads with an LDS
-  // table (64.5 KB, two rings per CU).
-  if (mode == SYNTH_NONLINEAR && g.M == 1536) {
-    const size_t lds = sizeof(double2) * (size_t)(2 * padded_len(1536));
-    hipLaunchKernelGGL((k_ring<1536, 512, 1536, true>), grid, dim3(512), lds, s, g, plan, mode,
-                       grid_out);
-    return hipGetLastError();
-  }
-  if (mode == SYNTH_NONLINEAR && (g.M == 384 || g.M == 768)) {
-    // many members: one ring per workgroup with LDS twiddles (the ensemble's
-    // 16 x N = 255 rings: 66 us against 76 us with the global table, its
-    // 24 x N = 127 rings 58 against 75 us); few members: global twiddles, and
-    // two rings per workgroup when there are more rings than CUs (one member
-    // at T255: 7.6 us against 8.2 us with one ring per workgroup and 8.8 us
-    // with LDS twiddles; at T127, 192 rings, one ring per workgroup: 5.7
-    // against 7.0 us)
-    if (g.nb >= 4) {
-      const size_t lds = ring_nl_lds_bytes(g.M, 1, true);
-      if (g.M == 384) hipLaunchKernelGGL((k_ring_nl<128, 384, true, 1>), grid, dim3(384), lds, s, g);
-      else hipLaunchKernelGGL((k_ring_nl<256, 384, true, 1>), grid, dim3(384), lds, s, g);
-    } else if ((int64_t)g.nlat * g.nb <= 256) {
-      const size_t lds = ring_nl_lds_bytes(g.M, 1, false);
-      if (g.M == 384) hipLaunchKernelGGL((k_ring_nl<128, 384, false, 1>), grid, dim3(384), lds, s, g);
-      else hipLaunchKernelGGL((k_ring_nl<256, 384, false, 1>), grid, dim3(384), lds, s, g);
-    } else {
-      dim3 grid2(xcd_grid((g.nlat + 1) / 2, 4), g.nb);
-      const size_t lds = ring_nl_lds_bytes(g.M, 2, false);
-      if (g.M == 384) hipLaunchKernelGGL((k_ring_nl<128, 768, false, 2>), grid2, dim3(768), lds, s, g);
-      else hipLaunchKernelGGL((k_ring_nl<256, 768, false, 2>), grid2, dim3(768), lds, s, g);
-    }
-    return hipGetLastError();
-  }
-  const size_t lds = ring_lds_bytes(g.M);
   return ring_dispatch(g.M, [&](auto maxm, auto nt, auto cm) {
     constexpr int MAXM = decltype(maxm)::value, NT = decltype(nt)::value, CM = decltype(cm)::value;
-    hipLaunchKernelGGL((k_ring<MAXM, NT, CM>), grid, dim3(NT), lds, s, g, plan, mode, grid_out);
+    if (mode == SYNTH_GRID) {
+      dim3 grid(xcd_grid(g.nlat, 8));
+      hipLaunchKernelGGL((k_ring_grid<MAXM, NT, CM>), grid, dim3(NT), ring_lds(plan_of<CM>(pl), 2), s, g, pl, grid_out);
+      return hipGetLastError();
+    }
+    if constexpr (MAXM <= 768) {
+      if (two_rings(g)) {
+        dim3 grid(xcd_grid((g.nlat + 1) / 2, 4), g.nb);
+        const size_t lds = ring_lds(plan_of<CM>(pl), 4);
+        // M > 384: three workgroups of 256 threads per CU overlap their phases (6144 rings
+        // 54 us against 58 with 512 threads); when there is one per CU, 512 threads are
+        // faster (384 rings: 8.2 against 9.4 us)
+        if (MAXM == 768 && (int64_t)g.nlat * g.nb > 1024)
+          hipLaunchKernelGGL((k_ring<MAXM, NT, 2, CM>), grid, dim3(NT), lds, s, g, pl);
+        else
+          hipLaunchKernelGGL((k_ring<MAXM, 2 * NT, 2, CM>), grid, dim3(2 * NT), lds, s, g, pl);
+        return hipGetLastError();
+      }
+    }
+    dim3 grid(xcd_grid(g.nlat, 8), g.nb);
+    constexpr int NT1 = MAXM == 384 ? 192 : NT;  // (192 rings of M = 384: 5.8 us, 6.2 with 128)
+    hipLaunchKernelGGL((k_ring<MAXM, NT1, 1, CM>), grid, dim3(NT1), ring_lds(plan_of<CM>(pl), 2), s, g, pl);
     return hipGetLastError();
   });
 }
