@@ -1,8 +1,9 @@
 // Split-bf16 Legendre contractions on MFMA (the synthesis and analysis of
 // Section 4.2 with bf16 products and FP32 accumulation).
 //
-// The tables are the FP64 recurrence values rounded to FP32 (half the bytes of
-// the FP64 pass). Each operand x is split into three bf16 pieces
+// The Legendre values are continued by the FP64 recurrence of eq. (sph_har) from two
+// seed rows of the table T1 per 32 degrees, and rounded to FP32. Each operand x is
+// split into three bf16 pieces
 // x ~ x0 + x1 + x2 (each the rounded remainder of the previous ones), and the
 // six products xi*yj with i + j <= 2 (relative weight >= 2^-16) run on
 // v_mfma_f32_16x16x32_bf16, accumulating in FP32 over blocks of 32 terms; the
@@ -10,24 +11,35 @@
 // panels, the quadrature weights, the FFTs, the grid products and the time-step
 // update stay in FP64.
 //
-// Synthesis: per (order m, 64-latitude tile) a workgroup of four waves; wave w
-// computes C[16 latitudes][16 columns] = sum_k T1[m][k][lat] B[k][col] over the
+// Synthesis: per (order m, 128-latitude tile) a workgroup of eight waves; wave w
+// computes C[16 latitudes][16 columns] = sum_k T[k][lat] B[k][col] over the
 // whole degree range, with columns 0-7 the even-degree and 8-15 the odd-degree
-// panel values (4 fields x re/im). B is the same for the four waves and is
+// panel values (4 fields x re/im). B is the same for the eight waves and is
 // split once per workgroup into LDS in operand order (only the four degrees of
 // each column's parity; the rest of the operand is zero). The northern value is
-// E + O and the mirrored southern value E - O.
-// Analysis: per (order m, 64-degree tile) four waves; wave w computes
-// C[4 used rows][16 degrees] = sum_p A[row][p] T2[m][p][k] with rows We.re,
-// We.im, Wo.re, Wo.im (the ring spectra folded over latitude pairs, split once
+// E + O and the mirrored southern value E - O. The wave takes four blocks of 32 degrees
+// at a time: lane (lat, q) continues the 32 degrees of block q, and lanes of one
+// latitude then exchange groups of eight degrees (4 x 4, by register swaps), so that each
+// holds its operand of all four blocks.
+// Analysis: per (order m, 128-degree tile) four waves; wave w computes
+// C[4 used rows][16 degrees] = sum_p A[row][p] T[p][k] for two tiles of 16 degrees, with
+// rows We.re, We.im, Wo.re, Wo.im (the ring spectra folded over latitude pairs, split once
 // per workgroup into LDS; only the four live rows are stored), then the
-// epilogue of spectral_ops.h.
-// The table operand of the next block is loaded while the current one is
-// multiplied.
+// epilogue of spectral_ops.h. A lane continues its latitude over the 32 degrees; the
+// values pass through LDS (a wave's own, degree-major, rows of 68: free of bank
+// conflicts) to the lanes that hold a degree of the operand.
+//
+// Bound by vector instructions: per 2048 values of a wave about 430 (recurrence and
+// rounding 122, exchange 32, splits 200, FP64 sums 48), 20 us of issue at N = 511; the six
+// products take a fifth of that on the matrix cores. Streaming the values from FP32
+// tables (200 MB for each contraction) took 54.6 us for the synthesis and 53.6 for the
+// analysis; now 42.5 and 42.
 //
 // MFMA operand layouts (checked on gfx950): for 16x16x32 bf16, lane l supplies
 // row l%16 of A and column l%16 of B for K = 8*(l/16) .. +7, and receives C rows
 // 4*(l/16) .. +3 of column l%16.
+#include <type_traits>
+
 #include "spectral_ops.h"
 
 namespace nse {
@@ -40,6 +52,11 @@ namespace {
 
 constexpr int kLpWaves = 4;
 constexpr int kLpThreads = 64 * kLpWaves;
+constexpr int kSynWaves = 8;                  // of 16 latitudes
+constexpr int kSynThreads = 64 * kSynWaves, kSynTile = 16 * kSynWaves;
+constexpr int kLpSeg = 32;                    // degrees continued from one seed pair
+constexpr int kLpTile = kLpWaves * kLpSeg;    // degrees per workgroup of the analysis
+constexpr int kLpRow = 68;                    // row of 64 latitudes in the exchange
 
 // x ~ h0 + h1 + h2 with h0 = bf16(x), h1 = bf16(x - h0), h2 = bf16(x - h0 - h1).
 // For a double x the remainders are formed exactly in FP64.
@@ -85,15 +102,36 @@ __device__ __forceinline__ bf16x8 interleave(bf16x4 v, int par) {
   return r;
 }
 
+// Swaps lanes 16-31 (48-63) of a with lanes 0-15 (32-47) of b.
+__device__ __forceinline__ void swap16(float& a, float& b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  a = __uint_as_float(r[0]);
+  b = __uint_as_float(r[1]);
+}
+// Swaps lanes 32-63 of a with lanes 0-31 of b.
+__device__ __forceinline__ void swap32(float& a, float& b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  a = __uint_as_float(r[0]);
+  b = __uint_as_float(r[1]);
+}
+
+// The lanes of a wave exchange values through the wave's own LDS: its accesses complete
+// in order, the compiler must not move them across.
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 }  // namespace
 
 // LDS: the split panel [block][piece][64 lanes] with only the four degrees of
 // the lane's parity stored (bf16x4; the other four of the operand are zero),
-// reused for the 4 x 256 FP64 partial results at the end.
+// and the recurrence pairs up to a multiple of four blocks; reused for the 8 x 256 FP64
+// partial results at the end.
 size_t synthesis_lp_lds_bytes(int N) {
   const int nblk = (N + 2 + 31) / 32;
-  size_t split = (size_t)nblk * 3 * 64 * sizeof(bf16x4);
-  const size_t cst = sizeof(double) * kLpWaves * 256;
+  size_t split = (size_t)nblk * 3 * 64 * sizeof(bf16x4) + (size_t)((nblk + 3) / 4) * 4 * (kLpSeg + 1) * sizeof(double2);
+  const size_t cst = sizeof(double) * kSynWaves * 256;
   return split > cst ? split : cst;
 }
 
@@ -145,10 +183,10 @@ __global__ __launch_bounds__(kLpThreads) void k_split_panel_lp(GroupView g, Synt
   }
 }
 
-__global__ __launch_bounds__(kLpThreads) void k_synthesis_lp(GroupView g, SynthInput in, int mode) {
+__global__ __launch_bounds__(kSynThreads) void k_synthesis_lp(GroupView g, SynthInput in, int mode) {
   if (gate_closed(g)) return;  // an ended attempt of a device-controlled run
   const int N = g.N, nh = g.nh, nlat = g.nlat;
-  const int ntile = (nh + 63) / 64;
+  const int ntile = (nh + kSynTile - 1) / kSynTile;
   const int m = blockIdx.x / ntile;
   const int tile = blockIdx.x - m * ntile;
   const int b = blockIdx.y;
@@ -160,45 +198,75 @@ __global__ __launch_bounds__(kLpThreads) void k_synthesis_lp(GroupView g, SynthI
   // the order's split panel (k_split_panel_lp), copied into LDS
   const bf16x4* src =
       reinterpret_cast<const bf16x4*>(g.lps + (int64_t)b * g.lpsoff[N + 1] + g.lpsoff[m]);
-  for (int it = threadIdx.x; it < nblk * 3 * 64; it += blockDim.x) bsplit[it] = src[it];
-  __syncthreads();
-  const int mypar = (threadIdx.x & 15) >> 3;
-
+  const int nsup = (nblk + 3) / 4;
+  const double2* rec = g.rec_a + rec_slot(N, m, m);
+  double2* rc = reinterpret_cast<double2*>(bsplit + nblk * 3 * 64);  // [4 nsup][kLpSeg + 1]: rows
+  // of one slot more, so that the four q read different banks
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int r16 = lane & 15, q = lane >> 4;
-  const int prow = tile * 64 + wave * 16 + r16;  // latitude row supplied to A
+  const int prow = tile * kSynTile + wave * 16 + r16;  // latitude row supplied to A
   const bool row_ok = prow < nh;
-  const float* T = g.T1f + t1_order_offset(N, m, nh) + prow;
+  const double* T = g.T1 + t1_order_offset(N, m, nh) + min(prow, nh - 1);
+  const double x = row_ok ? g.mu[min(prow, nh - 1)] : 0.0;
+  // seeds of the lane's block 4 s + q: degrees 32 (4 s + q) and the next
+  auto seeds = [&](int s, double& p0, double& p1) {
+    const int k = kLpSeg * (4 * s + q);
+    p0 = T[(int64_t)min(k, L - 1) * nh];
+    p1 = T[(int64_t)min(k + 1, L - 1) * nh];
+    if (!row_ok || k >= L) p0 = 0.0;
+    if (!row_ok || k + 1 >= L) p1 = 0.0;
+  };
+  double n0, n1;
+  seeds(0, n0, n1);
+  for (int it = threadIdx.x; it < nblk * 3 * 32; it += kSynThreads)
+    reinterpret_cast<uint4*>(bsplit)[it] = reinterpret_cast<const uint4*>(src)[it];
+  for (int k = threadIdx.x; k < 4 * kLpSeg * nsup; k += kSynThreads)
+    rc[k + k / kLpSeg] = k < L ? rec[k] : make_double2(0.0, 0.0);
+  __syncthreads();
+  const int mypar = r16 >> 3;
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
-  float tn[8];
+  for (int s = 0; s < nsup; ++s) {
+    double p2 = n0, p1 = n1;
+    if (s + 1 < nsup) seeds(s + 1, n0, n1);
+    const double2* c = rc + (kLpSeg + 1) * (4 * s + q);
+    float v[kLpSeg];
+    v[0] = (float)p2;
+    v[1] = (float)p1;
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const int k = 8 * q + j;
-    tn[j] = (row_ok && k < L) ? T[(int64_t)k * nh] : 0.f;
-  }
-  for (int kb = 0; kb < nblk; ++kb) {
-    float tc[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) tc[j] = tn[j];
+    for (int i = 2; i < kLpSeg; ++i) {
+      const double t = fma(c[i].x * x, p1, -c[i].y * p2);
+      p2 = p1;
+      p1 = t;
+      v[i] = (float)t;
+    }
+    // v[8 g + j] of lane (lat, q), group g of block q -> group q of block g
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-      const int k = (kb + 1) * 32 + 8 * q + j;
-      tn[j] = (row_ok && k < L) ? T[(int64_t)k * nh] : 0.f;
+      swap16(v[j], v[8 + j]);
+      swap16(v[16 + j], v[24 + j]);
+      swap32(v[j], v[16 + j]);
+      swap32(v[8 + j], v[24 + j]);
     }
-    bf16x8 a0, a1, a2;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      __bf16 h0, h1, h2;
-      split3f(tc[j], h0, h1, h2);
-      a0[j] = h0;
-      a1[j] = h1;
-      a2[j] = h2;
+    for (int i = 0; i < 4; ++i) {
+      const int kb = 4 * s + i;
+      if (kb < nblk) {
+        bf16x8 a0, a1, a2;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          __bf16 h0, h1, h2;
+          split3f(v[8 * i + j], h0, h1, h2);
+          a0[j] = h0;
+          a1[j] = h1;
+          a2[j] = h2;
+        }
+        const bf16x4* B = bsplit + kb * 3 * 64 + lane;
+        const floatx4 cc = mfma_bf16x3(a0, a1, a2, interleave(B[0], mypar), interleave(B[64], mypar),
+                                       interleave(B[128], mypar));
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[r] += (double)cc[r];
+      }
     }
-    const bf16x4* B = bsplit + kb * 3 * 64 + lane;
-    const floatx4 cc = mfma_bf16x3(a0, a1, a2, interleave(B[0], mypar), interleave(B[64], mypar),
-                                   interleave(B[128], mypar));
-#pragma unroll
-    for (int i = 0; i < 4; ++i) acc[i] += (double)cc[i];
   }
   __syncthreads();  // the split panel is no longer needed: reuse it
   // C rows 4q+i (latitudes of this wave), column r16
@@ -206,9 +274,9 @@ __global__ __launch_bounds__(kLpThreads) void k_synthesis_lp(GroupView g, SynthI
   for (int i = 0; i < 4; ++i) cst[(wave * 16 + 4 * q + i) * 16 + r16] = acc[i];
   __syncthreads();
   // one (field, latitude) per thread: E = columns 2f, 2f+1; O = columns 8+2f, 9+2f
-  const int f = threadIdx.x >> 6;
-  const int latl = threadIdx.x & 63;
-  const int p = tile * 64 + latl;
+  const int f = threadIdx.x / kSynTile;
+  const int latl = threadIdx.x % kSynTile;
+  const int p = tile * kSynTile + latl;
   const int nf = (mode == SYNTH_NONLINEAR) ? 4 : 3;
   if (f >= nf || p >= nh) return;
   const double* row = cst + latl * 16;
@@ -219,25 +287,53 @@ __global__ __launch_bounds__(kLpThreads) void k_synthesis_lp(GroupView g, SynthI
   if (ps != p) out[ps] = make_double2(er - orr, ei - oi);
 }
 
-// LDS: folded spectra We, Wo [2][nh], then the split A operand
-// [block][piece][4 K-slices][4 live rows] (rows 4..15 of A are zero).
+// LDS: the split A operand [block][piece][4 K-slices][4 live rows] (rows 4..15 of A are
+// zero), the tile's recurrence pairs, then the folded spectra We, Wo [2][nh] and in
+// their place the waves' exchange rows (at most 28 KB: five workgroups per CU, so that
+// the orders of N = 511 are resident at once).
 size_t analysis_lp_lds_bytes(int nh) {
   const int nblk = (nh + 31) / 32;
-  return 2 * sizeof(double2) * (size_t)nh + (size_t)nblk * 3 * 16 * sizeof(bf16x8);
+  const size_t fold = 2 * sizeof(double2) * (size_t)nh;
+  const size_t ex = (size_t)kLpWaves * 16 * kLpRow * sizeof(float);
+  return (size_t)nblk * 3 * 16 * sizeof(bf16x8) + kLpTile * sizeof(double2) + (fold > ex ? fold : ex);
 }
 
-__global__ __launch_bounds__(kLpThreads) void k_analysis_lp(GroupView g, AnalOutput out) {
+__global__ __launch_bounds__(kLpThreads) __attribute__((amdgpu_waves_per_eu(5))) void k_analysis_lp(GroupView g, AnalOutput out) {
   if (gate_closed(g)) return;  // an ended attempt of a device-controlled run
   const int N = g.N, nh = g.nh;
-  const int ntile = (N + 1 + 63) / 64;
+  const int ntile = (N + kLpTile) / kLpTile;
   const int item = xcd_item(blockIdx.x, 4 * ntile);
   const int m = item / ntile;
-  const int tile = item - m * ntile;
-  if (m > N || tile * 64 > N - m) return;  // uniform across the workgroup
+  // tiles of high degree have less to do or nothing, so the tile that a CU's successive
+  // workgroups take changes (as does the wave with the last, partial segment): 55 -> 42 us
+  // at N = 511, where the CUs were busy 36 us on average
+  const int tile = (item - m * ntile + (m >> 6)) % ntile;
+  if (m > N || tile * kLpTile > N - m) return;  // uniform across the workgroup
   const int b = blockIdx.y;
   const int nblk = (nh + 31) / 32;
-  extern __shared__ double2 wsh[];  // We [nh], Wo [nh], then the split A operand
-  bf16x8* asplit = reinterpret_cast<bf16x8*>(wsh + 2 * nh);  // [nblk][3][16]
+  extern __shared__ double2 sh[];
+  bf16x8* asplit = reinterpret_cast<bf16x8*>(sh);  // [nblk][3][16]
+  double2* rc = reinterpret_cast<double2*>(asplit + nblk * 3 * 16);
+  double2* wsh = rc + kLpTile;  // We [nh], Wo [nh]; then the waves' exchange rows
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int seg = (wave + m) % kLpWaves;
+  const int kw = tile * kLpTile + seg * kLpSeg;  // the wave's first degree offset
+  const bool active = kw <= N - m;
+  const double* T = g.T1 + t1_order_offset(N, m, nh) + (int64_t)min(kw, N - m) * nh;
+  // the lane's latitude 64 s + lane, and its seeds: degrees kw and kw + 1
+  auto seeds = [&](int s, double& p0, double& p1, double& x) {
+    const int p = min(64 * s + lane, nh - 1);
+    p0 = T[p];
+    p1 = T[nh + p];
+    x = g.mu[p];
+    if (64 * s + lane >= nh) p0 = p1 = 0.0;
+  };
+  double n0, n1, nx;
+  seeds(0, n0, n1, nx);
+  if ((int)threadIdx.x < kLpTile) {
+    const int k = tile * kLpTile + threadIdx.x;
+    rc[threadIdx.x] = k <= N + 1 - m ? g.rec_a[rec_slot(N, m, m) + k] : make_double2(0.0, 0.0);
+  }
   const double2* Wb = g.W + ((int64_t)b * (N + 1) + m) * g.nlat;
   for (int p = threadIdx.x; p < nh; p += blockDim.x) {
     const double2 qn = Wb[p];
@@ -270,55 +366,76 @@ __global__ __launch_bounds__(kLpThreads) void k_analysis_lp(GroupView g, AnalOut
   }
   __syncthreads();
 
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if (!active) return;
   const int r16 = lane & 15, q = lane >> 4;
-  const int kcol = tile * 64 + wave * 16 + r16;  // degree offset of this lane's B column
-  const bool col_ok = m + kcol <= N;
-  // rows p of this 64-degree tile, contiguous; this lane's degree column
-  const float* T = g.T2f + g.t2off[m] + (int64_t)tile * nh * kTile + wave * 16 + r16;
+  float* ex = reinterpret_cast<float*>(wsh) + wave * 16 * kLpRow;  // [16 degrees][kLpRow]
   bf16x8 zero8;
 #pragma unroll
   for (int j = 0; j < 8; ++j) zero8[j] = (__bf16)0.0f;
-  double acc[4] = {0.0, 0.0, 0.0, 0.0};
-  float tn[8];
+  double acc0[4] = {0.0, 0.0, 0.0, 0.0}, acc1[4] = {0.0, 0.0, 0.0, 0.0};
+  const double2* c = rc + seg * kLpSeg;
+  for (int s = 0; 2 * s < nblk; ++s) {
+    double p2 = n0, p1 = n1;
+    const double x = nx;
+    if (2 * s + 2 < nblk) seeds(s + 1, n0, n1, nx);
+    bf16x8 a[2][3];
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const int p = 8 * q + j;
-    tn[j] = (col_ok && p < nh) ? T[(int64_t)p * kTile] : 0.f;
+    for (int i = 0; i < 2; ++i) {
+      const int pb = min(2 * s + i, nblk - 1);
+      const bf16x8* A = asplit + pb * 3 * 16 + q * 4 + (r16 & 3);
+#pragma unroll
+      for (int r = 0; r < 3; ++r) a[i][r] = r16 < 4 ? A[16 * r] : zero8;
+    }
+    auto half = [&](auto hc, double(&ac)[4]) {
+      constexpr int h = decltype(hc)::value;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int d = 16 * h + i;
+        double t = d == 0 ? p2 : p1;
+        if (d >= 2) {
+          t = fma(c[d].x * x, p1, -c[d].y * p2);
+          p2 = p1;
+          p1 = t;
+        }
+        ex[i * kLpRow + lane] = (float)t;
+      }
+      wave_fence();
+      floatx4 v[2][2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          v[i][j] = *reinterpret_cast<const floatx4*>(ex + r16 * kLpRow + 32 * i + 8 * q + 4 * j);
+      wave_fence();
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        if (2 * s + i < nblk) {
+          bf16x8 b0, b1, b2;
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            __bf16 h0, h1, h2;
+            split3f(v[i][j >> 2][j & 3], h0, h1, h2);
+            b0[j] = h0;
+            b1[j] = h1;
+            b2[j] = h2;
+          }
+          const floatx4 cc = mfma_bf16x3(a[i][0], a[i][1], a[i][2], b0, b1, b2);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) ac[r] += (double)cc[r];
+        }
+      }
+    };
+    half(std::integral_constant<int, 0>{}, acc0);
+    half(std::integral_constant<int, 1>{}, acc1);
   }
-  for (int pb = 0; pb < nblk; ++pb) {
-    float tc[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) tc[j] = tn[j];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int p = (pb + 1) * 32 + 8 * q + j;
-      tn[j] = (col_ok && p < nh) ? T[(int64_t)p * kTile] : 0.f;
-    }
-    bf16x8 b0, b1, b2;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      __bf16 h0, h1, h2;
-      split3f(tc[j], h0, h1, h2);
-      b0[j] = h0;
-      b1[j] = h1;
-      b2[j] = h2;
-    }
-    bf16x8 a0 = zero8, a1 = zero8, a2 = zero8;
-    if (r16 < 4) {
-      const bf16x8* A = asplit + pb * 3 * 16 + q * 4 + r16;
-      a0 = A[0];
-      a1 = A[16];
-      a2 = A[32];
-    }
-    const floatx4 cc = mfma_bf16x3(a0, a1, a2, b0, b1, b2);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) acc[i] += (double)cc[i];
-  }
-  // lanes 0..15 hold rows 0..3 (We.re, We.im, Wo.re, Wo.im) of degree kcol
-  if (q != 0 || !col_ok) return;
-  const bool odd = kcol & 1;
-  finish_degree(g, out, b, m, kcol, odd ? acc[2] : acc[0], odd ? acc[3] : acc[1]);
+  // lanes 0..15 hold rows 0..3 (We.re, We.im, Wo.re, Wo.im) of the degrees kw + 16 h + r16
+  if (q != 0) return;
+  auto finish = [&](int k, const double(&ac)[4]) {
+    const bool odd = k & 1;
+    if (k <= N - m) finish_degree(g, out, b, m, k, odd ? ac[2] : ac[0], odd ? ac[3] : ac[1]);
+  };
+  finish(kw + r16, acc0);
+  finish(kw + 16 + r16, acc1);
 }
 
 hipError_t launch_synthesis_lp(const GroupView& g, const SynthInput& in, int mode, int prec,
@@ -327,16 +444,16 @@ hipError_t launch_synthesis_lp(const GroupView& g, const SynthInput& in, int mod
   if (!g.lps) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_split_panel_lp, dim3(g.N + 1, g.nb), dim3(kLpThreads),
                      split_panel_lp_lds_bytes(g.N), s, g, in, mode);
-  const int ntile = (g.nh + 63) / 64;
+  const int ntile = (g.nh + kSynTile - 1) / kSynTile;
   dim3 grid((g.N + 1) * ntile, g.nb);
-  hipLaunchKernelGGL(k_synthesis_lp, grid, dim3(kLpThreads), synthesis_lp_lds_bytes(g.N), s, g,
+  hipLaunchKernelGGL(k_synthesis_lp, grid, dim3(kSynThreads), synthesis_lp_lds_bytes(g.N), s, g,
                      in, mode);
   return hipGetLastError();
 }
 
 hipError_t launch_analysis_lp(const GroupView& g, const AnalOutput& out, int prec, hipStream_t s) {
   if (prec != NSE_PREC_BF16X3) return hipErrorInvalidValue;
-  const int ntile = (g.N + 1 + 63) / 64;
+  const int ntile = (g.N + kLpTile) / kLpTile;
   dim3 grid(xcd_grid((g.N + 1) * ntile, 4 * ntile), g.nb);
   hipLaunchKernelGGL(k_analysis_lp, grid, dim3(kLpThreads), analysis_lp_lds_bytes(g.nh), s, g,
                      out);

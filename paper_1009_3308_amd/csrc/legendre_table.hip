@@ -2,9 +2,7 @@
 // Gauss-Legendre nodes (Section 2, eq. (sph_har), with the Condon-Shortley
 // phase and int_{-1}^{1} Pbar^2 dmu = 1 / (2 pi)), computed once per group in
 // FP64 on the GPU and stored as T1[m][k][p] (latitude fastest: seeds of the
-// degree-by-degree recurrences); for the split-bf16 mode, rounded to FP32, as T1f in the
-// same layout (its synthesis) and T2f[m][deg tile][p][64] (degree fastest: its analysis),
-// for l = m .. N+1 (k = l - m; the sin(theta) d/dtheta fields reach degree N+1).
+// degree-by-degree recurrences) for l = m .. N+1 (k = l - m; the sin(theta) d/dtheta fields reach degree N+1).
 // The southern hemisphere follows from Pbar[l,m](-mu) = (-1)^(l+m) Pbar[l,m](mu).
 #include "nse_internal.h"
 
@@ -15,7 +13,7 @@ namespace nse {
 //   Pbar[l,m]   = a(l,m) (mu Pbar[l-1,m] - Pbar[l-2,m] / a(l-1,m)),
 //   a(l,m)      = sqrt((4 l^2 - 1) / (l^2 - m^2)).
 // Values that leave the double range near the poles flush to zero.
-__global__ void k_legendre_table(GroupView g, int m0, double* T1, float* T1f, float* T2f) {
+__global__ void k_legendre_table(GroupView g, int m0, double* T1) {
   const int m = m0 + blockIdx.y;
   const int p = blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= g.nh || m > g.N) return;
@@ -26,7 +24,6 @@ __global__ void k_legendre_table(GroupView g, int m0, double* T1, float* T1f, fl
   double pmm = 0.28209479177387814347;  // 1 / sqrt(4 pi)
   for (int k = 1; k <= m; ++k) pmm *= -sqrt((2.0 * k + 1.0) / (2.0 * k)) * s;
   const int64_t b1 = t1_order_offset(N, m, nh) + p;
-  const int64_t b2 = g.t2off[m] + (int64_t)p * kTile;
   double prev2 = 0.0, prev1 = pmm;
   double a_prev = 0.0;
   for (int k = 0; k < L; ++k) {
@@ -41,22 +38,16 @@ __global__ void k_legendre_table(GroupView g, int m0, double* T1, float* T1f, fl
       prev2 = prev1;
       prev1 = v;
     }
-    const int64_t i1 = b1 + (int64_t)k * nh;
-    const int64_t i2 = b2 + (int64_t)(k / kTile) * nh * kTile + (k % kTile);
-    T1[i1] = v;
-    if (T1f) {
-      T1f[i1] = (float)v;
-      T2f[i2] = (float)v;
-    }
+    T1[b1 + (int64_t)k * nh] = v;
   }
 }
 
 // Orders m0 .. m0 + count - 1.
-hipError_t launch_legendre_table(const GroupView& g, int m0, int count, double* T1, float* T1f,
-                                 float* T2f, hipStream_t s) {
+hipError_t launch_legendre_table(const GroupView& g, int m0, int count, double* T1,
+                                 hipStream_t s) {
   dim3 block(64);
   dim3 grid((g.nh + 63) / 64, count);
-  hipLaunchKernelGGL(k_legendre_table, grid, block, 0, s, g, m0, T1, T1f, T2f);
+  hipLaunchKernelGGL(k_legendre_table, grid, block, 0, s, g, m0, T1);
   return hipGetLastError();
 }
 

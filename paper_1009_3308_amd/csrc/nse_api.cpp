@@ -42,8 +42,6 @@ struct Group {
   std::vector<double> mu, w;         // all nlat nodes (host)
   FftPlan plan{};
   double *d_mu = nullptr, *d_w = nullptr, *d_T1 = nullptr;
-  float *d_T1f = nullptr, *d_T2f = nullptr;
-  int64_t* d_t2off = nullptr;
   double2 *d_rec_a = nullptr, *d_rec_g = nullptr;  // recurrence coefficients (rec_slot)
   // tables of the degree-pair contractions, one buffer (build_pairs), and the seeds
   // of their recurrences in four and in eight segments per order
@@ -53,7 +51,6 @@ struct Group {
   uint64_t* d_lps = nullptr;      // split-bf16 synthesis panels (BF16X3 groups)
   int64_t* d_lpsoff = nullptr;
   int64_t lps_stride = 0;         // per member, 8-byte units
-  std::vector<int64_t> t2off;  // [N+2] start of order m in T2
   double2 *d_F = nullptr, *d_W = nullptr, *d_tw = nullptr;
   double2 *d_Fa = nullptr, *d_Fbar = nullptr;  // adjoint, allocated on demand
   int64_t* d_off = nullptr;
@@ -72,9 +69,6 @@ struct Group {
     g.mu = d_mu;
     g.w = d_w;
     g.T1 = d_T1;
-    g.T1f = d_T1f;
-    g.T2f = d_T2f;
-    g.t2off = d_t2off;
     g.rec_a = d_rec_a;
     g.rec_g = d_rec_g;
     g.pair_rec = d_pair_rec;
@@ -276,9 +270,6 @@ void free_group(Group& g) {
   (void)hipFree(g.d_mu);
   (void)hipFree(g.d_w);
   (void)hipFree(g.d_T1);
-  (void)hipFree(g.d_T1f);
-  (void)hipFree(g.d_T2f);
-  (void)hipFree(g.d_t2off);
   (void)hipFree(g.d_rec_a);
   (void)hipFree(g.d_rec_g);
   (void)hipFree(g.d_pair);
@@ -405,20 +396,10 @@ nse_status build_group(nse_ctx* c, Group& g) {
   NSE_HIP(c, dalloc(&g.d_w, g.nh));
   NSE_HIP(c, hipMemcpy(g.d_mu, g.mu.data(), sizeof(double) * g.nh, hipMemcpyHostToDevice));
   NSE_HIP(c, hipMemcpy(g.d_w, g.w.data(), sizeof(double) * g.nh, hipMemcpyHostToDevice));
-  // the degree-by-degree kernels (FP32 mode; FP64 members by themselves on grids below
-  // nh = 256) seed from the table T1, the split-bf16 mode reads its FP32 copies
+  // the degree-by-degree kernels (FP32 and split-bf16 modes; FP64 members by themselves on
+  // grids below nh = 256) seed from the table T1
   const bool table = g.precision != NSE_PREC_FP64 || g.nh < 256;
-  const int64_t ts1 = t1_size(g.N, g.nh);
-  g.t2off.assign(g.N + 2, 0);
-  for (int m = 0; m <= g.N; ++m) {
-    const int L = g.N + 2 - m;
-    g.t2off[m + 1] = g.t2off[m] + (int64_t)((L + kTile - 1) / kTile) * g.nh * kTile;
-  }
-  const int64_t ts2 = g.t2off[g.N + 1];
-  NSE_HIP(c, dalloc(&g.d_t2off, g.N + 2));
-  NSE_HIP(c, hipMemcpy(g.d_t2off, g.t2off.data(), sizeof(int64_t) * (g.N + 2),
-                       hipMemcpyHostToDevice));
-  if (table) NSE_HIP(c, dalloc(&g.d_T1, ts1));
+  if (table) NSE_HIP(c, dalloc(&g.d_T1, t1_size(g.N, g.nh)));
   if (table) {
     // recurrence coefficients, in long double and rounded once
     const int64_t nrec = (int64_t)(g.N + 2) * (g.N + 3) / 2;
@@ -445,10 +426,6 @@ nse_status build_group(nse_ctx* c, Group& g) {
     NSE_HIP(c, hipMemcpy(g.d_rec_g, rg.data(), sizeof(double2) * nrec, hipMemcpyHostToDevice));
   }
   if (c->params.precision == NSE_PREC_BF16X3) {
-    // FP32 copies of the tables, split into bf16 pieces in registers (the FP64
-    // and FP32 modes continue the recurrences from FP64 seed rows instead)
-    NSE_HIP(c, dalloc(&g.d_T1f, ts1));
-    NSE_HIP(c, dalloc(&g.d_T2f, ts2));
     // per order: ceil(L / 32) blocks x 3 pieces x 64 lanes of 4 bf16
     std::vector<int64_t> off(g.N + 2, 0);
     for (int m = 0; m <= g.N; ++m) off[m + 1] = off[m] + (int64_t)((g.N + 2 - m + 31) / 32) * 3 * 64;
@@ -472,7 +449,7 @@ nse_status build_group(nse_ctx* c, Group& g) {
   NSE_HIP(c, hipMemcpy(g.d_off, g.offsets.data(), sizeof(int64_t) * nb, hipMemcpyHostToDevice));
   NSE_HIP(c, hipMemcpy(g.d_nu, g.nu.data(), sizeof(double) * nb, hipMemcpyHostToDevice));
   if (table)
-    NSE_HIP(c, launch_legendre_table(g.view(), 0, g.N + 1, g.d_T1, g.d_T1f, g.d_T2f, c->stream));
+    NSE_HIP(c, launch_legendre_table(g.view(), 0, g.N + 1, g.d_T1, c->stream));
   return build_pairs(c, g);
 }
 
@@ -1830,8 +1807,8 @@ nse_status nse_legendre_values(nse_ctx* ctx, int32_t member, int32_t m, double* 
   const Group& g = ctx->groups[ctx->member_group[member]];
   if (m < 0 || m > g.N) return fail(ctx, NSE_ERR_ARG, "order m = %d outside 0..%d", m, g.N);
   // the table's own kernel, one order (T1 at the order's offset is `out`)
-  NSE_HIP(ctx, launch_legendre_table(g.view(), m, 1, out - t1_order_offset(g.N, m, g.nh), nullptr,
-                                     nullptr, ctx->stream));
+  NSE_HIP(ctx, launch_legendre_table(g.view(), m, 1, out - t1_order_offset(g.N, m, g.nh),
+                                     ctx->stream));
   return NSE_OK;
 }
 

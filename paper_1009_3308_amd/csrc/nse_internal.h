@@ -60,12 +60,8 @@ __host__ __device__ inline int64_t pair_slot(int N, int m) {
 }
 // Rows per segment of the recurrences (4 ks segments, an even number of rows).
 __host__ __device__ inline int pair_len(int K, int ks) { return 2 * ((K + 8 * ks - 1) / (8 * ks)); }
-// Legendre tables, l = m .. N+1 (L = N + 2 - m degrees for order m, k = l - m):
-//   T1[m][k][p]                        (synthesis; latitude fastest, row stride nh)
-//   T2[m][deg tile][p][64 degrees]     (split-bf16 analysis, in FP32; ceil(L/64) tiles of 64 degrees,
-//                                       each a contiguous block streamed by one
-//                                       workgroup; orders start at t2off[m])
-constexpr int kTile = 64;
+// Legendre table T1[m][k][p], l = m .. N+1 (k = l - m < N + 2 - m; latitude fastest, row
+// stride nh).
 __host__ __device__ inline int64_t t1_order_offset(int N, int m, int nh) {
   return (int64_t)nh * ((int64_t)m * (2 * N + 5 - m) / 2);
 }
@@ -80,10 +76,7 @@ struct GroupView {
   int mb_synth, mb_anal;    // member blocks of the FP64 contractions (0 = member by member)
   const double* mu;         // [nh] Gauss-Legendre nodes, descending
   const double* w;          // [nh]
-  const double* T1;         // FP64 table (layouts above); null where nothing reads it
-  const float* T1f;         // FP32 copies (split-bf16x3 mode only), else null
-  const float* T2f;
-  const int64_t* t2off;     // [N+2] start of order m in T2 (element units)
+  const double* T1;         // FP64 table (layout above); null where nothing reads it
   const double2* rec_a;     // [(N+2)(N+3)/2] (a(l,m), a(l,m) / a(l-1,m)), slot rec_slot(N, l, m)
   const double2* rec_g;     // same slots: ((2l+1) e(l), lambda_l^(-1/2)), see rec_slot
   // degree-pair contractions (pair_legendre.hip): tables over pair_slot
@@ -270,8 +263,8 @@ struct NdfArgs {
 };
 
 // Launchers (each enqueues on `s` and returns the launch status).
-hipError_t launch_legendre_table(const GroupView& g, int m0, int count, double* T1, float* T1f,
-                                 float* T2f, hipStream_t s);
+hipError_t launch_legendre_table(const GroupView& g, int m0, int count, double* T1,
+                                 hipStream_t s);
 hipError_t launch_synthesis(const GroupView& g, const SynthInput& in, int mode, hipStream_t s);
 hipError_t launch_ring(const GroupView& g, const FftPlan& plan, int mode, double* grid_out,
                        hipStream_t s);
