@@ -274,17 +274,16 @@ __global__ __launch_bounds__(kSynThreads) void k_synthesis_lp(GroupView g, Synth
   for (int i = 0; i < 4; ++i) cst[(wave * 16 + 4 * q + i) * 16 + r16] = acc[i];
   __syncthreads();
   // one (field, latitude) per thread: E = columns 2f, 2f+1; O = columns 8+2f, 9+2f
-  const int f = threadIdx.x / kSynTile;
-  const int latl = threadIdx.x % kSynTile;
+  const int f = threadIdx.x & 3, latl = threadIdx.x >> 2;
   const int p = tile * kSynTile + latl;
   const int nf = (mode == SYNTH_NONLINEAR) ? 4 : 3;
   if (f >= nf || p >= nh) return;
   const double* row = cst + latl * 16;
   const double er = row[2 * f], ei = row[2 * f + 1], orr = row[8 + 2 * f], oi = row[9 + 2 * f];
-  double2* out = g.F + ((int64_t)(b * 4 + f) * (N + 1) + m) * nlat;
-  out[p] = make_double2(er + orr, ei + oi);
+  double2* out = g.F + ((int64_t)b * (N + 1) + m) * nlat * 4 + f;
+  out[4 * p] = make_double2(er + orr, ei + oi);
   const int ps = nlat - 1 - p;
-  if (ps != p) out[ps] = make_double2(er - orr, ei - oi);
+  if (ps != p) out[4 * ps] = make_double2(er - orr, ei - oi);
 }
 
 // LDS: the split A operand [block][piece][4 K-slices][4 live rows] (rows 4..15 of A are

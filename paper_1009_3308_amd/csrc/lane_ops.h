@@ -40,6 +40,33 @@ __device__ inline double lane_dpp(double v) {
   const int hi = __builtin_amdgcn_mov_dpp((int)(unsigned)(i >> 32), CTRL, 0xF, 0xF, false);
   return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
 }
+// The same for the banks (groups of four lanes of a 16-lane row) in MASK, the others keep
+// `old`.
+template <int CTRL, int MASK>
+__device__ inline double lane_dpp_banks(double old, double v) {
+  const unsigned long long o = __double_as_longlong(old), i = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp((int)(unsigned)o, (int)(unsigned)i, CTRL, 0xF, MASK, false);
+  const int hi = __builtin_amdgcn_update_dpp((int)(unsigned)(o >> 32), (int)(unsigned)(i >> 32), CTRL,
+                                             0xF, MASK, false);
+  return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
+}
+// Transposes v[index][bits 2, 3 of the lane]: v[f] of the lane with bits r becomes v[r] of
+// the lane with bits f.
+__device__ inline void transpose_banks(double (&v)[4]) {
+  constexpr int ror4 = 0x124, ror8 = 0x128, ror12 = 0x12C;  // lane l reads l - 4, 8, 12 mod 16
+#pragma unroll
+  for (int i = 0; i < 4; i += 2) {
+    const double a = v[i], b = v[i + 1];
+    v[i + 1] = lane_dpp_banks<ror12, 0x5>(b, a);
+    v[i] = lane_dpp_banks<ror4, 0xA>(a, b);
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const double a = v[i], b = v[i + 2];
+    v[i + 2] = lane_dpp_banks<ror8, 0x3>(b, a);
+    v[i] = lane_dpp_banks<ror8, 0xC>(a, b);
+  }
+}
 constexpr int kDppRowMirror = 0x140;      // lane i of a 16-lane row reads lane 15 - i
 constexpr int kDppRowHalfMirror = 0x141;  // lane i of an 8-lane half row reads lane 7 - i
 constexpr int kDppQuadXor2 = 0x4E;        // quad_perm [2, 3, 0, 1]

@@ -87,8 +87,8 @@ struct GroupView {
   const double2* pair_lam;  // [N+2] (lambda^(-1/2), lambda^(1/2)), zero at l = 0
   const double2* seeds1;    // (q_{k-1}, q_k) at the first k of every segment: [m][tile of 16
   const double2* seeds2;    // latitudes][4 ks segments][16] for ks = 1 and 2 (null: not kept)
-  double2* F;               // [nb][4][N+1][nlat] Fourier coefficients of grid fields
-  double2* Fa;              // adjoint: [nb][5][N+1][nlat] (4 forward fields + adjoint input)
+  double2* F;               // [nb][N+1][nlat][4] Fourier coefficients of grid fields
+  double2* Fa;              // adjoint: per member [N+1][nlat][4] forward fields and [N+1][nlat] adjoint input
   double2* Fbar;            // adjoint: [nb][4][N+1][nlat] cotangents of the field spectra
   double2* W;               // [nb][N+1][nlat] weighted ring spectra (analysis input),
                             // latitude fastest so the analysis reads them coalesced

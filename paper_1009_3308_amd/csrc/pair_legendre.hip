@@ -477,21 +477,35 @@ __global__ __launch_bounds__(64 * W) void k_synthesis_pair(GroupView g, SynthInp
 #pragma unroll
       for (int f = 0; f < NF; ++f) acc[t][f] += red[(t * NF + f) * 64];
   }
-  // lane: latitude 4 i + blk of the tile (a 16-lane row stores 64 contiguous bytes of
-  // either hemisphere), column j; E and O sit two lanes apart
-  constexpr int NS = NF == 5 ? 5 : 4;  // field stride of the output
-  double2* Fo = (NF == 5 ? g.Fa : g.F) + ((int64_t)b * NS * (N + 1) + m) * nlat;
+  // lane: latitude 4 i + blk of the tile, column j; E and O sit two lanes apart. The four
+  // fields then change places with the four blk, so that a store writes the 64 bytes
+  // of a latitude's fields (the fifth field of NF = 5 lies by itself). At N = 511 this
+  // costs the synthesis 1.2 us and saves the rings 4
+  const int64_t fstride = (int64_t)(N + 1) * nlat;
+  double* Fo = reinterpret_cast<double*>((NF == 5 ? g.Fa + b * 5 * fstride : g.F + b * 4 * fstride) +
+                                         (int64_t)m * nlat * 4);
   const bool odd = (lane & 2) != 0;
 #pragma unroll
   for (int t = 0; t < TL; ++t) {
-    const int p = (tile0 + t) * 16 + pair_out16(lane);
-    const int q = odd ? nlat - 1 - p : p;  // southern ring, northern ring
-    const bool st = tile0 + t < ntile && p < nh && (!odd || q != p);
+    double r[NF < 4 ? 4 : NF];
+    r[3] = 0.0;
 #pragma unroll
     for (int f = 0; f < NF; ++f) {
       const double v = acc[t][f], w = lane_dpp<kDppQuadXor2>(v);
-      const double r = odd ? fma(-xo[t], v, w) : fma(xo[t], w, v);
-      if (st) reinterpret_cast<double*>(Fo + (int64_t)f * (N + 1) * nlat)[2 * q + (lane & 1)] = r;
+      r[f] = odd ? fma(-xo[t], v, w) : fma(xo[t], w, v);
+    }
+    double r4[4] = {r[0], r[1], r[2], r[3]};
+    transpose_banks(r4);
+    const int p0 = (tile0 + t) * 16 + 4 * (lane >> 4), fl = (lane >> 2) & 3;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int p = p0 + i, q = odd ? nlat - 1 - p : p;  // southern ring, northern ring
+      if (tile0 + t < ntile && p < nh && (!odd || q != p)) Fo[(q * 4 + fl) * 2 + (lane & 1)] = r4[i];
+    }
+    if constexpr (NF == 5) {
+      const int p = (tile0 + t) * 16 + pair_out16(lane), q = odd ? nlat - 1 - p : p;
+      double* F4 = reinterpret_cast<double*>(g.Fa + b * 5 * fstride + 4 * fstride + (int64_t)m * nlat);
+      if (tile0 + t < ntile && p < nh && (!odd || q != p)) F4[2 * q + (lane & 1)] = r[4];
     }
   }
 }

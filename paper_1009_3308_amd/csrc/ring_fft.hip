@@ -279,7 +279,8 @@ __device__ __forceinline__ void stage(double2* x, int na, int PL, const FftPlan&
 // Compile-time plans of the default grids of N = 2^k - 1, M = 3 * 2^k, and of N = 100, M =
 // 320 (160 rings 5.0 us, 6.9 at run time; any other M: the one that
 // fft_plan found, a kernel argument). With every index a constant the ring takes 21.3
-// us instead of 24.4 at M = 1536 (768 rings), 53 instead of 64 us at M = 768 (6144 rings).
+// us instead of 24.4 at M = 1536 (768 rings), 53 instead of 64 us at M = 768 (6144 rings; both
+// before the four fields of an order lay together, as the figures below).
 // Measured against these plans: 12, 16, 8 and 16, 12, 8 at M = 1536 22.8 us (their
 // last pass needs more registers); 8, 8, 8, 3 over 384 threads 22.8; 16, 16, 3 at M =
 // 768 8.8 against 8.2 us for 384 rings; 4, 16, 3 at M = 192 10.5 against 9.8 us for 2304.
@@ -385,44 +386,61 @@ __device__ __forceinline__ int ring_node(const GroupView& g, int lat) {
   return lat < g.nh ? lat : g.nlat - 1 - lat;
 }
 
+// LDS slots from one array to the next: congruent to 8 (4 for two rings) modulo 16, so that
+// lanes that write the same order of the arrays hit different banks.
+template <int NR>
+__host__ __device__ __forceinline__ int array_len(const FftPlan& pl) {
+  constexpr int c = NR == 2 ? 4 : 8;
+  return (pl.len + 15 - c) / 16 * 16 + c;
+}
+
 // Spectra of NR neighbouring rings into LDS: array (ring rr, pair a) at x + (rr NP + a)
 // PL holds x_m = G^a_m + i G^b_m and x_{M-m} = conj(G^a_m) + i conj(G^b_m), zero in
-// between. pair(a, &ga, &gb) gives the pair's fields, [m][lat] with stride nlat between
-// orders; the third of NP = 3 pairs is one real field of spectrum ga / 2. All loads
-// are issued, unconditionally, before the first LDS write; neighbouring lanes take the
-// rings of one order, whose spectra share a cache line.
-template <int NP, int NR, int MAXM, int NT, typename P>
-__device__ __forceinline__ void load_spectra(double2* x, int PL, const FftPlan& pl, int N, int M, int nlat,
-                                             int lat0, P&& pair) {
-  constexpr int KI = (NR * NP * ((MAXM + 1) / 3) + NT - 1) / NT;  // N + 1 <= (M + 1) / 3
-  const int n1 = N + 1, top = NP * n1;
-  double2 ga[KI], gb[KI];
+// between. Pairs 0 and 1 are the fields (0, 1) and (2, 3) of F[m][lat][4] (REAL1: the
+// real field 2 twice); the third of NP = 3 pairs is the real field of spectrum F5 / 2,
+// F5[m][lat]. All loads are issued, unconditionally, before the first LDS write; two
+// lanes read the 64 bytes of an order, four those of two rings. (With the fields in
+// planes of their own every lane took a cache line by itself: the ring at M = 1536
+// needed 21.4 us instead of 17.5.)
+template <int NP, int NR, int MAXM, int NT, bool REAL1>
+__device__ __forceinline__ void load_spectra(double2* x, int PL, const FftPlan& pl, int N, int M,
+                                             int nlat, int lat0, const double2* F,
+                                             const double2* F5) {
+  constexpr int kOrders = (MAXM + 1) / 3;  // N + 1 <= (M + 1) / 3
+  constexpr int KI = (NR * 2 * kOrders + NT - 1) / NT;
+  constexpr int KR = NP == 3 ? (NR * kOrders + NT - 1) / NT : 0;
+  double2 ga[KI], gb[KI], gr[KR + 1];
 #pragma unroll
   for (int i = 0; i < KI; ++i) {
-    const int t = threadIdx.x + i * NT, rr = t % NR, tt = min(t / NR, top - 1);
-    const int a = NP == 3 && tt >= 2 * n1 ? 2 : (tt >= n1 ? 1 : 0);
-    const double2 *fa, *fb;
-    pair(a, fa, fb);
-    const int64_t off = (int64_t)(tt - a * n1) * nlat + min(lat0 + rr, nlat - 1);
-    ga[i] = fa[off];
-    gb[i] = fb[off];
+    const int t = threadIdx.x + i * NT, a = t & 1, rr = (t >> 1) % NR, m = min((t >> 1) / NR, N);
+    const double2* f = F + ((int64_t)m * nlat + min(lat0 + rr, nlat - 1)) * 4 + 2 * a;
+    ga[i] = f[0];
+    gb[i] = f[REAL1 && a ? 0 : 1];
   }
 #pragma unroll
-  for (int i = 0; i < KI; ++i) {
-    const int t = threadIdx.x + i * NT, rr = t % NR, tt = t / NR;
-    if (tt < top) {
-      const int a = NP == 3 && tt >= 2 * n1 ? 2 : (tt >= n1 ? 1 : 0), m = tt - a * n1;
-      double2* y = x + (rr * NP + a) * PL;
-      const bool real = NP == 3 && a == 2;
-      if (real) gb[i] = make_double2(0.0, 0.0);
-      if (m == 0) {
-        y[0] = make_double2(ga[i].x, gb[i].x);
-      } else {
-        const double h = real ? 0.5 : 1.0;
-        y[slot(pl, m)] = make_double2(h * (ga[i].x - gb[i].y), h * (ga[i].y + gb[i].x));
-        y[slot(pl, M - m)] = make_double2(h * (ga[i].x + gb[i].y), h * (gb[i].x - ga[i].y));
-      }
+  for (int i = 0; i < KR; ++i) {
+    const int t = threadIdx.x + i * NT, rr = t % NR, m = min(t / NR, N);
+    gr[i] = F5[(int64_t)m * nlat + min(lat0 + rr, nlat - 1)];
+  }
+  auto put = [&](double2* y, int m, double2 a, double2 b) {
+    if (m > N) return;
+    if (m == 0) {
+      y[0] = make_double2(a.x, b.x);
+    } else {
+      y[slot(pl, m)] = make_double2(a.x - b.y, a.y + b.x);
+      y[slot(pl, M - m)] = make_double2(a.x + b.y, b.x - a.y);
     }
+  };
+#pragma unroll
+  for (int i = 0; i < KI; ++i) {
+    const int t = threadIdx.x + i * NT, a = t & 1, rr = (t >> 1) % NR;
+    put(x + (rr * NP + a) * PL, (t >> 1) / NR, ga[i], gb[i]);
+  }
+#pragma unroll
+  for (int i = 0; i < KR; ++i) {
+    const int t = threadIdx.x + i * NT, rr = t % NR, m = t / NR;
+    const double h = m == 0 ? 1.0 : 0.5;
+    put(x + (rr * NP + 2) * PL, m, make_double2(h * gr[i].x, h * gr[i].y), make_double2(0.0, 0.0));
   }
   const int zb = M - 2 * N - 1;  // N < k < M - N
   for (int a = 0; a < NR * NP; ++a)
@@ -430,12 +448,12 @@ __device__ __forceinline__ void load_spectra(double2* x, int PL, const FftPlan& 
 }
 
 // Nonlinear mode: NR rings per workgroup.
-// Bound: at M = 1536 (768 rings, three per CU, 31 MB of spectra in and out) 21.3 us, of
-// which about 7 are the strided reads of the spectra, 6 the FP64 instructions and 5 the
-// LDS; the rings of a CU run in step, so these add up. Stockham rings with radices 8, 8,
-// 8, 3 took 22.8 us; 68 us became 54 for 6144 rings of M = 768 and 37 became 23 for 4608 of
-// M = 384, by fewer LDS passes without bank conflicts and one forward transform for
-// two rings; 17.5 became 13.7 for 480 rings of M = 960 (run-time plan).
+// Bound: at M = 1536 (768 rings, three per CU, 31 MB of spectra in and out) 17.3 us, of
+// which about 6 are the FP64 instructions, 5 the LDS and 4 the reads of the spectra; the
+// rings of a CU run in step, so these add up. Stockham rings with radices 8, 8, 8, 3 took
+// 22.8 us; 68 us became 50 for 6144 rings of M = 768 and 37 became 23 for 4608 of M = 384,
+// by fewer LDS passes without bank conflicts and one forward transform for two rings;
+// 17.5 became 12.5 for 480 rings of M = 960 (run-time plan).
 template <int MAXM, int NT, int NR, int CM>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_ring(GroupView g, FftPlan rt) {
   const FftPlan pl = plan_of<CM>(rt);
@@ -443,7 +461,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
   const int lat0 = NR * xcd_item(blockIdx.x, 8 / NR);  // XCD chunks of 8 rings share lines of F
   if (lat0 >= nlat) return;
   const int b = blockIdx.y;
-  const int PL = pl.len;
+  const int PL = array_len<NR>(pl);
   extern __shared__ double2 lds[];
   const double2* tw = g.tw;
   const int64_t fstride = (int64_t)(N + 1) * nlat;
@@ -458,11 +476,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
     // own mirror and is folded twice by the analysis
     c[r] = (6.283185307179586477 / M) * g.w[p] * (2 * p + 1 == nlat ? 0.5 : 1.0);
   }
-  load_spectra<2, NR, MAXM, NT>(lds, PL, pl, N, M, nlat, lat0,
-                                [&](int a, const double2*& fa, const double2*& fb) {
-                                  fa = F0 + 2 * a * fstride;
-                                  fb = fa + fstride;
-                                });
+  load_spectra<2, NR, MAXM, NT, false>(lds, PL, pl, N, M, nlat, lat0, F0, nullptr);
   // an ended attempt of a device-controlled run: checked once the loads are in
   // flight (nothing is stored before this barrier), so the flag costs no wait
   if (gate_closed(g)) return;
@@ -522,23 +536,19 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
 }
 
 // Grid mode: u_theta = f0 / sin, u_phi = -f1 / sin and the third field (f2). 625 rings of
-// M = 1250: 34.8 -> 19.7 us.
+// M = 1250: 34.8 -> 17.6 us.
 template <int MAXM, int NT, int CM>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_ring_grid(GroupView g, FftPlan rt, double* grid_out) {
   const FftPlan pl = plan_of<CM>(rt);
   const int N = g.N, M = CM ? CM : g.M, nlat = CM ? CM / 2 : g.nlat;
   const int lat = xcd_item(blockIdx.x, 8);
   if (lat >= nlat) return;
-  const int PL = pl.len;
+  const int PL = array_len<1>(pl);
   extern __shared__ double2 lds[];
   const int64_t fstride = (int64_t)(N + 1) * nlat;
   const double x = g.mu[ring_node(g, lat)];
   const double rs = 1.0 / sqrt((1.0 - x) * (1.0 + x));
-  load_spectra<2, 1, MAXM, NT>(lds, PL, pl, N, M, nlat, lat,
-                               [&](int a, const double2*& fa, const double2*& fb) {
-                                 fa = g.F + 2 * a * fstride;
-                                 fb = a ? fa : fa + fstride;
-                               });
+  load_spectra<2, 1, MAXM, NT, true>(lds, PL, pl, N, M, nlat, lat, g.F, nullptr);
   __syncthreads();
   for_stages<1, (CM > 0)>(pl, [&](int st) { run_stage<1, NT>(lds, 2, PL, pl, st, g.tw); });
   run_last<1, NT>(lds, 2, PL, pl);
@@ -563,8 +573,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
 //   Gbar_0 = sum_j gbar_j,  Gbar_m = 2 sum_j gbar_j e^{-i m phi_j}  (m >= 1),
 // written to Fbar[b][f][m][lat]. c_lat = (2 pi / M) w_p. Three inverse transforms per
 // ring, one pass for the cotangents (gbar0 + i gbar1, both of the vorticity-gradient
-// size, and gbar2 + i gbar3), two forward transforms: 59 -> 38 us for 768 rings of M = 1536
-// (384 threads; 256: 40.5), 14.3 -> 13.7 us for 384 of M = 768.
+// size, and gbar2 + i gbar3), two forward transforms: 59 -> 32 us for 768 rings of M = 1536
+// (384 threads against 256: 38 and 40.5 before the fields of an order lay together), 14.3 ->
+// 13.7 us for 384 of M = 768.
 template <int MAXM, int NT, int NR, int CM>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_ring_adj(GroupView g, FftPlan rt) {
   const FftPlan pl = plan_of<CM>(rt);
@@ -572,7 +583,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
   const int lat0 = NR * xcd_item(blockIdx.x, 8 / NR);
   if (lat0 >= nlat) return;
   const int b = blockIdx.y;
-  const int PL = pl.len;
+  const int PL = array_len<NR>(pl);
   extern __shared__ double2 lds[];
   const double2* tw = g.tw;
   const int64_t fstride = (int64_t)(N + 1) * nlat;
@@ -584,11 +595,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
     const double x = g.mu[p];
     cs[r] = (6.283185307179586477 / M) * g.w[p] / ((1.0 - x) * (1.0 + x));
   }
-  load_spectra<3, NR, MAXM, NT>(lds, PL, pl, N, M, nlat, lat0,
-                                [&](int a, const double2*& fa, const double2*& fb) {
-                                  fa = F5 + 2 * a * fstride;
-                                  fb = a < 2 ? fa + fstride : fa;
-                                });
+  load_spectra<3, NR, MAXM, NT, false>(lds, PL, pl, N, M, nlat, lat0, F5, F5 + 4 * fstride);
   __syncthreads();
   const int last = pl.nstages - 1;
   for_stages<1, (CM > 0)>(pl, [&](int st) { run_stage<1, NT>(lds, 3 * NR, PL, pl, st, tw); });
@@ -717,8 +724,9 @@ hipError_t ring_dispatch(int M, F&& launch) {
   return launch(integral_constant<int, kMaxM>{}, integral_constant<int, 256>{}, rt);
 }
 
-// LDS of na arrays of one ring.
-size_t ring_lds(const FftPlan& pl, int na) { return sizeof(double2) * (size_t)na * pl.len; }
+// LDS of na arrays, NR rings per workgroup.
+template <int NR>
+size_t ring_lds(const FftPlan& pl, int na) { return sizeof(double2) * (size_t)na * array_len<NR>(pl); }
 
 }  // namespace
 
@@ -735,13 +743,13 @@ hipError_t launch_ring_adjoint(const GroupView& g, const FftPlan& pl, hipStream_
     if constexpr (MAXM <= 768) {
       if (two_rings(g)) {
         dim3 grid(xcd_grid((g.nlat + 1) / 2, 4), g.nb);
-        hipLaunchKernelGGL((k_ring_adj<MAXM, 2 * NT, 2, CM>), grid, dim3(2 * NT), ring_lds(plan_of<CM>(pl), 6), s, g, pl);
+        hipLaunchKernelGGL((k_ring_adj<MAXM, 2 * NT, 2, CM>), grid, dim3(2 * NT), ring_lds<2>(plan_of<CM>(pl), 6), s, g, pl);
         return hipGetLastError();
       }
     }
     dim3 grid(xcd_grid(g.nlat, 8), g.nb);
     constexpr int NT1 = MAXM > 768 ? 384 : NT;
-    hipLaunchKernelGGL((k_ring_adj<MAXM, NT1, 1, CM>), grid, dim3(NT1), ring_lds(plan_of<CM>(pl), 3), s, g, pl);
+    hipLaunchKernelGGL((k_ring_adj<MAXM, NT1, 1, CM>), grid, dim3(NT1), ring_lds<1>(plan_of<CM>(pl), 3), s, g, pl);
     return hipGetLastError();
   });
 }
@@ -751,7 +759,7 @@ hipError_t launch_ring_project(const GroupView& g, const FftPlan& pl, const doub
   dim3 grid(xcd_grid(g.nlat, 8), g.nb);
   return ring_dispatch(g.M, [&](auto maxm, auto nt, auto cm) {
     constexpr int MAXM = decltype(maxm)::value, NT = decltype(nt)::value, CM = decltype(cm)::value;
-    hipLaunchKernelGGL((k_ring_project<MAXM, NT, CM>), grid, dim3(NT), ring_lds(plan_of<CM>(pl), 1), s, g, pl, u_grid);
+    hipLaunchKernelGGL((k_ring_project<MAXM, NT, CM>), grid, dim3(NT), ring_lds<1>(plan_of<CM>(pl), 1), s, g, pl, u_grid);
     return hipGetLastError();
   });
 }
@@ -762,13 +770,13 @@ hipError_t launch_ring(const GroupView& g, const FftPlan& pl, int mode, double* 
     constexpr int MAXM = decltype(maxm)::value, NT = decltype(nt)::value, CM = decltype(cm)::value;
     if (mode == SYNTH_GRID) {
       dim3 grid(xcd_grid(g.nlat, 8));
-      hipLaunchKernelGGL((k_ring_grid<MAXM, NT, CM>), grid, dim3(NT), ring_lds(plan_of<CM>(pl), 2), s, g, pl, grid_out);
+      hipLaunchKernelGGL((k_ring_grid<MAXM, NT, CM>), grid, dim3(NT), ring_lds<1>(plan_of<CM>(pl), 2), s, g, pl, grid_out);
       return hipGetLastError();
     }
     if constexpr (MAXM <= 768) {
       if (two_rings(g)) {
         dim3 grid(xcd_grid((g.nlat + 1) / 2, 4), g.nb);
-        const size_t lds = ring_lds(plan_of<CM>(pl), 4);
+        const size_t lds = ring_lds<2>(plan_of<CM>(pl), 4);
         // M > 384: three workgroups of 256 threads per CU overlap their phases (6144 rings
         // 54 us against 58 with 512 threads); when there is one per CU, 512 threads are
         // faster (384 rings: 8.2 against 9.4 us)
@@ -781,7 +789,7 @@ hipError_t launch_ring(const GroupView& g, const FftPlan& pl, int mode, double* 
     }
     dim3 grid(xcd_grid(g.nlat, 8), g.nb);
     constexpr int NT1 = MAXM == 384 ? 192 : NT;  // (192 rings of M = 384: 5.8 us, 6.2 with 128)
-    hipLaunchKernelGGL((k_ring<MAXM, NT1, 1, CM>), grid, dim3(NT1), ring_lds(plan_of<CM>(pl), 2), s, g, pl);
+    hipLaunchKernelGGL((k_ring<MAXM, NT1, 1, CM>), grid, dim3(NT1), ring_lds<1>(plan_of<CM>(pl), 2), s, g, pl);
     return hipGetLastError();
   });
 }

@@ -9,7 +9,7 @@
 // then takes a quarter of the degree range, accumulating even (l-m even) and
 // odd parts separately, and the four partial sums are added through LDS. Each
 // latitude yields the northern value E + O and the mirrored southern value
-// E - O. Output F[b][f][m][lat] is written latitude-contiguous.
+// E - O. Output F[b][m][lat][4 fields].
 //
 // The Legendre values are not streamed from the table T1[m][l-m][p]: each wave
 // reads two table rows at the start of its degree range and continues the
@@ -32,11 +32,14 @@ constexpr int kPanelConvPerThread = 10;
 constexpr int kRcPerThread = 3;
 
 constexpr int NF = 4;  // fields
+// Doubles of one wave's partial sums in LDS, [field][4][64], 8 more per field: the threads
+// that finish a latitude's fields then read different banks.
+constexpr int kRedField = 4 * 64 + 8, kRedWave = NF * kRedField;
 // Per lane 4 NF partial sums (NF fields x (E, O) x (re, im)). The panel
 // [L][NF] double2 is reused afterwards for the cross-wave reduction.
 __host__ __device__ inline int synth_pan_slots(int N) {
   const int pan = NF * (N + 2 + kOtfBatch);  // panel rows plus the padding a batch may read
-  const int red = kSynthWaves * 4 * NF * 64 / 2;
+  const int red = kSynthWaves * kRedWave / 2;
   return pan > red ? pan : red;
 }
 
@@ -200,31 +203,32 @@ __global__ __launch_bounds__(kSynthThreads) void k_synthesis(GroupView g, SynthI
     }
   }
   // cross-wave sums, one latitude slot at a time through the (no longer needed)
-  // panel; wave w finishes fields w, w+4, ... of its 64 latitudes
-  double* red = reinterpret_cast<double*>(pan);  // [wave][kRed][64]
+  // panel; four threads finish the fields of a latitude
+  static_assert(kSynthThreads == 64 * NF, "one thread per field and latitude");
+  const int f = threadIdx.x & 3, latl = threadIdx.x >> 2;
+  double* red = reinterpret_cast<double*>(pan);  // [wave][NF][kRedField]
   const int nf = (mode == SYNTH_GRID) ? 3 : NF;
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < kRed; ++i) red[(wave * kRed + i) * 64 + lane] = (double)acc[r][i];
+    for (int i = 0; i < kRed; ++i)
+      red[wave * kRedWave + (i >> 2) * kRedField + (i & 3) * 64 + lane] = (double)acc[r][i];
     __syncthreads();
-    const int p = pbase + 64 * r;
-    if (p < nh) {
-      for (int f = wave; f < nf; f += kSynthWaves) {
-        double er = 0.0, ei = 0.0, orr = 0.0, oi = 0.0;
+    const int p = pbase - lane + latl + 64 * r;
+    if (p < nh && f < nf) {
+      double er = 0.0, ei = 0.0, orr = 0.0, oi = 0.0;
 #pragma unroll
-        for (int w = 0; w < kSynthWaves; ++w) {
-          er += red[(w * kRed + 4 * f + 0) * 64 + lane];
-          ei += red[(w * kRed + 4 * f + 1) * 64 + lane];
-          orr += red[(w * kRed + 4 * f + 2) * 64 + lane];
-          oi += red[(w * kRed + 4 * f + 3) * 64 + lane];
-        }
-        double2* out = g.F + ((int64_t)(b * NF + f) * (N + 1) + m) * nlat;
-        out[p] = make_double2(er + orr, ei + oi);
-        const int ps = nlat - 1 - p;
-        if (ps != p) out[ps] = make_double2(er - orr, ei - oi);
+      for (int w = 0; w < kSynthWaves; ++w) {
+        er += red[w * kRedWave + f * kRedField + latl];
+        ei += red[w * kRedWave + f * kRedField + 64 + latl];
+        orr += red[w * kRedWave + f * kRedField + 128 + latl];
+        oi += red[w * kRedWave + f * kRedField + 192 + latl];
       }
+      double2* out = g.F + ((int64_t)b * (N + 1) + m) * nlat * NF + f;
+      out[4 * p] = make_double2(er + orr, ei + oi);
+      const int ps = nlat - 1 - p;
+      if (ps != p) out[4 * ps] = make_double2(er - orr, ei - oi);
     }
   }
 }
@@ -326,7 +330,7 @@ __device__ __forceinline__ void synthesis_adv_body(const GroupView& g, const Syn
   NdfCtl* sc = nullptr;
   if constexpr (STEP) {
     // the control block after the coefficient arrays and the cross-wave buffer
-    const int arrays = NF * (N + 1 + kOtfBatch), red = kSynthWaves * kRed * 64 / 2;
+    const int arrays = NF * (N + 1 + kOtfBatch), red = kSynthWaves * kRedWave / 2;
     sc = reinterpret_cast<NdfCtl*>(sh + (arrays > red ? arrays : red));
     double* norm = reinterpret_cast<double*>(sc + 1);
     int* prepf = reinterpret_cast<int*>(norm + 4);
@@ -502,34 +506,36 @@ __device__ __forceinline__ void synthesis_adv_body(const GroupView& g, const Syn
     }
   }
   // cross-wave sums through LDS (the coefficient arrays are no longer needed);
-  // wave w finishes field w of its latitudes; f0 and f3 take the factor i m
+  // four threads finish the fields of a latitude; f0 and f3 take the factor i m
+  const int f = threadIdx.x & 3, latl = threadIdx.x >> 2;
   const double dm = (double)m;
-  double* red = reinterpret_cast<double*>(sh);  // [wave][kRed][64]
+  double* red = reinterpret_cast<double*>(sh);  // [wave][NF][kRedField]
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < kRed; ++i) red[(wave * kRed + i) * 64 + lane] = acc[r][i];
+    for (int i = 0; i < kRed; ++i)
+      red[wave * kRedWave + (i >> 2) * kRedField + (i & 3) * 64 + lane] = acc[r][i];
     __syncthreads();
-    const int p = pbase + 64 * r;
-    for (int f = wave; f < NF && p < nh; f += kSynthWaves) {
+    const int p = pbase - lane + latl + 64 * r;
+    if (p < nh) {
       double er = 0.0, ei = 0.0, orr = 0.0, oi = 0.0;
 #pragma unroll
       for (int w = 0; w < kSynthWaves; ++w) {
-        er += red[(w * kRed + 4 * f + 0) * 64 + lane];
-        ei += red[(w * kRed + 4 * f + 1) * 64 + lane];
-        orr += red[(w * kRed + 4 * f + 2) * 64 + lane];
-        oi += red[(w * kRed + 4 * f + 3) * 64 + lane];
+        er += red[w * kRedWave + f * kRedField + latl];
+        ei += red[w * kRedWave + f * kRedField + 64 + latl];
+        orr += red[w * kRedWave + f * kRedField + 128 + latl];
+        oi += red[w * kRedWave + f * kRedField + 192 + latl];
       }
       double2 vn = make_double2(er + orr, ei + oi), vs = make_double2(er - orr, ei - oi);
       if (f == 0 || f == 3) {
         vn = make_double2(-dm * vn.y, dm * vn.x);
         vs = make_double2(-dm * vs.y, dm * vs.x);
       }
-      double2* out = g.F + ((int64_t)(b * NF + f) * (N + 1) + m) * nlat;
-      out[p] = vn;
+      double2* out = g.F + ((int64_t)b * (N + 1) + m) * nlat * NF + f;
+      out[4 * p] = vn;
       const int psouth = nlat - 1 - p;
-      if (psouth != p) out[psouth] = vs;
+      if (psouth != p) out[4 * psouth] = vs;
     }
   }
 }
@@ -545,7 +551,7 @@ __global__ __launch_bounds__(kSynthThreads) void k_synthesis_adv_step(GroupView 
 
 size_t synthesis_adv_lds_bytes(int N) {
   const int arrays = NF * (N + 1 + kOtfBatch);
-  const int red = kSynthWaves * 4 * NF * 64 / 2;
+  const int red = kSynthWaves * kRedWave / 2;
   return sizeof(double2) * (size_t)(arrays > red ? arrays : red);
 }
 
