@@ -509,7 +509,7 @@ nse_status timed_launch(nse_ctx* c, int kind, F&& launch) {
 // shorter workgroups, have the shorter chain: synthesis 6.8 against 7.4 us at N = 155
 // and 11.3 against 10.7 at N = 255 (nh = 117 and 192), analysis 5.2 against 7.2 us at
 // N = 155, 8.4 against 8.5 at N = 255 and 9.0 against 9.6 at N = 300 (nh = 240); at N =
-// 511 (nh = 384) the pairs take 24.6 against 37.2 and 18.8 against 29.2 us.
+// 511 (nh = 384) the pairs take 25.3 against 37.2 and 19 against 29.2 us.
 bool pair_synthesis(const GroupView& v, int mode) {
   return mode != SYNTH_NONLINEAR || v.mb_synth > 1 || v.nh >= 192;
 }

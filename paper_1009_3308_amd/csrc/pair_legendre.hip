@@ -210,6 +210,10 @@ __device__ __forceinline__ int64_t member_offset(const GroupView& g, int b) {
 // unconditional (indices clamped, values masked afterwards): in one block the
 // scalar loads of the arguments and the vector loads go out together, where a branch per
 // load had put some twenty argument round trips in a row.
+// Bound: at N = 511 the FP64 issue (products, recurrence) for 0.7 of the time, the rest the
+// prologue and the stores: 25.3 us, 38 by single degrees on the vector units; five fields 30
+// against 82, 16 members of N = 255 54 against 95. At N = 255 alone the chain of one
+// workgroup: 10.7 against 11.3.
 template <int NF, int MS, int W, int TL, int KS>
 __global__ __launch_bounds__(64 * W) void k_synthesis_pair(GroupView g, SynthInput in, int nsplit) {
   static_assert(NF >= 3 && NF <= 5 && W % KS == 0, "three (grid), four or five (adjoint) fields");
@@ -526,7 +530,8 @@ hipError_t launch_synth_pair_as(const GroupView& g, SynthInput in, hipStream_t s
 }
 
 // Segments per order: eight (two waves share an order's rows) for single members on grids
-// below nh = 256, where the chain of a workgroup counts; four elsewhere.
+// below nh = 256, where the chain of a workgroup counts (N = 255: synthesis 10.7 us against
+// 11.4 with four, five fields 12.0 against 13.5, adjoint 13.2 against 22.2); four elsewhere.
 bool pair_eight(const GroupView& g, int mb) { return g.nh < 256 && mb < 2; }
 
 template <int NF, int MS>
@@ -535,6 +540,7 @@ hipError_t launch_synth_pair_nf(const GroupView& g, const SynthInput& in, hipStr
   if (g.nh <= 48) return launch_synth_pair_as<NF, MS, 3, 1, 1>(g, in, s);
   if (g.nh <= 96) return launch_synth_pair_as<NF, MS, 2, 3, 1>(g, in, s);
   if (g.nh <= 192) return launch_synth_pair_as<NF, MS, 4, 3, 1>(g, in, s);
+  // (N = 511: eight waves of three tiles 25.3 us, four of three 29.8, six of four 29.6)
   return launch_synth_pair_as<NF, MS, 8, 3, 1>(g, in, s);
 }
 
@@ -562,7 +568,9 @@ namespace {
 // segments is summed over the wave's latitudes by GW products into one accumulator,
 // its blocks of different latitudes are added (row rotations) and the sums go to
 // LDS, where the waves meet. The lane butterfly of the degree-by-degree form moved
-// every sum through six exchanges.
+// every sum through six exchanges. N = 511: 19 us against 30 by single degrees, bound by
+// the FP64 issue and, for a third of the time, the load phase; 16 members of N = 255 36
+// against 38, 24 of N = 63 9 against 9.
 template <int CTRL>
 __device__ __forceinline__ double add_dpp(double v) {
   return v + lane_dpp<CTRL>(v);
@@ -883,7 +891,10 @@ namespace {
 // (zero at l = 0, real at m = 0), stored or used in the adjoint of the NDF step. One
 // workgroup holds an order, so the degrees couple through LDS and no panel
 // cotangents go through memory. NFLD = 2: f0 and f1 only (the projection).
-// Waves: WL groups of latitudes for every FW fields.
+// Waves: WL groups of latitudes for every FW fields. N = 511: 44 us against 111 for the
+// analysis from a table and 6.5 for the transpose (two fields 25.5); N = 255 with the step
+// adjoint 14.4 against 13.7 and 4.9. Bound by the FP64 issue with the row sums, 0.6 of the
+// time, then by the 25 MB of Fbar at its start.
 // DEP: 0, or the step adjoint with that many history rows at most.
 template <int NFLD, int FW, int WL, int GW, int KS, int DEP>
 __global__ __launch_bounds__(64 * WL * (NFLD / FW), 4) void k_adjoint_pair(GroupView g,
@@ -1083,6 +1094,10 @@ hipError_t launch_adj_pair(const GroupView& g, double2* alpha_bar, const StepAdj
     if (g.nh <= 192) return launch_adj_pair_as<NFLD, 2, 4, 6, 2>(g, alpha_bar, sa, s);
     return launch_adj_pair_as<NFLD, 2, 4, 8, 2>(g, alpha_bar, sa, s);
   }
+  // nh > 192: with a wave per field 44 us for the four fields of N = 511 against 48 with
+  // two fields per wave, whose recurrence is shared but whose row sums are twice as many;
+  // for two fields 27.0 against 25.5
+  if constexpr (NFLD == 2) return launch_adj_pair_as<2, 2, 4, 6, 1>(g, alpha_bar, sa, s);
   return launch_adj_pair_as<NFLD, 1, 2, 12, 1>(g, alpha_bar, sa, s);
 }
 
