@@ -33,11 +33,11 @@ FP64_VECTOR_PEAK_TFLOPS = 78.6
 # its two HIP events, which spreads the event overhead (about 2.5 us) thin
 PROFILE_REPEAT = 10
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic.json")
-# the source file of each kernel; measured traffic is used only while it and
-# every file it includes (its local #include "..." closure) are unchanged since
-# the counters were taken
+# the source file of each kernel at N = 255 (FP64, one member); measured traffic is
+# used only while it and every file it includes (its local #include "..." closure)
+# are unchanged since the counters were taken
 KERNEL_ROOTS = {
-    "synthesis": "paper_1009_3308_amd/csrc/synthesis.hip",
+    "synthesis": "paper_1009_3308_amd/csrc/pair_legendre.hip",
     "ring": "paper_1009_3308_amd/csrc/ring_fft.hip",
     "analysis": "paper_1009_3308_amd/csrc/analysis.hip",
 }
@@ -82,24 +82,24 @@ def host_cpu_model():
 
 
 def algorithmic_bytes(N, nlat, order, nsrc):
-    """HBM bytes each kernel must move per launch (one member). The FP64
-    synthesis reads two table rows per wave (four waves per order) and the FP64
-    analysis two per 16-degree block of a wave, as seeds of the Legendre
-    recurrence, instead of the table; both read the per-degree recurrence
-    coefficients of the group (two double2 per degree l = m..N for the
-    synthesis, one for the analysis) once."""
+    """HBM bytes each FP64 kernel must move per launch (one member). The synthesis
+    by degree pairs reads two seed values per latitude and segment of its
+    recurrence (eight segments per order below 256 northern latitudes, four above)
+    and ten coefficients per pair of degrees; the analysis the same seeds with two
+    coefficients, or (below 256 northern latitudes) two table rows per 16-degree
+    block of a wave with two coefficients per degree."""
     nh = (nlat + 1) // 2
     slots = (N + 1) * (N + 2) // 2
     F = 4 * nlat * (N + 1) * 16
     W = nlat * (N + 1) * 16
-    seeds = 8 * 2 * 4 * nh * (N + 1)
+    seeds = 16 * (8 if nh < 256 else 4) * nh * (N + 1)
     blocks = sum((N + 1 - m + 15) // 16 for m in range(N + 1))
+    anal_seeds = 8 * 2 * nh * blocks + slots * 16 if nh < 256 else seeds + slots * 8
     return {
-        "synthesis": seeds + nsrc * slots * 16 + F + slots * 32,
+        "synthesis": seeds + nsrc * slots * 16 + F + slots * 40,
         "ring": F + W,
-        # two table rows per 16-degree block (recurrence seeds), ring spectra, states,
-        # recurrence coefficients
-        "analysis": 8 * 2 * nh * blocks + W + (2 * (order + 1) + 1) * slots * 16 + slots * 16,
+        # seeds and coefficients, ring spectra, states
+        "analysis": anal_seeds + W + (2 * (order + 1) + 1) * slots * 16,
     }
 
 

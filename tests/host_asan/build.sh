@@ -10,7 +10,7 @@ OUT=$HERE/_build
 mkdir -p "$OUT"
 HIPCC=${HIPCC:-/opt/rocm/bin/hipcc}
 FLAGS="-O1 -g -fPIC -std=c++17 --offload-arch=gfx950 -Xclang -target-feature -Xclang -packed-fp32-ops -Xarch_host -fsanitize=address -Xarch_host -fno-omit-frame-pointer -I$ROOT/include -I$ROOT/paper_1009_3308_amd/csrc"
-SRCS="host_numerics.cpp nse_api.cpp legendre_table.hip synthesis.hip ring_fft.hip analysis.hip contract_lp.hip adjoint.hip ensemble.hip ndf_adaptive.hip diagnostics.hip"
+SRCS="host_numerics.cpp nse_api.cpp legendre_table.hip synthesis.hip ring_fft.hip analysis.hip contract_lp.hip pair_legendre.hip ndf_adaptive.hip diagnostics.hip"
 pids=""
 for f in $SRCS; do
   "$HIPCC" -x hip $FLAGS -c "$ROOT/paper_1009_3308_amd/csrc/$f" -o "$OUT/${f%.*}.o" &
