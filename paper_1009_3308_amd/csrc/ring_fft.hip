@@ -453,7 +453,7 @@ __device__ __forceinline__ void load_spectra(double2* x, int PL, const FftPlan& 
 // rings of a CU run in step, so these add up. Stockham rings with radices 8, 8, 8, 3 took
 // 22.8 us; 68 us became 50 for 6144 rings of M = 768 and 37 became 23 for 4608 of M = 384,
 // by fewer LDS passes without bank conflicts and one forward transform for two rings;
-// 17.5 became 12.5 for 480 rings of M = 960 (run-time plan).
+// 17.5 became 11.3 for 480 rings of M = 960 (run-time plan).
 template <int MAXM, int NT, int NR, int CM>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_ring(GroupView g, FftPlan rt) {
   const FftPlan pl = plan_of<CM>(rt);
@@ -721,6 +721,7 @@ hipError_t ring_dispatch(int M, F&& launch) {
   if (M <= 192) return launch(integral_constant<int, 192>{}, integral_constant<int, 64>{}, rt);
   if (M <= 384) return launch(integral_constant<int, 384>{}, integral_constant<int, 128>{}, rt);
   if (M <= 768) return launch(integral_constant<int, 768>{}, integral_constant<int, 256>{}, rt);
+  if (M <= 1024) return launch(integral_constant<int, 1024>{}, integral_constant<int, 256>{}, rt);
   return launch(integral_constant<int, kMaxM>{}, integral_constant<int, 256>{}, rt);
 }
 
@@ -730,11 +731,12 @@ size_t ring_lds(const FftPlan& pl, int na) { return sizeof(double2) * (size_t)na
 
 }  // namespace
 
-// Two rings per workgroup (M <= 768: their LDS is 39 to 78 KB) when there are more rings
-// than CUs: neighbouring rings share cache lines of the spectra, and one forward transform
+// Two rings per workgroup (M <= 1024, adjoint M <= 768: their LDS is at most 79 KB) when
+// there are more rings than CUs: neighbouring rings share cache lines of the spectra, and one forward transform
 // serves both. With run-time plans M = 768, 6144 rings: 64 us against 81 with one ring per
-// workgroup; 384 rings: 10.9 against 12.6; M = 192, 2304 rings: 13.4 against 16.2. Up to
-// 256 rings half of the CUs would idle.
+// workgroup; 384 rings: 10.9 against 12.6; M = 192, 2304 rings: 13.4 against 16.2; M = 960,
+// 480 rings: 11.3 against 12.6. Up to 256 rings half of the CUs would idle; above M = 1024 a
+// member alone has more than 256 pairs of rings, of which a CU holds one.
 inline bool two_rings(const GroupView& g) { return (int64_t)g.nlat * g.nb > 256; }
 
 hipError_t launch_ring_adjoint(const GroupView& g, const FftPlan& pl, hipStream_t s) {
@@ -773,11 +775,11 @@ hipError_t launch_ring(const GroupView& g, const FftPlan& pl, int mode, double* 
       hipLaunchKernelGGL((k_ring_grid<MAXM, NT, CM>), grid, dim3(NT), ring_lds<1>(plan_of<CM>(pl), 2), s, g, pl, grid_out);
       return hipGetLastError();
     }
-    if constexpr (MAXM <= 768) {
+    if constexpr (MAXM <= 1024) {
       if (two_rings(g)) {
         dim3 grid(xcd_grid((g.nlat + 1) / 2, 4), g.nb);
         const size_t lds = ring_lds<2>(plan_of<CM>(pl), 4);
-        // M > 384: three workgroups of 256 threads per CU overlap their phases (6144 rings
+        // M = 768: three workgroups of 256 threads per CU overlap their phases (6144 rings
         // 54 us against 58 with 512 threads); when there is one per CU, 512 threads are
         // faster (384 rings: 8.2 against 9.4 us)
         if (MAXM == 768 && (int64_t)g.nlat * g.nb > 1024)
