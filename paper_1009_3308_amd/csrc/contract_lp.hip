@@ -21,11 +21,11 @@
 // at a time: lane (lat, q) continues the 32 degrees of block q, and lanes of one
 // latitude then exchange groups of eight degrees (4 x 4, by register swaps), so that each
 // holds its operand of all four blocks.
-// Analysis: per (order m, 128-degree tile) four waves; wave w computes
-// C[4 used rows][16 degrees] = sum_p A[row][p] T[p][k] for two tiles of 16 degrees, with
+// Analysis: per (order m, tile of 64 or 128 degrees) four waves; wave w computes
+// C[4 used rows][16 degrees] = sum_p A[row][p] T[p][k] for one or two tiles of 16 degrees, with
 // rows We.re, We.im, Wo.re, Wo.im (the ring spectra folded over latitude pairs, split once
 // per workgroup into LDS; only the four live rows are stored), then the
-// epilogue of spectral_ops.h. A lane continues its latitude over the 32 degrees; the
+// epilogue of spectral_ops.h. A lane continues its latitude over the 16 or 32 degrees; the
 // values pass through LDS (a wave's own, degree-major, rows of 68: free of bank
 // conflicts) to the lanes that hold a degree of the operand.
 //
@@ -55,7 +55,7 @@ constexpr int kLpThreads = 64 * kLpWaves;
 constexpr int kSynWaves = 8;                  // of 16 latitudes
 constexpr int kSynThreads = 64 * kSynWaves, kSynTile = 16 * kSynWaves;
 constexpr int kLpSeg = 32;                    // degrees continued from one seed pair
-constexpr int kLpTile = kLpWaves * kLpSeg;    // degrees per workgroup of the analysis
+constexpr int kLpTile = kLpWaves * kLpSeg;    // most degrees per workgroup of the analysis
 constexpr int kLpRow = 68;                    // row of 64 latitudes in the exchange
 
 // x ~ h0 + h1 + h2 with h0 = bf16(x), h1 = bf16(x - h0), h2 = bf16(x - h0 - h1).
@@ -218,10 +218,28 @@ __global__ __launch_bounds__(kSynThreads) void k_synthesis_lp(GroupView g, Synth
   };
   double n0, n1;
   seeds(0, n0, n1);
-  for (int it = threadIdx.x; it < nblk * 3 * 32; it += kSynThreads)
-    reinterpret_cast<uint4*>(bsplit)[it] = reinterpret_cast<const uint4*>(src)[it];
-  for (int k = threadIdx.x; k < 4 * kLpSeg * nsup; k += kSynThreads)
-    rc[k + k / kLpSeg] = k < L ? rec[k] : make_double2(0.0, 0.0);
+  // the panel and the recurrence pairs: all loads before the first LDS write (one round
+  // trip to memory instead of three)
+  constexpr int kMaxBlk = (kMaxM / 3 + 1 + 31) / 32;  // L <= N + 2, 3 N + 2 <= M
+  constexpr int KB = (kMaxBlk * 96 + kSynThreads - 1) / kSynThreads;
+  constexpr int KR = ((kMaxBlk + 3) / 4 * 4 * kLpSeg + kSynThreads - 1) / kSynThreads;
+  uint4 bv[KB];
+  double2 rv[KR];
+#pragma unroll
+  for (int i = 0; i < KB; ++i)
+    bv[i] = reinterpret_cast<const uint4*>(src)[min((int)threadIdx.x + i * kSynThreads, nblk * 96 - 1)];
+#pragma unroll
+  for (int i = 0; i < KR; ++i) rv[i] = rec[min((int)threadIdx.x + i * kSynThreads, L - 1)];
+#pragma unroll
+  for (int i = 0; i < KB; ++i) {
+    const int it = threadIdx.x + i * kSynThreads;
+    if (it < nblk * 96) reinterpret_cast<uint4*>(bsplit)[it] = bv[i];
+  }
+#pragma unroll
+  for (int i = 0; i < KR; ++i) {
+    const int k = threadIdx.x + i * kSynThreads;
+    if (k < 4 * kLpSeg * nsup) rc[k + k / kLpSeg] = k < L ? rv[i] : make_double2(0.0, 0.0);
+  }
   __syncthreads();
   const int mypar = r16 >> 3;
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
@@ -297,26 +315,30 @@ size_t analysis_lp_lds_bytes(int nh) {
   return (size_t)nblk * 3 * 16 * sizeof(bf16x8) + kLpTile * sizeof(double2) + (fold > ex ? fold : ex);
 }
 
-__global__ __launch_bounds__(kLpThreads) __attribute__((amdgpu_waves_per_eu(5))) void k_analysis_lp(GroupView g, AnalOutput out) {
+// H: tiles of 16 degrees per wave, one or two.
+template <int H>
+__global__ __launch_bounds__(kLpThreads) __attribute__((amdgpu_waves_per_eu(5))) void k_analysis_lp(
+    GroupView g, AnalOutput out) {
+  constexpr int kSeg = 16 * H, kTile = kLpWaves * kSeg;  // degrees per wave, per workgroup
   if (gate_closed(g)) return;  // an ended attempt of a device-controlled run
   const int N = g.N, nh = g.nh;
-  const int ntile = (N + kLpTile) / kLpTile;
+  const int ntile = (N + kTile) / kTile;
   const int item = xcd_item(blockIdx.x, 4 * ntile);
   const int m = item / ntile;
   // tiles of high degree have less to do or nothing, so the tile that a CU's successive
   // workgroups take changes (as does the wave with the last, partial segment): 55 -> 42 us
   // at N = 511, where the CUs were busy 36 us on average
   const int tile = (item - m * ntile + (m >> 6)) % ntile;
-  if (m > N || tile * kLpTile > N - m) return;  // uniform across the workgroup
+  if (m > N || tile * kTile > N - m) return;  // uniform across the workgroup
   const int b = blockIdx.y;
   const int nblk = (nh + 31) / 32;
   extern __shared__ double2 sh[];
   bf16x8* asplit = reinterpret_cast<bf16x8*>(sh);  // [nblk][3][16]
   double2* rc = reinterpret_cast<double2*>(asplit + nblk * 3 * 16);
-  double2* wsh = rc + kLpTile;  // We [nh], Wo [nh]; then the waves' exchange rows
+  double2* wsh = rc + kTile;  // We [nh], Wo [nh]; then the waves' exchange rows
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int seg = (wave + m) % kLpWaves;
-  const int kw = tile * kLpTile + seg * kLpSeg;  // the wave's first degree offset
+  const int kw = tile * kTile + seg * kSeg;  // the wave's first degree offset
   const bool active = kw <= N - m;
   const double* T = g.T1 + t1_order_offset(N, m, nh) + (int64_t)min(kw, N - m) * nh;
   // the lane's latitude 64 s + lane, and its seeds: degrees kw and kw + 1
@@ -329,16 +351,26 @@ __global__ __launch_bounds__(kLpThreads) __attribute__((amdgpu_waves_per_eu(5)))
   };
   double n0, n1, nx;
   seeds(0, n0, n1, nx);
-  if ((int)threadIdx.x < kLpTile) {
-    const int k = tile * kLpTile + threadIdx.x;
-    rc[threadIdx.x] = k <= N + 1 - m ? g.rec_a[rec_slot(N, m, m) + k] : make_double2(0.0, 0.0);
-  }
+  // the tile's recurrence pairs and the ring spectra: all loads before the first LDS write
+  const int kr = tile * kTile + (int)threadIdx.x;
+  const double2 rv = g.rec_a[rec_slot(N, m, m) + min(kr, N + 1 - m)];
+  constexpr int KW = (kMaxM / 4 + kLpThreads - 1) / kLpThreads;  // nh <= kMaxM / 4
   const double2* Wb = g.W + ((int64_t)b * (N + 1) + m) * g.nlat;
-  for (int p = threadIdx.x; p < nh; p += blockDim.x) {
-    const double2 qn = Wb[p];
-    const double2 qs = Wb[g.nlat - 1 - p];
-    wsh[p] = make_double2(qn.x + qs.x, qn.y + qs.y);
-    wsh[nh + p] = make_double2(qn.x - qs.x, qn.y - qs.y);
+  double2 qn[KW], qs[KW];
+#pragma unroll
+  for (int i = 0; i < KW; ++i) {
+    const int p = min((int)threadIdx.x + i * kLpThreads, nh - 1);
+    qn[i] = Wb[p];
+    qs[i] = Wb[g.nlat - 1 - p];
+  }
+  if ((int)threadIdx.x < kTile) rc[threadIdx.x] = kr <= N + 1 - m ? rv : make_double2(0.0, 0.0);
+#pragma unroll
+  for (int i = 0; i < KW; ++i) {
+    const int p = threadIdx.x + i * kLpThreads;
+    if (p < nh) {
+      wsh[p] = make_double2(qn[i].x + qs[i].x, qn[i].y + qs[i].y);
+      wsh[nh + p] = make_double2(qn[i].x - qs[i].x, qn[i].y - qs[i].y);
+    }
   }
   __syncthreads();
   // A operand of every 32-latitude block, split once: lane row r = l%16 holds
@@ -366,13 +398,14 @@ __global__ __launch_bounds__(kLpThreads) __attribute__((amdgpu_waves_per_eu(5)))
   __syncthreads();
 
   if (!active) return;
+  const bool two = kw + 16 <= N - m;  // the second tile has a degree
   const int r16 = lane & 15, q = lane >> 4;
   float* ex = reinterpret_cast<float*>(wsh) + wave * 16 * kLpRow;  // [16 degrees][kLpRow]
   bf16x8 zero8;
 #pragma unroll
   for (int j = 0; j < 8; ++j) zero8[j] = (__bf16)0.0f;
   double acc0[4] = {0.0, 0.0, 0.0, 0.0}, acc1[4] = {0.0, 0.0, 0.0, 0.0};
-  const double2* c = rc + seg * kLpSeg;
+  const double2* c = rc + seg * kSeg;
   for (int s = 0; 2 * s < nblk; ++s) {
     double p2 = n0, p1 = n1;
     const double x = nx;
@@ -425,7 +458,9 @@ __global__ __launch_bounds__(kLpThreads) __attribute__((amdgpu_waves_per_eu(5)))
       }
     };
     half(std::integral_constant<int, 0>{}, acc0);
-    half(std::integral_constant<int, 1>{}, acc1);
+    if constexpr (H == 2) {
+      if (two) half(std::integral_constant<int, 1>{}, acc1);
+    }
   }
   // lanes 0..15 hold rows 0..3 (We.re, We.im, Wo.re, Wo.im) of the degrees kw + 16 h + r16
   if (q != 0) return;
@@ -434,7 +469,7 @@ __global__ __launch_bounds__(kLpThreads) __attribute__((amdgpu_waves_per_eu(5)))
     if (k <= N - m) finish_degree(g, out, b, m, k, odd ? ac[2] : ac[0], odd ? ac[3] : ac[1]);
   };
   finish(kw + r16, acc0);
-  finish(kw + 16 + r16, acc1);
+  if constexpr (H == 2) finish(kw + 16 + r16, acc1);
 }
 
 hipError_t launch_synthesis_lp(const GroupView& g, const SynthInput& in, int mode, int prec,
@@ -452,10 +487,22 @@ hipError_t launch_synthesis_lp(const GroupView& g, const SynthInput& in, int mod
 
 hipError_t launch_analysis_lp(const GroupView& g, const AnalOutput& out, int prec, hipStream_t s) {
   if (prec != NSE_PREC_BF16X3) return hipErrorInvalidValue;
-  const int ntile = (g.N + kLpTile) / kLpTile;
-  dim3 grid(xcd_grid((g.N + 1) * ntile, 4 * ntile), g.nb);
-  hipLaunchKernelGGL(k_analysis_lp, grid, dim3(kLpThreads), analysis_lp_lds_bytes(g.nh), s, g,
-                     out);
+  // One tile of 16 degrees per wave has the shorter chain, two share the seeds, the fold
+  // and the split of the ring spectra: the line lies where the workgroups of two tiles fill
+  // the chip. One and two tiles: N = 127 6.2 and 8.5 us, N = 255 10.8 and 13.6, N = 340 19.8
+  // and 22.2, N = 420 31.0 and 29.3, N = 511 45.7 and 41.6, 16 members of N = 127 28.3 and
+  // 25.2, 4 of N = 255 33.2 and 31.3.
+  auto launch = [&](auto hc) {
+    constexpr int H = decltype(hc)::value, kTile = kLpWaves * 16 * H;
+    const int ntile = (g.N + kTile) / kTile;
+    dim3 grid(xcd_grid((g.N + 1) * ntile, 4 * ntile), g.nb);
+    hipLaunchKernelGGL(k_analysis_lp<H>, grid, dim3(kLpThreads), analysis_lp_lds_bytes(g.nh), s, g,
+                       out);
+  };
+  if ((int64_t)(g.N + 1) * (g.N + 1) * g.nb < 160000)
+    launch(std::integral_constant<int, 1>{});
+  else
+    launch(std::integral_constant<int, 2>{});
   return hipGetLastError();
 }
 

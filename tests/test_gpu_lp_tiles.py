@@ -37,8 +37,9 @@ SIZES = [(1, 3), (2, 5), (9, 32), (30, 0), (31, 64), (32, 75), (62, 128), (63, 1
          (126, 240), (127, 256), (128, 270), (130, 0), (160, 320)]
 
 
-@pytest.mark.parametrize("N,nlat", SIZES)
-@pytest.mark.parametrize("members", [1, 3])
+# (ten members: the analysis takes two tiles of degrees per wave from 160000 orders and degrees)
+@pytest.mark.parametrize("N,nlat,members", [(n, l, b) for n, l in SIZES for b in (1, 3)]
+                         + [(126, 240, 10), (128, 270, 10), (160, 320, 7)])
 def test_split_bf16_tiles(N, nlat, members):
     print(f"case: bf16x3 N={N} nlat={nlat} members={members}", flush=True)
     s = pkg.Sphere([(N, nlat, 1e-3)] * members, omega=OMEGA, dt=1e-3, precision="bf16x3")
