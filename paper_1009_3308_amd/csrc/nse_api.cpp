@@ -46,7 +46,7 @@ struct Group {
   // tables of the degree-pair contractions, one buffer (build_pairs), and the seeds
   // of their recurrences in four and in eight segments per order
   double2* d_pair = nullptr;
-  double2 *d_pair_rec = nullptr, *d_pair_con = nullptr, *d_pair_lam = nullptr, *d_pair_syn = nullptr;
+  double2 *d_pair_rec = nullptr, *d_pair_equ = nullptr, *d_pair_con = nullptr, *d_pair_lam = nullptr, *d_pair_syn = nullptr;
   double2 *d_seeds1 = nullptr, *d_seeds2 = nullptr;
   uint64_t* d_lps = nullptr;      // split-bf16 synthesis panels (BF16X3 groups)
   int64_t* d_lpsoff = nullptr;
@@ -72,6 +72,7 @@ struct Group {
     g.rec_a = d_rec_a;
     g.rec_g = d_rec_g;
     g.pair_rec = d_pair_rec;
+    g.pair_equ = reinterpret_cast<const double*>(d_pair_equ);
     g.pair_syn = reinterpret_cast<const double*>(d_pair_syn);
     g.pair_con = d_pair_con;
     g.pair_lam = d_pair_lam;
@@ -310,7 +311,8 @@ hipError_t dalloc(T** p, size_t count) {
 // double and rounded once (the seeds in double-double on the device). Per (m, k) with
 // l = m + 2k, e = e(l, m):
 //   s_{k+1} = s_{k-1} g_k / g_{k+1}, g_k = e(l) e(l+1), s_0 = s_1 = 1;
-//   A_k = s_k / (s_{k+1} g_{k+1}), B_k = -A_k (e(l+1)^2 + e(l+2)^2);
+//   A_k = s_k / (s_{k+1} g_{k+1}), B_k = -A_k (e(l+1)^2 + e(l+2)^2), and for the two forms of
+//   the step A_k + B_k - 2 and B_k + 2 (each rounded once: they are small);
 //   c1_k = s_k e(l+1), c2_k = s_k e(l+2);
 //   synthesis columns of the fields i m c and S c (S c[l] = cm(l) c[l-1] - cp(l) c[l+1],
 //   cm(l) = (l-1) e(l), cp(l) = (l+2) e(l+1)) of coefficients c[l], over the degrees
@@ -319,12 +321,14 @@ hipError_t dalloc(T** p, size_t count) {
 nse_status build_pairs(nse_ctx* c, Group& g) {
   const int N = g.N;
   const int64_t np = pair_slot(N, N) + pair_count(N, N);
-  // one host buffer and one copy: (A, B), their low parts, (c1, c2 | s), the synthesis
-  // columns, (lambda^(-1/2), lambda^(1/2)), the starting values
-  std::vector<double2> all((size_t)8 * np + 2 * N + 3);
-  double2 *rec = all.data(), *lo = rec + np, *con = lo + np, *syn2 = con + 2 * np,
-          *lam = syn2 + 4 * np, *q0 = lam + N + 2;
-  double* syn = reinterpret_cast<double*>(syn2);
+  // one host buffer and one copy: (A, A + B - 2), B + 2, (c1, c2 | s), the synthesis
+  // columns, (lambda^(-1/2), lambda^(1/2)), then for the seeds (A, B), their low parts and
+  // the starting values
+  const int64_t ne = (np + 1) / 2;
+  std::vector<double2> all((size_t)9 * np + ne + 2 * N + 3);
+  double2 *rec = all.data(), *equ2 = rec + np, *con = equ2 + ne, *syn2 = con + 2 * np,
+          *lam = syn2 + 4 * np, *hi = lam + N + 2, *lo = hi + np, *q0 = lo + np;
+  double *syn = reinterpret_cast<double*>(syn2), *equ = reinterpret_cast<double*>(equ2);
   std::vector<long double> e(N + 8), s(N + 8);
   long double pr = std::sqrt(1.0L / (4.0L * 3.14159265358979323846264338327950288L));
   for (int l = 1; l <= N + 1; ++l) {
@@ -349,8 +353,10 @@ nse_status build_pairs(nse_ctx* c, Group& g) {
       const int64_t i = pair_slot(N, m) + k;
       const long double A = s[k] / (s[k + 1] * e[2 * k + 2] * e[2 * k + 3]);
       const long double B = -A * (e[2 * k + 1] * e[2 * k + 1] + e[2 * k + 2] * e[2 * k + 2]);
-      rec[i] = make_double2((double)A, (double)B);
-      lo[i] = make_double2((double)(A - rec[i].x), (double)(B - rec[i].y));
+      rec[i] = make_double2((double)A, (double)(A + B - 2.0L));
+      equ[i] = (double)(B + 2.0L);
+      hi[i] = make_double2((double)A, (double)B);
+      lo[i] = make_double2((double)(A - hi[i].x), (double)(B - hi[i].y));
       const long double c1 = s[k] * e[2 * k + 1], c2 = s[k] * e[2 * k + 2];
       con[2 * i] = make_double2((double)c1, (double)c2);
       con[2 * i + 1] = make_double2((double)s[k], 0.0);
@@ -370,6 +376,7 @@ nse_status build_pairs(nse_ctx* c, Group& g) {
   NSE_HIP(c, dalloc(&g.d_pair, all.size()));
   NSE_HIP(c, hipMemcpy(g.d_pair, all.data(), sizeof(double2) * all.size(), hipMemcpyHostToDevice));
   g.d_pair_rec = g.d_pair;
+  g.d_pair_equ = g.d_pair + (equ2 - rec);
   g.d_pair_con = g.d_pair + (con - rec);
   g.d_pair_syn = g.d_pair + (syn2 - rec);
   g.d_pair_lam = g.d_pair + (lam - rec);
@@ -381,8 +388,8 @@ nse_status build_pairs(nse_ctx* c, Group& g) {
     double2*& seeds = ks == 1 ? g.d_seeds1 : g.d_seeds2;
     NSE_HIP(c, dalloc(&seeds, tiles * ks * 64));
     NSE_HIP(c, hipMemsetAsync(seeds, 0, sizeof(double2) * tiles * ks * 64, c->stream));
-    NSE_HIP(c, launch_pair_seeds(g.view(), ks, g.d_pair + (lo - rec), g.d_pair + (q0 - rec), seeds,
-                                 c->stream));
+    NSE_HIP(c, launch_pair_seeds(g.view(), ks, g.d_pair + (hi - rec), g.d_pair + (lo - rec),
+                                 g.d_pair + (q0 - rec), seeds, c->stream));
   }
   return NSE_OK;
 }
@@ -506,10 +513,10 @@ nse_status timed_launch(nse_ctx* c, int kind, F&& launch) {
 //
 // A member by itself (member block 0) on a small grid is bound by the chain of one workgroup, not by
 // arithmetic, and the degree-by-degree kernels, which cut an order into more and
-// shorter workgroups, have the shorter chain: synthesis 6.8 against 7.4 us at N = 155
-// and 11.3 against 10.7 at N = 255 (nh = 117 and 192), analysis 5.2 against 7.2 us at
-// N = 155, 8.4 against 8.5 at N = 255 and 9.0 against 9.6 at N = 300 (nh = 240); at N =
-// 511 (nh = 384) the pairs take 25.3 against 37.2 and 19 against 29.2 us.
+// shorter workgroups, have the shorter chain: synthesis 7.3 against 7.9 us at N = 155
+// and 11.4 against 11.1 at N = 255 (nh = 117 and 192), analysis 5.3 against 6.7 us at
+// N = 155, 8.5 against 9.3 at N = 255 and 8.8 against 11.0 at N = 300 (nh = 240); at N =
+// 511 (nh = 384) the pairs take 27.5 against 37.2 and 18.6 against 29.2 us.
 bool pair_synthesis(const GroupView& v, int mode) {
   return mode != SYNTH_NONLINEAR || v.mb_synth > 1 || v.nh >= 192;
 }

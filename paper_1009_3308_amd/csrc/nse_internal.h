@@ -80,12 +80,13 @@ struct GroupView {
   const double2* rec_a;     // [(N+2)(N+3)/2] (a(l,m), a(l,m) / a(l-1,m)), slot rec_slot(N, l, m)
   const double2* rec_g;     // same slots: ((2l+1) e(l), lambda_l^(-1/2)), see rec_slot
   // degree-pair contractions (pair_legendre.hip): tables over pair_slot
-  const double2* pair_rec;  // (A_k, B_k)
+  const double2* pair_rec;  // (A_k, A_k + B_k - 2)
+  const double* pair_equ;   // B_k + 2
   const double* pair_syn;   // [8]: coefficients of the synthesis columns, see build_group
   const double2* pair_con;  // [2]: (c1, c2), (s, -) of Pbar[l_k] = c1_k q_k + c2_{k-1} q_{k-1},
                             // Pbar[l_k + 1] = mu s_k q_k
   const double2* pair_lam;  // [N+2] (lambda^(-1/2), lambda^(1/2)), zero at l = 0
-  const double2* seeds1;    // (q_{k-1}, q_k) at the first k of every segment: [m][tile of 16
+  const double2* seeds1;    // (d_k, q_k) at the first k of every segment: [m][tile of 16
   const double2* seeds2;    // latitudes][4 ks segments][16] for ks = 1 and 2 (null: not kept)
   double2* F;               // [nb][N+1][nlat][4] Fourier coefficients of grid fields
   double2* Fa;              // adjoint: per member [N+1][nlat][4] forward fields and [N+1][nlat] adjoint input
@@ -274,8 +275,9 @@ hipError_t launch_ring_project(const GroupView& g, const FftPlan& plan, const do
                                hipStream_t s);
 hipError_t launch_adjoint_pair(const GroupView& g, double2* alpha_bar, const StepAdjointArgs* sa,
                                bool projection, hipStream_t s);
-hipError_t launch_pair_seeds(const GroupView& g, int ks, const double2* rec_lo, const double2* pq0,
-                             double2* seeds, hipStream_t s);
+hipError_t launch_pair_seeds(const GroupView& g, int ks, const double2* rec_hi,
+                             const double2* rec_lo, const double2* pq0, double2* seeds,
+                             hipStream_t s);
 hipError_t launch_synthesis_pair(const GroupView& g, const SynthInput& in, int mode,
                                  hipStream_t s);
 hipError_t launch_analysis_pair(const GroupView& g, const AnalOutput& out, hipStream_t s);

@@ -8,11 +8,27 @@
 //   Pbar[l_k, m]     = e(l_k + 1) Q_k + e(l_k) Q_{k-1},
 //   Pbar[l_k + 1, m] = mu Q_k,
 //   e(l_k+2) e(l_k+3) Q_{k+1} = (mu^2 - e(l_k+1)^2 - e(l_k+2)^2) Q_k - e(l_k) e(l_k+1) Q_{k-1},
-// so a pair of degrees costs one recurrence step. With Q_k = s_k q_k and
+// so a pair of degrees costs one recurrence step (the recurrence in mu^2 of K. Ishioka,
+// J. Meteorol. Soc. Japan 96 (2018) 241-249). With Q_k = s_k q_k and
 // s_{k+1} = s_{k-1} g_k / g_{k+1}, g_k = e(l_k) e(l_k + 1), s_0 = s_1 = 1, the step is
-//   q_{k+1} = (A_k mu^2 + B_k) q_k - q_{k-1}:
-// two FMAs for two degrees (the degree-by-degree form takes three operations for
-// one). The even and the odd degrees of a pair share q_k, so the sums of all
+//   q_{k+1} = (A_k mu^2 + B_k) q_k - q_{k-1}.
+// Its characteristic roots meet at +1 towards the pole (factor +2) and at -1 towards
+// the equator (factor -2), where the rounding of the factor grows with the square of
+// the number of steps. The kernels therefore carry a difference beside q:
+//   pole     d_k = q_k - q_{k-1}:  d_{k+1} = tau q_k + d_k,  q_{k+1} = d_{k+1} + q_k,
+//            tau = A_k (-sin^2) + (A_k + B_k - 2),
+//   equator  d_k = q_k + q_{k-1}:  d_{k+1} = tau q_k - d_k,  q_{k+1} = d_{k+1} - q_k,
+//            tau = A_k mu^2 + (B_k + 2),
+// whose tau is small where the roots meet and is rounded relative to itself: three
+// operations for two degrees (the degree-by-degree form takes three for one). With
+// sigma = 1 at the pole, -1 at the equator, p_k = sigma^k q_k and e_k = sigma^k d_k (k from
+// the start of the segment) both are the same step,
+//   e_{k+1} = sigma tau p_k + e_k,  p_{k+1} = e_{k+1} + p_k,
+// and the sign goes to the products of the odd rows. In between either form does; a wave
+// takes the form of the half that holds its middle latitude.
+// Unweighted sums of N = 511 over all orders: 4.7e-15 off (relative l2), 1.8e-14 with the
+// two-operation step, 1.7e-14 with the degree-by-degree recurrence of the table.
+// The even and the odd degrees of a pair share q_k, so the sums of all
 // fields over both parities are one matrix product per order,
 //   synthesis  C[lat][c] = sum_k q_k(mu_lat) B[k][c],   F(north/south) = E +- mu O,
 //   analysis   S[k][c]   = sum_lat q_k(mu_lat) W[lat][c],
@@ -28,6 +44,7 @@
 // blk; checked on gfx950): lane l supplies A[i = l%4][kk = l/16] and
 // B[kk = l/16][j = l%4] of block (l/4)%4, and receives D[i = l/16][j = l%4] of it.
 #include <algorithm>
+#include <type_traits>
 
 #include "adjoint_device.h"
 #include "lane_ops.h"
@@ -37,15 +54,34 @@ namespace nse {
 
 namespace {
 
+// Whether the latitudes p .. p + count - 1 take the polar form: their middle lies in the
+// polar half.
+__device__ __forceinline__ bool pair_polar(int p, int count, int nh) { return 2 * p + count <= nh; }
+// The argument of sigma tau at node x, and d of a seed stored with the form of its tile.
+__device__ __forceinline__ double pair_arg(bool polar, double x) {
+  return -(polar ? (1.0 - x) * (1.0 + x) : x * x);
+}
+__device__ __forceinline__ double pair_diff(bool polar, const double2& seed, int tile, int nh) {
+  return pair_polar(16 * tile, 16, nh) == polar ? seed.x : fma(2.0, seed.y, -seed.x);
+}
+// One step: rc = (A_k, A_k + B_k - 2) at the pole, (A_k, -B_k - 2) at the equator. SIGN -1:
+// the equator's step of (d, q) themselves.
+template <int SIGN = 0>
+__device__ __forceinline__ void pair_step(const double2& rc, double t, double& e, double& p) {
+  const double tau = fma(rc.x, t, rc.y);
+  e = SIGN < 0 ? -fma(tau, p, e) : fma(tau, p, e);
+  p = SIGN < 0 ? e - p : e + p;
+}
+
 __device__ __forceinline__ double mfma4(double a, double b, double c) {
   return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 0);
 }
 
 // ---------------------------------------------------------------------------
-// Seeds, once per group: q_{k-1}, q_k at the first k of every segment, for the
-// recurrence run in double-double from k = 0 (its rounding grows like K^(3/2) near the
-// poles and the equator, where the roots of the recurrence are double; the
-// segments restart from values correct to the last place).
+// Seeds, once per group: (d_k, q_k) at the first k of every segment, d_k of the polar form
+// on the polar half of the tiles of 16 latitudes and of the other form on the rest, from
+// the recurrence run in double-double from k = 0; the segments restart from values
+// correct to the last place.
 struct dd {
   double h, l;
 };
@@ -75,8 +111,9 @@ __device__ __forceinline__ dd dd_sqrt(dd a) {
 
 // One thread per (latitude, order). pq0[m] = (-1)^m sqrt(prod (2i+1)/(2i)) / (sqrt(4 pi) e(m+1)),
 // so q_0 = pq0[m] sin^m(theta); values below the double range flush to zero.
-__global__ __launch_bounds__(64) void k_pair_seeds(GroupView g, int ks, const double2* rec_lo,
-                                                   const double2* pq0, double2* seeds) {
+__global__ __launch_bounds__(64) void k_pair_seeds(GroupView g, int ks, const double2* rec_hi,
+                                                   const double2* rec_lo, const double2* pq0,
+                                                   double2* seeds) {
   const int N = g.N, nh = g.nh, m = blockIdx.y;
   const int p = blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= nh) return;
@@ -107,11 +144,14 @@ __global__ __launch_bounds__(64) void k_pair_seeds(GroupView g, int ks, const do
   }
   const int len = pair_len(K, ks);
   const int64_t sbase = ((int64_t)m * ((nh + 15) / 16) + (p >> 4)) * (64 * ks) + (p & 15);
+  const double sg = pair_polar(p & ~15, 16, nh) ? -1.0 : 1.0;
   dd q0 = {0.0, 0.0}, q1 = q;
   for (int k = 0; k < K; ++k) {
-    if (k % len == 0)
-      seeds[sbase + (int64_t)(k / len) * 16] = make_double2(ldexp(q0.h, ex), ldexp(q1.h, ex));
-    const double2 hi = g.pair_rec[base + k], lo = rec_lo[base + k];
+    if (k % len == 0) {
+      const dd d = dd_add(q1, {sg * q0.h, sg * q0.l});
+      seeds[sbase + (int64_t)(k / len) * 16] = make_double2(ldexp(d.h, ex), ldexp(q1.h, ex));
+    }
+    const double2 hi = rec_hi[base + k], lo = rec_lo[base + k];
     const dd t = dd_add(dd_mul({hi.x, lo.x}, y), {hi.y, lo.y});
     const dd z = dd_mul(t, q1);
     const dd n = dd_add(z, {-q0.h, -q0.l});
@@ -128,10 +168,11 @@ __global__ __launch_bounds__(64) void k_pair_seeds(GroupView g, int ks, const do
 
 }  // namespace
 
-hipError_t launch_pair_seeds(const GroupView& g, int ks, const double2* rec_lo, const double2* pq0,
-                             double2* seeds, hipStream_t s) {
+hipError_t launch_pair_seeds(const GroupView& g, int ks, const double2* rec_hi,
+                             const double2* rec_lo, const double2* pq0, double2* seeds,
+                             hipStream_t s) {
   dim3 grid((g.nh + 63) / 64, g.N + 1);
-  hipLaunchKernelGGL(k_pair_seeds, grid, dim3(64), 0, s, g, ks, rec_lo, pq0, seeds);
+  hipLaunchKernelGGL(k_pair_seeds, grid, dim3(64), 0, s, g, ks, rec_hi, rec_lo, pq0, seeds);
   return hipGetLastError();
 }
 
@@ -140,13 +181,13 @@ namespace {
 // ---------------------------------------------------------------------------
 // Synthesis. Workgroup of W waves per (order, TL W / KS tiles of 16 latitudes, member):
 // the matrix B[k][c] of the order is built in LDS from the input state (a row of
-// 16 or 20 columns followed by A_k, B_k), then wave w takes TL tiles and the
+// 16 or 20 columns followed by the two forms' coefficients), then wave w takes TL tiles and the
 // (w mod KS)-th part of k, its four 16-lane groups a segment of it each.
 constexpr int kPairCols = 16;
 
 template <int NF>
-constexpr int pair_row() {  // doubles per LDS row: columns, then A_k and B_k
-  return (NF == 5 ? 20 : 16) + 2;
+constexpr int pair_row() {  // doubles per LDS row: columns, then (A, A + B - 2), (A, -B - 2)
+  return (NF == 5 ? 20 : 16) + 4;
 }
 
 // Latitude of the tile that a lane supplies as row of A, and that it receives.
@@ -211,10 +252,11 @@ __device__ __forceinline__ int64_t member_offset(const GroupView& g, int b) {
 // scalar loads of the arguments and the vector loads go out together, where a branch per
 // load had put some twenty argument round trips in a row.
 // Bound: at N = 511 the FP64 issue (products, recurrence) for 0.7 of the time, the rest the
-// prologue and the stores: 25.3 us, 38 by single degrees on the vector units; five fields 30
-// against 82, 16 members of N = 255 54 against 95. At N = 255 alone the chain of one
-// workgroup: 10.7 against 11.3.
-template <int NF, int MS, int W, int TL, int KS>
+// prologue and the stores: 27.5 us (25.6 with the two-operation step), 38 by single degrees on
+// the vector units; five fields 34 against 82, 16 members of N = 255 64 against 95. At N = 255
+// alone the chain of one workgroup: 11.2 against 11.4.
+// TWO: a loop for each half of the latitudes, else one for both (see sums below).
+template <int NF, int MS, int W, int TL, int KS, bool TWO>
 __global__ __launch_bounds__(64 * W) void k_synthesis_pair(GroupView g, SynthInput in, int nsplit) {
   static_assert(NF >= 3 && NF <= 5 && W % KS == 0, "three (grid), four or five (adjoint) fields");
   constexpr int NT = 64 * W, RS = pair_row<NF>(), TW = TL * (W / KS);
@@ -239,6 +281,7 @@ __global__ __launch_bounds__(64 * W) void k_synthesis_pair(GroupView g, SynthInp
   const double2 z2 = make_double2(0.0, 0.0);
   pin_arg(g.mu);
   pin_arg(g.pair_rec);
+  pin_arg(g.pair_equ);
   pin_arg(g.pair_syn);
   pin_arg(g.pair_lam);
   const double2* seeds = KS == 2 ? g.seeds2 : g.seeds1;
@@ -276,6 +319,7 @@ __global__ __launch_bounds__(64 * W) void k_synthesis_pair(GroupView g, SynthInp
     }
   }
   double2 cf[4], rcv = z2, cc = z2, cs = z2;
+  double rce = 0.0;
 #pragma unroll
   for (int u = 0; u < 4; ++u) cf[u] = z2;
   if (64 * wave < K) {
@@ -284,18 +328,19 @@ __global__ __launch_bounds__(64 * W) void k_synthesis_pair(GroupView g, SynthInp
 #pragma unroll
     for (int u = 0; u < 4; ++u) cf[u] = c[u];
     rcv = g.pair_rec[k];
+    rce = g.pair_equ[k];
     if (NF != 4) {
       cc = g.pair_con[2 * k];
       cs = g.pair_con[2 * k + 1];
     }
   }
   double2 sd[TL];
-  double x2[TL], xo[TL];  // mu of the lane's latitude as A row, and of its output
+  double xa[TL], xo[TL];  // mu of the lane's latitude as A row, and of its output
 #pragma unroll
   for (int t = 0; t < TL; ++t) {
     const int tile = min(tile0 + t, ntile - 1);
     sd[t] = seeds[(((int64_t)m * ntile + tile) * KS + kh) * 64 + (lane & 48) + pair_row16(lane)];
-    x2[t] = g.mu[min(tile * 16 + pair_row16(lane), nh - 1)];
+    xa[t] = g.mu[min(tile * 16 + pair_row16(lane), nh - 1)];
     xo[t] = g.mu[min(tile * 16 + pair_out16(lane), nh - 1)];
   }
 #pragma unroll
@@ -344,10 +389,12 @@ __global__ __launch_bounds__(64 * W) void k_synthesis_pair(GroupView g, SynthInp
   // flight (nothing is stored before this barrier), so the flag costs no wait
   if (gate_closed(g)) return;
   __syncthreads();
-  // B of the rows: column 4 f + .. is stored as [k][j][f], j = E.re, E.im, O.re, O.im
+  // B of the rows: columns of fields 0 and 1 as [k][j][f], j = E.re, E.im, O.re, O.im, then
+  // those of 2 and 3, then of 4 (16-byte pieces that the four lanes of a group read side by side)
 #pragma unroll
   for (int u = 0; u < 4; ++u) pin(cf[u]);
   pin(rcv);
+  pin(rce);
   if (NF != 4) {
     pin(cc);
     pin(cs);
@@ -375,27 +422,28 @@ __global__ __launch_bounds__(64 * W) void k_synthesis_pair(GroupView g, SynthInp
     };
     const Cols p = cols(psi + 2 * k);
     row[0] = make_double2(p.mE.x, p.dE.x);
-    row[2] = make_double2(p.mE.y, p.dE.y);
-    row[4] = make_double2(p.mO.x, p.dO.x);
-    row[6] = make_double2(p.mO.y, p.dO.y);
+    row[1] = make_double2(p.mE.y, p.dE.y);
+    row[2] = make_double2(p.mO.x, p.dO.x);
+    row[3] = make_double2(p.mO.y, p.dO.y);
     if constexpr (NF == 3) {
       // grid mode: the third field is the vorticity, or Psi_N = -psi
       const double sg = in.stream ? -1.0 : 1.0;
       double2 E, O;
       plain((in.stream ? psi : zet) + 2 * k, E, O);
-      row[1] = make_double2(sg * E.x, 0.0);
-      row[3] = make_double2(sg * E.y, 0.0);
-      row[5] = make_double2(sg * O.x, 0.0);
+      row[4] = make_double2(sg * E.x, 0.0);
+      row[5] = make_double2(sg * E.y, 0.0);
+      row[6] = make_double2(sg * O.x, 0.0);
       row[7] = make_double2(sg * O.y, 0.0);
     } else {
       const Cols z = cols(zet + 2 * k);
-      row[1] = make_double2(z.dE.x, z.mE.x);
-      row[3] = make_double2(z.dE.y, z.mE.y);
-      row[5] = make_double2(z.dO.x, z.mO.x);
+      row[4] = make_double2(z.dE.x, z.mE.x);
+      row[5] = make_double2(z.dE.y, z.mE.y);
+      row[6] = make_double2(z.dO.x, z.mO.x);
       row[7] = make_double2(z.dO.y, z.mO.y);
     }
     if constexpr (NF == 5) plain(fif + 2 * k, row[8], row[9]);
-    row[RS / 2 - 1] = rcv;
+    row[RS / 2 - 2] = rcv;
+    row[RS / 2 - 1] = make_double2(rcv.x, -rce);
   } else if ((int)threadIdx.x < rows) {
     double2* row = reinterpret_cast<double2*>(Bm + threadIdx.x * RS);
 #pragma unroll
@@ -405,62 +453,76 @@ __global__ __launch_bounds__(64 * W) void k_synthesis_pair(GroupView g, SynthInp
 
   double acc[TL][NF];
 #pragma unroll
-  for (int t = 0; t < TL; ++t) {
-    x2[t] *= x2[t];
+  for (int t = 0; t < TL; ++t)
 #pragma unroll
     for (int f = 0; f < NF; ++f) acc[t][f] = 0.0;
-  }
   if (tile0 < ntile) {
     // two rows at a time; the next two rows' operands are read from LDS during
     // this pair's products (the last pair reads its own rows again)
     const double* row = Bm + (4 * kh + (lane >> 4)) * len * RS;
-    const double* col = row + 4 * (lane & 3);
-    struct Ops {
-      double2 b01, b23, rc;
-      double b4;
-    };
-    auto read = [&](int off) {
-      Ops o;
-      o.b01 = *reinterpret_cast<const double2*>(col + off);
-      o.b23 = *reinterpret_cast<const double2*>(col + off + 2);
-      o.rc = *reinterpret_cast<const double2*>(row + off + RS - 2);
-      o.b4 = NF == 5 ? row[off + 16 + (lane & 3)] : 0.0;
-      return o;
-    };
-    auto keep = [](Ops& o) {
-      pin(o.b01);
-      pin(o.b23);
-      pin(o.rc);
-      if constexpr (NF == 5) pin(o.b4);
-    };
-    auto step = [&](const Ops& o, double (&qa)[TL], double (&qb)[TL]) {
-      // products with q = qb, then qa <- (A mu^2 + B) qb - qa
-#pragma unroll
-      for (int t = 0; t < TL; ++t) {
-        acc[t][0] = mfma4(qb[t], o.b01.x, acc[t][0]);
-        acc[t][1] = mfma4(qb[t], o.b01.y, acc[t][1]);
-        acc[t][2] = mfma4(qb[t], o.b23.x, acc[t][2]);
-        if constexpr (NF >= 4) acc[t][3] = mfma4(qb[t], o.b23.y, acc[t][3]);
-        if constexpr (NF == 5) acc[t][4] = mfma4(qb[t], o.b4, acc[t][4]);
-        qa[t] = fma(fma(o.rc.x, x2[t], o.rc.y), qb[t], -qa[t]);
-      }
-    };
-    double qa[TL], qb[TL];
+    const double* col = row + 2 * (lane & 3);
+    const bool polar = pair_polar(16 * tile0, 16 * TL, nh);
+    const double* form = row + (polar ? RS - 4 : RS - 2);
+    const double sigma = polar ? 1.0 : -1.0;
+    double e[TL], p[TL], tx[TL];
 #pragma unroll
     for (int t = 0; t < TL; ++t) {
-      qa[t] = sd[t].x;
-      qb[t] = sd[t].y;
+      e[t] = pair_diff(polar, sd[t], min(tile0 + t, ntile - 1), nh);
+      p[t] = sd[t].y;
+      tx[t] = pair_arg(polar, xa[t]);
     }
-    Ops o0 = read(0), o1 = read(RS);
-    for (int j = 0; j < len; j += 2) {
-      const int nx = j + 2 < len ? (j + 2) * RS : j * RS;
-      Ops n0 = read(nx), n1 = read(nx + RS);
-      step(o0, qa, qb);
-      step(o1, qb, qa);
-      keep(n0);
-      keep(n1);
-      o0 = n0;
-      o1 = n1;
+    // SIGN 1, -1: a loop for each half, with q itself (the signs are operand modifiers);
+    // 0: one loop for both with p_k = sigma^k q_k
+    auto sums = [&](auto sign) {
+      constexpr int SIGN = decltype(sign)::value;
+      struct Ops {
+        double2 b01, b23, rc;
+        double b4;
+      };
+      auto read = [&](int off) {
+        Ops o;
+        o.b01 = *reinterpret_cast<const double2*>(col + off);
+        o.b23 = *reinterpret_cast<const double2*>(col + off + 8);
+        o.rc = *reinterpret_cast<const double2*>(form + off);
+        o.b4 = NF == 5 ? row[off + 16 + (lane & 3)] : 0.0;
+        return o;
+      };
+      auto keep = [](Ops& o) {
+        pin(o.b01);
+        pin(o.b23);
+        pin(o.rc);
+        if constexpr (NF == 5) pin(o.b4);
+      };
+      auto step = [&](const Ops& o, bool odd) {
+#pragma unroll
+        for (int t = 0; t < TL; ++t) {
+          const double q = SIGN == 0 && odd ? sigma * p[t] : p[t];
+          acc[t][0] = mfma4(q, o.b01.x, acc[t][0]);
+          acc[t][1] = mfma4(q, o.b01.y, acc[t][1]);
+          acc[t][2] = mfma4(q, o.b23.x, acc[t][2]);
+          if constexpr (NF >= 4) acc[t][3] = mfma4(q, o.b23.y, acc[t][3]);
+          if constexpr (NF == 5) acc[t][4] = mfma4(q, o.b4, acc[t][4]);
+          pair_step<SIGN>(o.rc, tx[t], e[t], p[t]);
+        }
+      };
+      Ops o0 = read(0), o1 = read(RS);
+      for (int j = 0; j < len; j += 2) {
+        const int nx = j + 2 < len ? (j + 2) * RS : j * RS;
+        Ops n0 = read(nx), n1 = read(nx + RS);
+        step(o0, false);
+        step(o1, true);
+        keep(n0);
+        keep(n1);
+        o0 = n0;
+        o1 = n1;
+      }
+    };
+    if constexpr (!TWO) {
+      sums(std::integral_constant<int, 0>{});
+    } else if (polar) {
+      sums(std::integral_constant<int, 1>{});
+    } else {
+      sums(std::integral_constant<int, -1>{});
     }
   }
   if constexpr (KS > 1) {
@@ -514,7 +576,7 @@ __global__ __launch_bounds__(64 * W) void k_synthesis_pair(GroupView g, SynthInp
   }
 }
 
-template <int NF, int MS, int W, int TL, int KS>
+template <int NF, int MS, int W, int TL, int KS, bool TWO = (NF < 5)>
 hipError_t launch_synth_pair_as(const GroupView& g, SynthInput in, hipStream_t s) {
   constexpr int TW = TL * (W / KS);
   if (in.nsrc < 1 || in.nsrc > MS) return hipErrorInvalidValue;
@@ -525,22 +587,31 @@ hipError_t launch_synth_pair_as(const GroupView& g, SynthInput in, hipStream_t s
   const size_t red = KS > 1 ? sizeof(double) * (size_t)(W / KS) * TL * NF * 64 : 0;
   const size_t lds = sizeof(double2) * (size_t)((NF == 5 ? 3 : 2) * (2 * K + 4)) + std::max(mat, red);
   const dim3 grid = pair_places(g, NF == 4 ? g.mb_synth : 0, nsplit);
-  hipLaunchKernelGGL((k_synthesis_pair<NF, MS, W, TL, KS>), grid, dim3(64 * W), lds, s, g, in, nsplit);
+  hipLaunchKernelGGL((k_synthesis_pair<NF, MS, W, TL, KS, TWO>), grid, dim3(64 * W), lds, s, g, in, nsplit);
   return hipGetLastError();
 }
 
 // Segments per order: eight (two waves share an order's rows) for single members on grids
-// below nh = 256, where the chain of a workgroup counts (N = 255: synthesis 10.7 us against
-// 11.4 with four, five fields 12.0 against 13.5, adjoint 13.2 against 22.2); four elsewhere.
+// below nh = 256, where the chain of a workgroup counts (N = 255: synthesis 11.1 us against
+// 12.1 with four, five fields 12.9 against 14.5, adjoint 12.6 against 24.6; N = 300:
+// synthesis 16.4 against 18.6); four elsewhere.
 bool pair_eight(const GroupView& g, int mb) { return g.nh < 256 && mb < 2; }
 
 template <int NF, int MS>
 hipError_t launch_synth_pair_nf(const GroupView& g, const SynthInput& in, hipStream_t s) {
-  if (pair_eight(g, NF == 4 ? g.mb_synth : 0)) return launch_synth_pair_as<NF, MS, 6, 2, 2>(g, in, s);
+  // Two loops save the signs of the odd rows and take 4 to 30 VGPRs more. They pay while the
+  // workgroups are resident at once: N = 511, four fields 27.1 us against 28.4, five (135
+  // VGPRs, three waves per SIMD) 43 against 33.4; eight segments and two workgroups per
+  // order at N = 255 11.3 against 11.7, three at N = 300 17.2 against 16.1
+  if (pair_eight(g, NF == 4 ? g.mb_synth : 0)) {
+    if (NF < 5 && g.nh <= 192) return launch_synth_pair_as<NF, MS, 6, 2, 2>(g, in, s);
+    return launch_synth_pair_as<NF, MS, 6, 2, 2, false>(g, in, s);
+  }
   if (g.nh <= 48) return launch_synth_pair_as<NF, MS, 3, 1, 1>(g, in, s);
   if (g.nh <= 96) return launch_synth_pair_as<NF, MS, 2, 3, 1>(g, in, s);
   if (g.nh <= 192) return launch_synth_pair_as<NF, MS, 4, 3, 1>(g, in, s);
-  // (N = 511: eight waves of three tiles 25.3 us, four of three 29.8, six of four 29.6)
+  // (N = 511, measured with the two-operation step: eight waves of three tiles 25.3 us, four of
+  // three 29.8, six of four 29.6)
   return launch_synth_pair_as<NF, MS, 8, 3, 1>(g, in, s);
 }
 
@@ -568,9 +639,11 @@ namespace {
 // segments is summed over the wave's latitudes by GW products into one accumulator,
 // its blocks of different latitudes are added (row rotations) and the sums go to
 // LDS, where the waves meet. The lane butterfly of the degree-by-degree form moved
-// every sum through six exchanges. N = 511: 19 us against 30 by single degrees, bound by
-// the FP64 issue and, for a third of the time, the load phase; 16 members of N = 255 36
-// against 38, 24 of N = 63 9 against 9.
+// every sum through six exchanges. N = 511: 18.6 us against 30 by single degrees, bound by
+// the FP64 issue and, for a third of the time, the load phase; 16 members of N = 255 38
+// against 38, 24 of N = 127 14.3 and of N = 63 7 against 9. (A conditional over whole
+// double2 values at the LDS stores had put the loaded values into scratch memory: 19.6, 41.8,
+// 19.3 and 9.8 us with the shorter step.)
 template <int CTRL>
 __device__ __forceinline__ double add_dpp(double v) {
   return v + lane_dpp<CTRL>(v);
@@ -582,74 +655,125 @@ constexpr int kDppRowRor4 = 0x124;
 // start in different banks (the epilogue reads down the rows).
 template <int KS>
 constexpr int pair_sums() {
-  return 16 * KS + 2;
+  return 16 * KS + 1;
 }
+// The adjoint's sums take the rows about a segment too (see EDGE) where segments are long:
+// with eight segments per order and at most 22 rows the spikes are below 3e-13.
+template <int KS>
+constexpr bool pair_edge() {
+  return KS == 1;
+}
+// Coefficients of n rows (segments side by side) in LDS: (A_k, A_k + B_k - 2) then
+// (A_k, -B_k - 2), 16 bytes a read (N = 511: 18.6 us against 20.3 for two reads), or PACKED
+// A_k, A_k + B_k - 2, -B_k - 2, where two workgroups on a compute unit need the room.
+template <bool PACKED>
+struct PairRec {
+  static constexpr int kRow = PACKED ? 3 : 4;  // doubles per row
+  const double *a, *b;
+  __device__ __forceinline__ PairRec(const double* rec, int n, int r, bool polar)
+      : a(PACKED ? rec + r : rec + 2 * (r + (polar ? 0 : n))), b(rec + r + (polar ? 1 : 2) * n) {}
+  __device__ __forceinline__ double2 get(int r) const {
+    return PACKED ? make_double2(a[r], b[r]) : *reinterpret_cast<const double2*>(a + 2 * r);
+  }
+  static __device__ __forceinline__ void put(double* rec, int n, int r, double A, double pole,
+                                             double equ) {
+    if (PACKED) {
+      rec[r] = A;
+      rec[n + r] = pole;
+      rec[2 * n + r] = equ;
+    } else {
+      double2* v = reinterpret_cast<double2*>(rec);
+      v[r] = make_double2(A, pole);
+      v[n + r] = make_double2(A, equ);
+    }
+  }
+};
 // Rows of one wave: red[j pair_sums + seg 4 + col] = sum over the wave's latitudes of
-// q_k W[lat][col], k = seg len + j. wf [lat][4], x2s [lat], rec [j][seg].
-template <int GW, int KS, int FW = 1>
-__device__ __forceinline__ void pair_rows(const double2 (&seed)[GW], const double (&w)[FW][GW],
-                                          const double (&y)[GW], int len, const double2* rec,
-                                          double* red, int lane) {
-  constexpr int NS = 4 * KS;
+// q_k W[lat][col], k = seg len + j. The wave's latitudes start at p0, its group i holds
+// p0 + LG i .. + LG - 1 (this lane's: lo of them). w [lat][4], rec: PairRec.
+// EDGE: the rows before and after the segment too, j = -1 .. len at rows 0 .. len + 1. The
+// adjoint's sums over neighbouring rows cancel to 1 / l^2 near the equator; across segments,
+// one continued over 66 rows and one fresh from its seed, the cancellation leaves
+// 1e-12 of an order's rms at single degrees (N = 511), within one 1e-13.
+template <int GW, int KS, bool EDGE = false, int FW = 1>
+__device__ __forceinline__ void pair_rows(const double2 (&seed)[GW], const double (&x)[GW],
+                                          const double (&w)[FW][GW], int p0, int lo, int nh, int len,
+                                          const double* rec, double* red, int lane) {
+  constexpr int NS = 4 * KS, LG = 16 / KS;
   const int segA = (lane & 3) + 4 * (((lane >> 2) & 3) % KS);
   const int segD = (lane >> 4) + 4 * (((lane >> 2) & 3) % KS);
-  const double2* rl = rec + segA;
+  const bool polar = pair_polar(p0, GW * LG, nh);
+  const double sigma = polar ? 1.0 : -1.0;
+  const PairRec<EDGE> rl(rec, len * NS, segA, polar);
+  const int rows = EDGE ? len + 2 : len;
   double* out = red + segD * 4 + (lane & 3);
   const bool wr = (lane & 12) < 4 * KS;
-  double qa[GW], qb[GW];
+  double e[GW], p[GW], t[GW];
 #pragma unroll
   for (int i = 0; i < GW; ++i) {
-    qa[i] = seed[i].x;
-    qb[i] = seed[i].y;
+    e[i] = pair_diff(polar, seed[i], min(p0 + i * LG + lo, nh - 1) >> 4, nh);
+    p[i] = seed[i].y;
+    t[i] = pair_arg(polar, x[i]);
   }
-  auto row = [&](const double2& rc, int j, double (&pa)[GW], double (&pb)[GW]) {
-    double d[FW], e[FW];
+  auto store = [&](const double (&v0)[FW], const double (&v1)[FW], int j, bool odd) {
 #pragma unroll
-    for (int f = 0; f < FW; ++f) d[f] = e[f] = 0.0;
+    for (int f = 0; f < FW; ++f) {
+      double v = GW > 1 ? v0[f] + v1[f] : v0[f];
+      if (odd) v *= sigma;
+      if (KS <= 2) v = add_dpp<kDppRowRor8>(v);
+      if (KS == 1) v = add_dpp<kDppRowRor4>(v);
+      if (wr) out[(f * rows + j) * pair_sums<KS>()] = v;
+    }
+  };
+  // back: the row before the state's; go: the state moves on to the next row
+  auto row = [&](const double2& rc, int j, bool odd, bool back, bool go) {
+    double v0[FW], v1[FW];
+#pragma unroll
+    for (int f = 0; f < FW; ++f) v0[f] = v1[f] = 0.0;
 #pragma unroll
     for (int i = 0; i < GW; ++i) {
+      const double q = back ? p[i] - e[i] : p[i];
 #pragma unroll
       for (int f = 0; f < FW; ++f) {
         if (i & 1)
-          e[f] = mfma4(pb[i], w[f][i], e[f]);
+          v1[f] = mfma4(q, w[f][i], v1[f]);
         else
-          d[f] = mfma4(pb[i], w[f][i], d[f]);
+          v0[f] = mfma4(q, w[f][i], v0[f]);
       }
-      pa[i] = fma(fma(rc.x, y[i], rc.y), pb[i], -pa[i]);
+      if (go) pair_step(rc, t[i], e[i], p[i]);
     }
-#pragma unroll
-    for (int f = 0; f < FW; ++f) {
-      double v = GW > 1 ? d[f] + e[f] : d[f];
-      if (KS <= 2) v = add_dpp<kDppRowRor8>(v);
-      if (KS == 1) v = add_dpp<kDppRowRor4>(v);
-      if (wr) out[(f * len + j) * pair_sums<KS>()] = v;
-    }
+    store(v0, v1, j, odd);
   };
-  double2 r0 = rl[0], r1 = rl[NS];
+  double2 r0 = rl.get(0), r1 = rl.get(NS);
+  const int j0 = EDGE ? 1 : 0;
+  if (EDGE) row(r0, 0, true, true, false);
   for (int j = 0; j < len; j += 2) {
     const int nx = (j + 2 < len ? j + 2 : j) * NS;
-    double2 n0 = rl[nx], n1 = rl[nx + NS];
-    row(r0, j, qa, qb);
-    row(r1, j + 1, qb, qa);
+    double2 n0 = rl.get(nx), n1 = rl.get(nx + NS);
+    row(r0, j + j0, false, false, true);
+    row(r1, j + 1 + j0, true, false, true);
     pin(n0);
     pin(n1);
     r0 = n0;
     r1 = n1;
   }
+  if (EDGE) row(r0, len + 1, false, false, false);
 }
 
-// Sum over the waves of columns (c, c + 1) of row k.
+// Segment and row of k (k < 2^9).
+__device__ __forceinline__ int2 pair_seg(int k, int len, float rlen) {
+  const int seg = (int)(((float)k + 0.5f) * rlen);
+  return make_int2(seg, k - seg * len);
+}
+// Sum over the waves of columns (c, c + 1) of row j of a segment.
 template <int W, int KS>
-__device__ __forceinline__ double2 pair_fetch(const double* red, int k, int len, float rlen, int c,
-                                              int stride) {
-  const int seg = (int)(((float)k + 0.5f) * rlen), j = k - seg * len;  // k / len (k < 2^9)
+__device__ __forceinline__ double2 pair_fetch(const double* red, int seg, int j, int c, int stride) {
   const double* r = red + j * pair_sums<KS>() + seg * 4 + c;
   double2 v = make_double2(0.0, 0.0);
 #pragma unroll
   for (int w = 0; w < W; ++w) {
-    const double2 u = *reinterpret_cast<const double2*>(r + w * stride);
-    v.x += u.x;
-    v.y += u.y;
+    v.x += r[w * stride];
+    v.y += r[w * stride + 1];
   }
   return v;
 }
@@ -713,14 +837,15 @@ __global__ __launch_bounds__(64 * W) void k_analysis_pair(GroupView g, AnalOutpu
   const int K = pair_count(N, m), len = pair_len(K, KS);
   const int nhp = (nh + 15) & ~15;
   extern __shared__ double2 sh2[];
-  double2* rec = sh2;                                       // [len][NS]
-  double* red = reinterpret_cast<double*>(rec + len * NS);  // [W][len][pair_sums]
+  double* rec = reinterpret_cast<double*>(sh2);        // PairRec of [len][NS]
+  double* red = rec + PairRec<false>::kRow * len * NS;  // [W][len][pair_sums]
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const double2 z2 = make_double2(0.0, 0.0);
   const int64_t pbase = pair_slot(N, m);
   pin_arg(g.mu);
   pin_arg(g.pair_rec);
+  pin_arg(g.pair_equ);
   pin_arg(g.pair_con);
   pin_arg(g.pair_lam);
   const double2* seeds = KS == 2 ? g.seeds2 : g.seeds1;
@@ -752,13 +877,16 @@ __global__ __launch_bounds__(64 * W) void k_analysis_pair(GroupView g, AnalOutpu
   // mu Wo = mu (Q(p) - Q(p')).
   constexpr int RI = ((KS == 2 ? 340 : kMaxM / 3) / 2 + 2 + 2 * NS + NT - 1) / NT;
   double2 rcv[RI];
+  double rce[RI];
 #pragma unroll
   for (int i = 0; i < RI; ++i) {
     const int r = threadIdx.x + i * NT;
-    rcv[i] = g.pair_rec[pbase + min((r % NS) * len + r / NS, K - 1)];
+    const int64_t k = pbase + min((r % NS) * len + r / NS, K - 1);
+    rcv[i] = g.pair_rec[k];
+    rce[i] = g.pair_equ[k];
   }
   double2 seed[GW];
-  double y[GW], w[1][GW], qs[GW];
+  double x[GW], w[1][GW], qs[GW];
   const int lo = (lane >> 4) + 4 * (((lane >> 2) & 3) / KS);
   const int segA = (lane & 3) + 4 * (((lane >> 2) & 3) % KS);
   const double* Wb = reinterpret_cast<const double*>(g.W + ((int64_t)b * (N + 1) + m) * nlat) + (lane & 1);
@@ -766,7 +894,7 @@ __global__ __launch_bounds__(64 * W) void k_analysis_pair(GroupView g, AnalOutpu
   for (int i = 0; i < GW; ++i) {
     const int p = min((wave * GW + i) * LG + lo, nh - 1);
     seed[i] = seeds[(((int64_t)m * (nhp >> 4) + (p >> 4)) * NS + segA) * 16 + (p & 15)];
-    y[i] = g.mu[p];
+    x[i] = g.mu[p];
     w[0][i] = Wb[2 * p];
     qs[i] = Wb[2 * (nlat - 1 - p)];
   }
@@ -793,7 +921,11 @@ __global__ __launch_bounds__(64 * W) void k_analysis_pair(GroupView g, AnalOutpu
   for (int i = 0; i < RI; ++i) {
     const int r = threadIdx.x + i * NT;
     pin(rcv[i]);
-    if (r < len * NS) rec[r] = (r % NS) * len + r / NS < K ? rcv[i] : z2;
+    pin(rce[i]);
+    if (r < len * NS) {
+      const bool in = (r % NS) * len + r / NS < K;
+      PairRec<false>::put(rec, len * NS, r, in ? rcv[i].x : 0.0, in ? rcv[i].y : 0.0, in ? -rce[i] : 0.0);
+    }
   }
   // an ended attempt of a device-controlled run: checked once the loads are in
   // flight (nothing is stored before this barrier), so the flag costs no wait
@@ -803,16 +935,15 @@ __global__ __launch_bounds__(64 * W) void k_analysis_pair(GroupView g, AnalOutpu
 #pragma unroll
   for (int i = 0; i < GW; ++i) {
     pin(seed[i]);
-    pin(y[i]);
+    pin(x[i]);
     pin(w[0][i]);
     pin(qs[i]);
-    const double v = (lane & 2) ? y[i] * (w[0][i] - qs[i]) : w[0][i] + qs[i];
+    const double v = (lane & 2) ? x[i] * (w[0][i] - qs[i]) : w[0][i] + qs[i];
     w[0][i] = (wave * GW + i) * LG + lo < nh ? v : 0.0;
-    y[i] *= y[i];
   }
   if (!NDF && !kEarly && 64 * wave < La) load_inputs(min((int)threadIdx.x, La - 1));
   __syncthreads();
-  pair_rows<GW, KS>(seed, w, y, len, rec, red + wave * len * pair_sums<KS>(), lane);
+  pair_rows<GW, KS>(seed, x, w, wave * GW * LG, lo, nh, len, rec, red + wave * len * pair_sums<KS>(), lane);
   const float rlen = 1.0f / (float)len;
   const int stride = len * pair_sums<KS>();
   double nv[4] = {0.0, 0.0, 0.0, 0.0};
@@ -821,11 +952,13 @@ __global__ __launch_bounds__(64 * W) void k_analysis_pair(GroupView g, AnalOutpu
   for (int k = threadIdx.x; k < La; k += NT) {
     const int kp = k >> 1;
     if (k >= NT) load_inputs(k);
-    double2 v = pair_fetch<W, KS>(red, kp, len, rlen, 2 * (k & 1), stride);
+    const int2 at = pair_seg(kp, len, rlen);
+    double2 v = pair_fetch<W, KS>(red, at.x, at.y, 2 * (k & 1), stride);
     v.x *= c0.x;
     v.y *= c0.x;
     if (!(k & 1) && kp > 0) {
-      const double2 u = pair_fetch<W, KS>(red, kp - 1, len, rlen, 0, stride);
+      const int2 before = pair_seg(kp - 1, len, rlen);
+      const double2 u = pair_fetch<W, KS>(red, before.x, before.y, 0, stride);
       v.x = fma(c1.y, u.x, v.x);
       v.y = fma(c1.y, u.y, v.y);
     }
@@ -854,7 +987,7 @@ __global__ __launch_bounds__(64 * W) void k_analysis_pair(GroupView g, AnalOutpu
 template <int W, int GW, int KS>
 hipError_t launch_anal_pair_as(const GroupView& g, const AnalOutput& out, hipStream_t s) {
   const size_t len = pair_len(pair_count(g.N, 0), KS);
-  const size_t lds = len * 64 * KS + len * pair_sums<KS>() * 8 * W;
+  const size_t lds = PairRec<false>::kRow * len * 32 * KS + len * pair_sums<KS>() * 8 * W;
   const dim3 grid = pair_places(g, g.mb_anal, 1), block(64 * W);
   if (out.mode == ANAL_NDF)
     hipLaunchKernelGGL((k_analysis_pair<W, GW, KS, -1>), grid, block, lds, s, g, out);
@@ -891,9 +1024,9 @@ namespace {
 // (zero at l = 0, real at m = 0), stored or used in the adjoint of the NDF step. One
 // workgroup holds an order, so the degrees couple through LDS and no panel
 // cotangents go through memory. NFLD = 2: f0 and f1 only (the projection).
-// Waves: WL groups of latitudes for every FW fields. N = 511: 44 us against 111 for the
-// analysis from a table and 6.5 for the transpose (two fields 25.5); N = 255 with the step
-// adjoint 14.4 against 13.7 and 4.9. Bound by the FP64 issue with the row sums, 0.6 of the
+// Waves: WL groups of latitudes for every FW fields. N = 511: 47 us against 111 for the
+// analysis from a table and 6.5 for the transpose (two fields 25); N = 255 with the step
+// adjoint 13.5 against 13.7 and 4.9. Bound by the FP64 issue with the row sums, 0.6 of the
 // time, then by the 25 MB of Fbar at its start.
 // DEP: 0, or the step adjoint with that many history rows at most.
 template <int NFLD, int FW, int WL, int GW, int KS, int DEP>
@@ -902,15 +1035,16 @@ __global__ __launch_bounds__(64 * WL * (NFLD / FW), 4) void k_adjoint_pair(Group
                                                                       StepAdjointArgs sa) {
   constexpr int W = WL * (NFLD / FW), NT = 64 * W, NS = 4 * KS, LG = 16 / KS;
   constexpr int RSUM = pair_sums<KS>();
+  constexpr bool EDGE = pair_edge<KS>();
   const int N = g.N, nh = g.nh, nlat = g.nlat;
   int m, b, split;
   if (!pair_place(g, 0, 1, m, b, split)) return;  // uniform across the workgroup
-  const int K = pair_count(N, m), len = pair_len(K, KS);
+  const int K = pair_count(N, m), len = pair_len(K, KS), rows = EDGE ? len + 2 : len;
   const int nhp = (nh + 15) & ~15;
   extern __shared__ double2 sh2[];
-  double2* rec = sh2;                                      // [len][NS]
-  double* wf = reinterpret_cast<double*>(rec + len * NS);  // [NFLD][nhp][4]
-  double* red = wf;                                        // [W][FW][len][RSUM], after the fold is read
+  double* rec = reinterpret_cast<double*>(sh2);       // PairRec of [len][NS]
+  double* wf = rec + PairRec<EDGE>::kRow * len * NS;  // [NFLD][nhp][4]
+  double* red = wf;                                   // [W][FW][rows][RSUM], after the fold is read
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wl = wave % WL, f0 = (wave / WL) * FW;
@@ -918,6 +1052,7 @@ __global__ __launch_bounds__(64 * WL * (NFLD / FW), 4) void k_adjoint_pair(Group
   const int64_t pbase = pair_slot(N, m);
   pin_arg(g.mu);
   pin_arg(g.pair_rec);
+  pin_arg(g.pair_equ);
   pin_arg(g.pair_syn);
   pin_arg(g.pair_lam);
   const double2* seeds = KS == 2 ? g.seeds2 : g.seeds1;
@@ -939,20 +1074,23 @@ __global__ __launch_bounds__(64 * WL * (NFLD / FW), 4) void k_adjoint_pair(Group
   }
   constexpr int RI = ((KS == 2 ? 340 : kMaxM / 3) / 2 + 2 + 2 * NS + NT - 1) / NT;
   double2 rcv[RI];
+  double rce[RI];
 #pragma unroll
   for (int i = 0; i < RI; ++i) {
     const int r = threadIdx.x + i * NT;
-    rcv[i] = g.pair_rec[pbase + min((r % NS) * len + r / NS, K - 1)];
+    const int64_t k = pbase + min((r % NS) * len + r / NS, K - 1);
+    rcv[i] = g.pair_rec[k];
+    rce[i] = g.pair_equ[k];
   }
   double2 seed[GW];
-  double y[GW], w[FW][GW];
+  double x[GW], w[FW][GW];
   const int lo = (lane >> 4) + 4 * (((lane >> 2) & 3) / KS);
   const int segA = (lane & 3) + 4 * (((lane >> 2) & 3) % KS);
 #pragma unroll
   for (int i = 0; i < GW; ++i) {
     const int p = min((wl * GW + i) * LG + lo, nh - 1);
     seed[i] = seeds[(((int64_t)m * (nhp >> 4) + (p >> 4)) * NS + segA) * 16 + (p & 15)];
-    y[i] = g.mu[p];
+    x[i] = g.mu[p];
   }
 #pragma unroll
   for (int i = 0; i < FI; ++i) {
@@ -977,13 +1115,16 @@ __global__ __launch_bounds__(64 * WL * (NFLD / FW), 4) void k_adjoint_pair(Group
   for (int i = 0; i < RI; ++i) {
     const int r = threadIdx.x + i * NT;
     pin(rcv[i]);
-    if (r < len * NS) rec[r] = (r % NS) * len + r / NS < K ? rcv[i] : z2;
+    pin(rce[i]);
+    if (r < len * NS) {
+      const bool in = (r % NS) * len + r / NS < K;
+      PairRec<EDGE>::put(rec, len * NS, r, in ? rcv[i].x : 0.0, in ? rcv[i].y : 0.0, in ? -rce[i] : 0.0);
+    }
   }
   __syncthreads();
 #pragma unroll
   for (int i = 0; i < GW; ++i) {
     const int p = (wl * GW + i) * LG + lo;
-    y[i] *= y[i];
 #pragma unroll
     for (int f = 0; f < FW; ++f)
       w[f][i] = p < nhp ? wf[((f0 + f) * nhp + p) * 4 + (lane & 3)] : 0.0;
@@ -1017,14 +1158,20 @@ __global__ __launch_bounds__(64 * WL * (NFLD / FW), 4) void k_adjoint_pair(Group
         hin[j] = sa.hin[(j < sa.depth ? j : 0) * sa.state_count + sbase + kk];
     }
   };
-  if (64 * wave < La) load_inputs(min((int)threadIdx.x, La - 1));
-  pair_rows<GW, KS, FW>(seed, w, y, len, rec, red + wave * FW * len * RSUM, lane);
+  // (with twelve groups of latitudes they would take the recurrence's registers: 52 us
+  // against 46.5 at N = 511)
+  constexpr bool kLate = GW >= 12;
+  if (!kLate && 64 * wave < La) load_inputs(min((int)threadIdx.x, La - 1));
+  pair_rows<GW, KS, EDGE, FW>(seed, x, w, wl * GW * LG, lo, nh, len, rec, red + wave * FW * rows * RSUM,
+                              lane);
+  if (kLate && 64 * wave < La) load_inputs(min((int)threadIdx.x, La - 1));
   __syncthreads();
   const float rlen = 1.0f / (float)len;
-  // sums of field f, columns (c, c + 1), row k
-  auto sum = [&](int f, int c, int k) {
-    return pair_fetch<WL, KS>(red + ((f / FW) * WL * FW + f % FW) * len * RSUM, k, len, rlen, c,
-                              FW * len * RSUM);
+  // sums of field f, columns (c, c + 1), row k; EDGE: from the segment of row k0
+  auto sum = [&](int f, int c, int k, int k0) {
+    const int2 at = pair_seg(EDGE ? k0 : k, len, rlen);
+    return pair_fetch<WL, KS>(red + ((f / FW) * WL * FW + f % FW) * rows * RSUM, at.x,
+                              EDGE ? at.y + 1 + k - k0 : at.y, c, FW * rows * RSUM);
   };
   for (int kk = threadIdx.x; kk < La; kk += NT) {
     if (kk >= NT) load_inputs(kk);
@@ -1033,11 +1180,13 @@ __global__ __launch_bounds__(64 * WL * (NFLD / FW), 4) void k_adjoint_pair(Group
     auto cot = [&](int fm, int fd) {
       double2 v;
       if (kk & 1) {
-        const double2 o = sum(fm, 2, k), e1 = sum(fd, 0, ka), e0 = sum(fd, 0, k), eb = sum(fd, 0, kb);
+        const double2 o = sum(fm, 2, k, k), e1 = sum(fd, 0, ka, k), e0 = sum(fd, 0, k, k),
+                      eb = sum(fd, 0, kb, k);
         v.x = cf[0] * o.y + cf[1] * e1.x + cf[2] * e0.x + cf[3] * eb.x;
         v.y = -cf[0] * o.x + cf[1] * e1.y + cf[2] * e0.y + cf[3] * eb.y;
       } else {
-        const double2 e0 = sum(fm, 0, k), eb = sum(fm, 0, kb), o0 = sum(fd, 2, k), ob = sum(fd, 2, kb);
+        const double2 e0 = sum(fm, 0, k, k), eb = sum(fm, 0, kb, k), o0 = sum(fd, 2, k, k),
+                      ob = sum(fd, 2, kb, k);
         v.x = cf[0] * e0.y + cf[1] * eb.y + cf[2] * o0.x + cf[3] * ob.x;
         v.y = -cf[0] * e0.x - cf[1] * eb.x + cf[2] * o0.y + cf[3] * ob.y;
       }
@@ -1065,8 +1214,9 @@ hipError_t launch_adj_pair_as(const GroupView& g, double2* alpha_bar, const Step
   constexpr int W = WL * (NFLD / FW);
   const int nhp = (g.nh + 15) & ~15;
   const size_t len = pair_len(pair_count(g.N, 0), KS);
-  const size_t lds = len * 64 * KS + std::max((size_t)NFLD * nhp * 32,
-                                              len * pair_sums<KS>() * 8 * W * FW);
+  const size_t rows = pair_edge<KS>() ? len + 2 : len;
+  const size_t lds = PairRec<pair_edge<KS>()>::kRow * len * 32 * KS + std::max((size_t)NFLD * nhp * 32,
+                                                  rows * pair_sums<KS>() * 8 * W * FW);
   const dim3 grid = pair_places(g, 0, 1), block(64 * W);
   if constexpr (NFLD == 4) {
     if (sa && sa->depth <= 3) {
@@ -1094,9 +1244,9 @@ hipError_t launch_adj_pair(const GroupView& g, double2* alpha_bar, const StepAdj
     if (g.nh <= 192) return launch_adj_pair_as<NFLD, 2, 4, 6, 2>(g, alpha_bar, sa, s);
     return launch_adj_pair_as<NFLD, 2, 4, 8, 2>(g, alpha_bar, sa, s);
   }
-  // nh > 192: with a wave per field 44 us for the four fields of N = 511 against 48 with
+  // nh > 192: with a wave per field 46.5 us for the four fields of N = 511 against 50.5 with
   // two fields per wave, whose recurrence is shared but whose row sums are twice as many;
-  // for two fields 27.0 against 25.5
+  // for two fields 27.0 against 25.5 (with the two-operation step)
   if constexpr (NFLD == 2) return launch_adj_pair_as<2, 2, 4, 6, 1>(g, alpha_bar, sa, s);
   return launch_adj_pair_as<NFLD, 1, 2, 12, 1>(g, alpha_bar, sa, s);
 }
