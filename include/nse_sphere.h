@@ -70,7 +70,7 @@ enum {
 };
 
 enum {
-  NSE_FLAG_GRAPH = 1,       /* replay nse_step through a captured hipGraph      */
+  NSE_FLAG_GRAPH = 1,       /* replay captured hipGraphs of steps that come back */
   NSE_FLAG_AUTOTUNE = 2,    /* time the member-block sizes of every FP64 group
                                with >= 2 members at init and keep the fastest */
   NSE_FLAG_CHECK_FINITE = 4 /* flag NaN/Inf in the state; nse_sync reports it   */
@@ -128,6 +128,18 @@ nse_status nse_get_member_blocks(const nse_ctx* ctx, int32_t member,
                                  int32_t* synth_block, int32_t* anal_block);
 nse_status nse_set_member_blocks(nse_ctx* ctx, int32_t member,
                                  int32_t synth_block, int32_t anal_block);
+
+/* NSE_FLAG_GRAPH: nse_step and the trajectory calls replay graphs of their
+ * fixed-coefficient steps (index > order): nse_step in chunks of ten steps, one graph
+ * per (hist, forcing); a trajectory call one graph per (traj, hist_bar, forcing,
+ * nsteps, range of steps). Capturing costs more than launching the kernels once,
+ * so a sequence runs without a graph when it comes the first time and is captured when the
+ * same one is among the last few that did (nse_step: at once if at least forty
+ * fixed-coefficient steps are left). A context keeps at most eight graphs. Steps on
+ * a null stream (nse_step) and while kernels are timed are always launched one by
+ * one; results are the same bit for bit. nse_graph_counts writes how many such graphs the context has captured and
+ * launched so far (either pointer may be NULL). */
+nse_status nse_graph_counts(const nse_ctx* ctx, int64_t* captured, int64_t* launched);
 
 /* Rebinds the context to another hipStream_t (captured graphs are dropped). */
 nse_status nse_set_stream(nse_ctx* ctx, void* hip_stream);
@@ -203,9 +215,9 @@ nse_status nse_step_adjoint(nse_ctx* ctx, const double* hist,
  * traj[0] is the final state and traj[nsteps - i ..] is the history before step
  * step0 + i, as nse_step_adjoint_trajectory reads it. The results equal those
  * of nse_step (the same kernels; the new state is stored one slot lower
- * instead of rotating the history). With NSE_FLAG_GRAPH the steps with fixed
- * coefficients (index > order) replay one captured graph per (traj, forcing,
- * nsteps, step0 range). NSE_ERR_ARG for NULL traj or negative step0, nsteps. */
+ * instead of rotating the history). With NSE_FLAG_GRAPH a call that comes back
+ * replays its steps with fixed coefficients (index > order) from a graph (see
+ * nse_graph_counts). NSE_ERR_ARG for NULL traj or negative step0, nsteps. */
 nse_status nse_step_trajectory(nse_ctx* ctx, double* traj, const double* forcing,
                                int64_t step0, int32_t nsteps);
 
@@ -214,8 +226,7 @@ nse_status nse_step_trajectory(nse_ctx* ctx, double* traj, const double* forcing
  * step0 + nsteps - 1) on input and dL/d(history before step step0) on output,
  * the step adjoints of nse_step_adjoint applied from the last step back, each
  * reading its history from traj. Requires newton_iters == 1; hist_bar may not
- * overlap traj. With NSE_FLAG_GRAPH the fixed-coefficient steps replay one
- * captured graph per (traj, hist_bar, nsteps, step0 range). */
+ * overlap traj. NSE_FLAG_GRAPH as for nse_step_trajectory. */
 nse_status nse_step_adjoint_trajectory(nse_ctx* ctx, const double* traj, const double* forcing,
                                        int64_t step0, int32_t nsteps, double* hist_bar);
 

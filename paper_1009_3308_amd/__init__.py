@@ -42,6 +42,7 @@ EXPORTS = (
     "nse_adaptive_log",
     "nse_energy_spectrum", "nse_synthesize_psi", "nse_inertial_manifold",
     "nse_nonlinear_adjoint_noalloc", "nse_step_trajectory", "nse_step_adjoint_trajectory",
+    "nse_graph_counts",
 )
 
 ATTEMPT_ACCEPTED, ATTEMPT_ERROR_FAIL, ATTEMPT_NEWTON_FAIL = 0, 1, 2
@@ -131,6 +132,7 @@ def lib():
         "nse_analyze_velocity": (st, [vp, dp, dp]),
         "nse_get_member_blocks": (st, [vp, i32, ctypes.POINTER(i32), ctypes.POINTER(i32)]),
         "nse_set_member_blocks": (st, [vp, i32, i32, i32]),
+        "nse_graph_counts": (st, [vp, ctypes.POINTER(i64), ctypes.POINTER(i64)]),
         "nse_legendre_values": (st, [vp, i32, i32, dp]),
         "nse_sync": (st, [vp]),
         "nse_profile_enable": (st, [vp, i32]),
@@ -242,6 +244,12 @@ class Sphere:
                                      mu.ctypes.data_as(ctypes.c_void_p),
                                      w.ctypes.data_as(ctypes.c_void_p)), self._h)
         return mu, w
+
+    def graph_counts(self):
+        """(captured, launched): step and trajectory graphs of this context so far."""
+        c, n = ctypes.c_int64(), ctypes.c_int64()
+        _check(lib().nse_graph_counts(self._handle(), ctypes.byref(c), ctypes.byref(n)), self._h)
+        return c.value, n.value
 
     def new_state(self):
         import torch

@@ -6,9 +6,9 @@ takes part in autograd. Its backward pass is the discrete adjoint: the
 history is kept only every `checkpoint_every` steps during the forward run;
 each segment is recomputed forward from its checkpoint into a trajectory
 buffer (nse_step_trajectory, which keeps every intermediate history in place),
-then swept backward over that buffer (nse_step_adjoint_trajectory). Both
-replay captured graphs for the fixed-coefficient steps, and one buffer serves
-every segment. Every step and every adjoint step runs in the HIP library; this
+then swept backward over that buffer (nse_step_adjoint_trajectory). One buffer serves
+every segment; in a context with graphs both calls replay one for the
+fixed-coefficient steps when a buffer comes back with the same steps. Every step and every adjoint step runs in the HIP library; this
 module only schedules the segments and keeps the checkpoints.
 
 Gradients follow torch's convention for complex tensors and a real loss,

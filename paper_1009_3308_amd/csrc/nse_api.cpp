@@ -155,6 +155,7 @@ struct nse_ctx {
   uint64_t graph_clock = 0;
   // the last sequences run without a graph (worth_capture)
   std::vector<GraphEntry> seen;
+  int64_t graphs_captured = 0, graphs_launched = 0;
   // per-kernel timing: every launch is issued `profile_repeat` times between
   // one pair of events (0 = timing off)
   bool profiling = false;
@@ -1412,6 +1413,13 @@ nse_status nse_set_member_blocks(nse_ctx* ctx, int32_t member, int32_t synth_blo
   return NSE_OK;
 }
 
+nse_status nse_graph_counts(const nse_ctx* ctx, int64_t* captured, int64_t* launched) {
+  if (!ctx) return NSE_ERR_ARG;
+  if (captured) *captured = ctx->graphs_captured;
+  if (launched) *launched = ctx->graphs_launched;
+  return NSE_OK;
+}
+
 nse_status nse_set_stream(nse_ctx* ctx, void* hip_stream) {
   if (!ctx) return NSE_ERR_ARG;
   drop_graphs(ctx);
@@ -1510,6 +1518,7 @@ static nse_status step_graph(nse_ctx* ctx, double2* h, const double2* f, int64_t
   }
   ge.used = ++ctx->graph_clock;
   ctx->graphs.push_back(ge);
+  ctx->graphs_captured++;
   *out = ge.exec;
   return NSE_OK;
 }
@@ -1545,8 +1554,10 @@ nse_status nse_step(nse_ctx* ctx, double* hist, const double* forcing, int64_t s
       nse_status s = step_graph(ctx, h, f, k, &exec);
       if (s != NSE_OK) return s;
     }
-    for (; exec && end - k >= kGraphChunk; k += kGraphChunk)
+    for (; exec && end - k >= kGraphChunk; k += kGraphChunk) {
       NSE_HIP(ctx, hipGraphLaunch(exec, ctx->stream));
+      ctx->graphs_launched++;
+    }
   }
   for (; k < end; ++k) {
     nse_status s = enqueue_step(ctx, h, f, k);
@@ -1655,6 +1666,7 @@ nse_status run_sequence_graph(nse_ctx* ctx, int kind, const void* traj, const vo
   ge.i1 = i1;
   if (GraphEntry* g = find_graph(ctx, ge)) {
     NSE_HIP(ctx, hipGraphLaunch(g->exec, ctx->stream));
+    ctx->graphs_launched++;
     return NSE_OK;
   }
   if (!worth_capture(ctx, ge)) return enqueue();
@@ -1690,7 +1702,9 @@ nse_status run_sequence_graph(nse_ctx* ctx, int kind, const void* traj, const vo
   }
   ge.used = ++ctx->graph_clock;
   ctx->graphs.push_back(ge);
+  ctx->graphs_captured++;
   NSE_HIP(ctx, hipGraphLaunch(ge.exec, ctx->stream));
+  ctx->graphs_launched++;
   return NSE_OK;
 }
 

@@ -1,7 +1,7 @@
 #!/bin/bash
 # Builds the C-ABI library with AddressSanitizer on its host code only (device
-# code is compiled as in the product build) and the asan_driver harness.
-# Output: tests/host_asan/_build/asan_driver. Run it with
+# code is compiled as in the product build) and the harnesses asan_driver and asan_graphs.
+# Output: tests/host_asan/_build/asan_driver, asan_graphs. Run them with
 #   ASAN_OPTIONS=detect_leaks=0:verify_asan_link_order=0 tests/host_asan/_build/asan_driver
 set -e
 HERE=$(cd "$(dirname "$0")" && pwd)
@@ -17,6 +17,10 @@ for f in $SRCS; do
   pids="$pids $!"
 done
 for p in $pids; do wait $p; done
-"$HIPCC" -x hip $FLAGS -c "$HERE/asan_driver.cpp" -o "$OUT/asan_driver.o"
-"$HIPCC" --offload-arch=gfx950 -Xarch_host -fsanitize=address "$OUT"/*.o -o "$OUT/asan_driver"
-echo "built $OUT/asan_driver"
+OBJS=""
+for f in $SRCS; do OBJS="$OBJS $OUT/${f%.*}.o"; done
+for d in asan_driver asan_graphs; do
+  "$HIPCC" -x hip $FLAGS -c "$HERE/$d.cpp" -o "$OUT/$d.o"
+  "$HIPCC" --offload-arch=gfx950 -Xarch_host -fsanitize=address $OBJS "$OUT/$d.o" -o "$OUT/$d"
+  echo "built $OUT/$d"
+done
