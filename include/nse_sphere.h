@@ -136,8 +136,9 @@ nse_status nse_set_member_blocks(nse_ctx* ctx, int32_t member,
  * so a sequence runs without a graph when it comes the first time and is captured when the
  * same one is among the last few that did (nse_step: at once if at least forty
  * fixed-coefficient steps are left). A context keeps at most eight graphs. Steps on
- * a null stream (nse_step) and while kernels are timed are always launched one by
- * one; results are the same bit for bit. nse_graph_counts writes how many such graphs the context has captured and
+ * a null stream (nse_step), while kernels are timed, or while the caller captures the
+ * stream are always launched one by one (into the caller's graph in the last case);
+ * results are the same bit for bit. nse_graph_counts writes how many such graphs the context has captured and
  * launched so far (either pointer may be NULL). */
 nse_status nse_graph_counts(const nse_ctx* ctx, int64_t* captured, int64_t* launched);
 

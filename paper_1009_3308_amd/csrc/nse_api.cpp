@@ -1458,6 +1458,16 @@ nse_status nse_nonlinear(nse_ctx* ctx, const double* alpha, double* n_out) {
 
 namespace {
 
+// Whether a sequence may run from a graph of the context's own. While the caller
+// captures the stream, it may not: neither a capture can begin nor a graph be
+// launched there, and the kernels themselves go into the caller's graph.
+static bool graph_allowed(const nse_ctx* ctx) {
+  if (!(ctx->params.flags & NSE_FLAG_GRAPH) || ctx->profiling) return false;
+  if (!ctx->stream) return true;
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  return hipStreamIsCapturing(ctx->stream, &st) == hipSuccess && st == hipStreamCaptureStatusNone;
+}
+
 // The graph kept for the sequence `key`, or null.
 static GraphEntry* find_graph(nse_ctx* ctx, const GraphEntry& key) {
   for (auto& g : ctx->graphs)
@@ -1541,9 +1551,7 @@ nse_status nse_step(nse_ctx* ctx, double* hist, const double* forcing, int64_t s
     nse_status s = enqueue_step(ctx, h, f, k);
     if (s != NSE_OK) return s;
   }
-  const bool graph =
-      (ctx->params.flags & NSE_FLAG_GRAPH) && ctx->stream != nullptr && !ctx->profiling;
-  if (graph && end - k >= kGraphChunk) {
+  if (end - k >= kGraphChunk && ctx->stream && graph_allowed(ctx)) {
     GraphEntry key;
     key.hist = h;
     key.forcing = f;
@@ -1743,8 +1751,7 @@ nse_status nse_step_trajectory(nse_ctx* ctx, double* traj, const double* forcing
     if (s != NSE_OK) return s;
   }
   if (i == n) return NSE_OK;
-  const bool graph =
-      (ctx->params.flags & NSE_FLAG_GRAPH) && !ctx->profiling && n - i >= 2;
+  const bool graph = n - i >= 2 && graph_allowed(ctx);
   const int64_t i0 = i;
   const auto body = [&]() -> nse_status {
     for (int64_t j = i0; j < n; ++j) {
@@ -1779,8 +1786,7 @@ nse_status nse_step_adjoint_trajectory(nse_ctx* ctx, const double* traj, const d
   const auto body = [&]() -> nse_status {
     return enqueue_adjoint_sweep(ctx, tr, n, step0, n, ifix, hb);
   };
-  const bool graph =
-      (ctx->params.flags & NSE_FLAG_GRAPH) && !ctx->profiling && n - ifix >= 2;
+  const bool graph = n - ifix >= 2 && graph_allowed(ctx);
   s = graph ? run_sequence_graph(ctx, 2, traj, hist_bar, forcing, n, ifix, n, body) : body();
   if (s != NSE_OK) return s;
   return enqueue_adjoint_sweep(ctx, tr, n, step0, ifix, 0, hb);

@@ -126,3 +126,51 @@ def test_trajectory_graphs_equal_eager_bitwise(specs):
     assert e.graph_counts() == (0, 0)
     s.close()
     e.close()
+
+
+def test_steps_and_trajectories_inside_the_callers_capture():
+    # after a call outside, the sequence has come before: inside a capture of the caller's it
+    # has to be recorded, not captured again; the recorded steps replay bitwise, with eager
+    # work and synchronisation between the replays
+    specs, n = [(31, 0, 1e-3)] * 2 + [(20, 0, 1e-3)], 20
+    print("case: caller's capture", flush=True)
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        s = pkg.Sphere(specs, omega=OMEGA, dt=1e-3, graph=True, stream=stream)
+        f = _forcing(s, specs)
+        h, h0 = s.new_history(), _history(s, specs)
+        tr, hb, bar = s.new_trajectory(n), s.new_history(), _history(s, specs, 40)
+
+        def work():
+            s.step(h, f, 3, n)
+            s.step_trajectory(tr, f, 3, n)
+            s.step_adjoint_trajectory(tr, f, 3, n, hb)
+
+        def reset(seed):
+            h.copy_(h0 * (1.0 + 0.1 * seed))
+            tr[n:] = h
+            hb.copy_(bar * (2.0 - seed))
+
+        reset(0)
+        work()
+        s.sync()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=stream):
+            work()
+        assert s.graph_counts() == (0, 0)
+        for seed in range(3):
+            reset(seed)
+            g.replay()
+            stream.synchronize()
+            got = (h.clone(), tr.clone(), hb.clone())
+            reset(seed)
+            for i in range(n):  # one step at a time: no graph
+                s.step(h, f, 3 + i, 1)
+            e = pkg.Sphere(specs, omega=OMEGA, dt=1e-3, stream=stream)
+            e.step_trajectory(tr, f, 3, n)
+            e.step_adjoint_trajectory(tr, f, 3, n, hb)
+            e.sync()
+            e.close()
+            for a, b in zip(got, (h, tr, hb)):
+                assert torch.equal(a, b), seed
+        s.close()
