@@ -633,8 +633,8 @@ hipError_t launch_synthesis_pair(const GroupView& g, const SynthInput& in, int m
 namespace {
 
 // ---------------------------------------------------------------------------
-// Analysis. Workgroup of W waves per (order, member). The k range is cut into 4 KS
-// segments of `len` rows; a wave holds GW groups of 16 / KS latitudes (their
+// Analysis. Workgroup of W waves per (order, member). The k range is cut into four
+// segments of `len` rows; a wave holds GW groups of 16 latitudes (their
 // recurrences and folded spectra in registers) and walks the rows once: row j of all
 // segments is summed over the wave's latitudes by GW products into one accumulator,
 // its blocks of different latitudes are added (row rotations) and the sums go to
@@ -827,14 +827,14 @@ __device__ __forceinline__ void finish_step(const AnalOutput& out, double nu, in
 
 // DEP: 0 nonlinear mode, 3 or 6 step modes with that many history rows at most,
 // -1 ANAL_NDF.
-template <int W, int GW, int KS, int DEP>
+template <int W, int GW, int DEP>
 __global__ __launch_bounds__(64 * W) void k_analysis_pair(GroupView g, AnalOutput out) {
-  constexpr int NT = 64 * W, NS = 4 * KS, LG = 16 / KS;
+  constexpr int NT = 64 * W, NS = 4, LG = 16;
   constexpr bool NDF = DEP < 0;
   const int N = g.N, nh = g.nh, nlat = g.nlat;
   int m, b, split;
   if (!pair_place(g, g.mb_anal, 1, m, b, split)) return;  // uniform across the workgroup
-  const int K = pair_count(N, m), len = pair_len(K, KS);
+  const int K = pair_count(N, m), len = pair_len(K, 1);
   const int nhp = (nh + 15) & ~15;
   extern __shared__ double2 sh2[];
   double* rec = reinterpret_cast<double*>(sh2);        // PairRec of [len][NS]
@@ -848,8 +848,7 @@ __global__ __launch_bounds__(64 * W) void k_analysis_pair(GroupView g, AnalOutpu
   pin_arg(g.pair_equ);
   pin_arg(g.pair_con);
   pin_arg(g.pair_lam);
-  const double2* seeds = KS == 2 ? g.seeds2 : g.seeds1;
-  pin_arg(seeds);
+  pin_arg(g.seeds1);
   pin_arg(g.W);
   pin_arg(g.gate);
   // the step's parameters are read ahead of the sums too: behind them each would
@@ -875,7 +874,7 @@ __global__ __launch_bounds__(64 * W) void k_analysis_pair(GroupView g, AnalOutpu
   // the seeds, the node and the lane's component (re or im) of the two rings of its
   // latitude, from which the lane forms its own column of We = Q(p) + Q(p') or
   // mu Wo = mu (Q(p) - Q(p')).
-  constexpr int RI = ((KS == 2 ? 340 : kMaxM / 3) / 2 + 2 + 2 * NS + NT - 1) / NT;
+  constexpr int RI = (kMaxM / 3 / 2 + 2 + 2 * NS + NT - 1) / NT;
   double2 rcv[RI];
   double rce[RI];
 #pragma unroll
@@ -887,13 +886,12 @@ __global__ __launch_bounds__(64 * W) void k_analysis_pair(GroupView g, AnalOutpu
   }
   double2 seed[GW];
   double x[GW], w[1][GW], qs[GW];
-  const int lo = (lane >> 4) + 4 * (((lane >> 2) & 3) / KS);
-  const int segA = (lane & 3) + 4 * (((lane >> 2) & 3) % KS);
+  const int lo = (lane >> 4) + 4 * ((lane >> 2) & 3), segA = lane & 3;
   const double* Wb = reinterpret_cast<const double*>(g.W + ((int64_t)b * (N + 1) + m) * nlat) + (lane & 1);
 #pragma unroll
   for (int i = 0; i < GW; ++i) {
     const int p = min((wave * GW + i) * LG + lo, nh - 1);
-    seed[i] = seeds[(((int64_t)m * (nhp >> 4) + (p >> 4)) * NS + segA) * 16 + (p & 15)];
+    seed[i] = g.seeds1[(((int64_t)m * (nhp >> 4) + (p >> 4)) * NS + segA) * 16 + (p & 15)];
     x[i] = g.mu[p];
     w[0][i] = Wb[2 * p];
     qs[i] = Wb[2 * (nlat - 1 - p)];
@@ -913,10 +911,6 @@ __global__ __launch_bounds__(64 * W) void k_analysis_pair(GroupView g, AnalOutpu
     c0 = g.pair_con[2 * (pbase + kp) + (k & 1)];          // (c1, c2) or (s, -)
     c1 = g.pair_con[2 * (pbase + (kp > 0 ? kp - 1 : 0))];  // of the pair before
   };
-  // (the small grids' epilogue would wait for these; on the large ones, bound by
-  // bandwidth here, they go out behind the loads that the sums need)
-  constexpr bool kEarly = !NDF && KS == 2;
-  if (kEarly && 64 * wave < La) load_inputs(min((int)threadIdx.x, La - 1));
 #pragma unroll
   for (int i = 0; i < RI; ++i) {
     const int r = threadIdx.x + i * NT;
@@ -941,11 +935,12 @@ __global__ __launch_bounds__(64 * W) void k_analysis_pair(GroupView g, AnalOutpu
     const double v = (lane & 2) ? x[i] * (w[0][i] - qs[i]) : w[0][i] + qs[i];
     w[0][i] = (wave * GW + i) * LG + lo < nh ? v : 0.0;
   }
-  if (!NDF && !kEarly && 64 * wave < La) load_inputs(min((int)threadIdx.x, La - 1));
+  // (behind the loads that the sums need)
+  if (!NDF && 64 * wave < La) load_inputs(min((int)threadIdx.x, La - 1));
   __syncthreads();
-  pair_rows<GW, KS>(seed, x, w, wave * GW * LG, lo, nh, len, rec, red + wave * len * pair_sums<KS>(), lane);
+  pair_rows<GW, 1>(seed, x, w, wave * GW * LG, lo, nh, len, rec, red + wave * len * pair_sums<1>(), lane);
   const float rlen = 1.0f / (float)len;
-  const int stride = len * pair_sums<KS>();
+  const int stride = len * pair_sums<1>();
   double nv[4] = {0.0, 0.0, 0.0, 0.0};
   if (NDF && (int)threadIdx.x < La) load_inputs(threadIdx.x);
   __syncthreads();
@@ -953,12 +948,12 @@ __global__ __launch_bounds__(64 * W) void k_analysis_pair(GroupView g, AnalOutpu
     const int kp = k >> 1;
     if (k >= NT) load_inputs(k);
     const int2 at = pair_seg(kp, len, rlen);
-    double2 v = pair_fetch<W, KS>(red, at.x, at.y, 2 * (k & 1), stride);
+    double2 v = pair_fetch<W, 1>(red, at.x, at.y, 2 * (k & 1), stride);
     v.x *= c0.x;
     v.y *= c0.x;
     if (!(k & 1) && kp > 0) {
       const int2 before = pair_seg(kp - 1, len, rlen);
-      const double2 u = pair_fetch<W, KS>(red, before.x, before.y, 0, stride);
+      const double2 u = pair_fetch<W, 1>(red, before.x, before.y, 0, stride);
       v.x = fma(c1.y, u.x, v.x);
       v.y = fma(c1.y, u.y, v.y);
     }
@@ -984,19 +979,19 @@ __global__ __launch_bounds__(64 * W) void k_analysis_pair(GroupView g, AnalOutpu
   }
 }
 
-template <int W, int GW, int KS>
+template <int W, int GW>
 hipError_t launch_anal_pair_as(const GroupView& g, const AnalOutput& out, hipStream_t s) {
-  const size_t len = pair_len(pair_count(g.N, 0), KS);
-  const size_t lds = PairRec<false>::kRow * len * 32 * KS + len * pair_sums<KS>() * 8 * W;
+  const size_t len = pair_len(pair_count(g.N, 0), 1);
+  const size_t lds = PairRec<false>::kRow * len * 32 + len * pair_sums<1>() * 8 * W;
   const dim3 grid = pair_places(g, g.mb_anal, 1), block(64 * W);
   if (out.mode == ANAL_NDF)
-    hipLaunchKernelGGL((k_analysis_pair<W, GW, KS, -1>), grid, block, lds, s, g, out);
+    hipLaunchKernelGGL((k_analysis_pair<W, GW, -1>), grid, block, lds, s, g, out);
   else if (out.mode == ANAL_NONLINEAR)
-    hipLaunchKernelGGL((k_analysis_pair<W, GW, KS, 0>), grid, block, lds, s, g, out);
+    hipLaunchKernelGGL((k_analysis_pair<W, GW, 0>), grid, block, lds, s, g, out);
   else if (out.depth <= 3)
-    hipLaunchKernelGGL((k_analysis_pair<W, GW, KS, 3>), grid, block, lds, s, g, out);
+    hipLaunchKernelGGL((k_analysis_pair<W, GW, 3>), grid, block, lds, s, g, out);
   else
-    hipLaunchKernelGGL((k_analysis_pair<W, GW, KS, 6>), grid, block, lds, s, g, out);
+    hipLaunchKernelGGL((k_analysis_pair<W, GW, 6>), grid, block, lds, s, g, out);
   return hipGetLastError();
 }
 
@@ -1004,11 +999,11 @@ hipError_t launch_anal_pair_as(const GroupView& g, const AnalOutput& out, hipStr
 
 hipError_t launch_analysis_pair(const GroupView& g, const AnalOutput& out, hipStream_t s) {
   // W GW tiles of 16 latitudes cover the nh of the size class
-  if (g.nh <= 48) return launch_anal_pair_as<1, 3, 1>(g, out, s);
-  if (g.nh <= 96) return launch_anal_pair_as<1, 6, 1>(g, out, s);
-  if (g.nh <= 192) return launch_anal_pair_as<3, 4, 1>(g, out, s);
-  if (g.nh <= 320) return launch_anal_pair_as<4, 5, 1>(g, out, s);
-  return launch_anal_pair_as<4, 6, 1>(g, out, s);
+  if (g.nh <= 48) return launch_anal_pair_as<1, 3>(g, out, s);
+  if (g.nh <= 96) return launch_anal_pair_as<1, 6>(g, out, s);
+  if (g.nh <= 192) return launch_anal_pair_as<3, 4>(g, out, s);
+  if (g.nh <= 320) return launch_anal_pair_as<4, 5>(g, out, s);
+  return launch_anal_pair_as<4, 6>(g, out, s);
 }
 
 namespace {
@@ -1215,8 +1210,8 @@ hipError_t launch_adj_pair_as(const GroupView& g, double2* alpha_bar, const Step
   const int nhp = (g.nh + 15) & ~15;
   const size_t len = pair_len(pair_count(g.N, 0), KS);
   const size_t rows = pair_edge<KS>() ? len + 2 : len;
-  const size_t lds = PairRec<pair_edge<KS>()>::kRow * len * 32 * KS + std::max((size_t)NFLD * nhp * 32,
-                                                  rows * pair_sums<KS>() * 8 * W * FW);
+  const size_t lds = PairRec<pair_edge<KS>()>::kRow * len * 32 * KS +
+                     std::max((size_t)NFLD * nhp * 32, rows * pair_sums<KS>() * 8 * W * FW);
   const dim3 grid = pair_places(g, 0, 1), block(64 * W);
   if constexpr (NFLD == 4) {
     if (sa && sa->depth <= 3) {
@@ -1247,8 +1242,10 @@ hipError_t launch_adj_pair(const GroupView& g, double2* alpha_bar, const StepAdj
   // nh > 192: with a wave per field 46.5 us for the four fields of N = 511 against 50.5 with
   // two fields per wave, whose recurrence is shared but whose row sums are twice as many;
   // for two fields 27.0 against 25.5 (with the two-operation step)
-  if constexpr (NFLD == 2) return launch_adj_pair_as<2, 2, 4, 6, 1>(g, alpha_bar, sa, s);
-  return launch_adj_pair_as<NFLD, 1, 2, 12, 1>(g, alpha_bar, sa, s);
+  if constexpr (NFLD == 2)
+    return launch_adj_pair_as<2, 2, 4, 6, 1>(g, alpha_bar, sa, s);
+  else
+    return launch_adj_pair_as<NFLD, 1, 2, 12, 1>(g, alpha_bar, sa, s);
 }
 
 }  // namespace
