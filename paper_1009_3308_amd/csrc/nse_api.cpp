@@ -1310,6 +1310,13 @@ nse_status nse_sphere_init(const nse_member* members, int32_t n_members, const n
       g.N = mem[i].N;
       g.nlat = mem[i].nlat;
       g.plan = fft_plan(2 * g.nlat);
+      if (pair_lds_bytes(g.N, (g.nlat + 1) / 2) > kMaxLds ||
+          ring_lds_bytes(2 * g.nlat, g.plan) > kMaxLds) {
+        char buf[256];
+        snprintf(buf, sizeof buf, "member %d: N = %d on %d latitudes needs more LDS than a workgroup has",
+                 i, g.N, g.nlat);
+        return init_fail(NSE_ERR_UNSUPPORTED, buf);
+      }
       c->groups.push_back(g);
       gi = (int)c->groups.size() - 1;
     }

@@ -14,7 +14,8 @@ namespace nse {
 
 constexpr int kMaxSources = 6;   // predictor terms of NDF_5 (q + 1 <= 6)
 constexpr int kMaxStepCoef = 7;  // c_0 .. c_{q+1} of NDF_5
-constexpr int kMaxM = 1536;      // largest supported longitude count (ring LDS <= 64 KiB)
+constexpr int kMaxM = 1536;      // largest supported longitude count
+constexpr size_t kMaxLds = 160 << 10;  // LDS of a compute unit of gfx950, the most a workgroup may take
 
 // Linear work item of block `bid` such that the blocks the dispatcher places on one
 // XCD (bid % 8, round-robin) take consecutive chunks of `chunk` items, and chunks
@@ -286,12 +287,15 @@ hipError_t launch_inertial_manifold(const GroupView& g, const double2* n, const 
                                     int N1, double omega, double2* phi, hipStream_t s);
 hipError_t launch_ndf_correct(const GroupView& g, const NdfArgs& a, hipStream_t s);
 
-// Dynamic LDS of the launches (validated against 64 KiB at init).
+// Dynamic LDS of the launches (checked at init: these against 64 KiB, which the kernels below
+// nh = 256 and of the reduced precisions stay within, the next two against kMaxLds).
 size_t synthesis_lds_bytes(int N);
 size_t analysis_otf_lds_bytes(int nh);
 size_t synthesis_lp_lds_bytes(int N);
 size_t split_panel_lp_lds_bytes(int N);
 size_t analysis_lp_lds_bytes(int nh);
+size_t pair_lds_bytes(int N, int nh);
+size_t ring_lds_bytes(int M, const FftPlan& plan);
 
 // Host numerics.
 void gauss_legendre(int n, std::vector<double>& mu, std::vector<double>& w);

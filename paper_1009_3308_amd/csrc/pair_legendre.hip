@@ -576,16 +576,21 @@ __global__ __launch_bounds__(64 * W) void k_synthesis_pair(GroupView g, SynthInp
   }
 }
 
+template <int NF, int W, int TL, int KS>
+size_t synth_pair_lds(int N) {
+  const int K = pair_count(N, 0), len = pair_len(K, KS);
+  const size_t mat = sizeof(double) * (size_t)(4 * KS * len) * pair_row<NF>();
+  const size_t red = KS > 1 ? sizeof(double) * (size_t)(W / KS) * TL * NF * 64 : 0;
+  return sizeof(double2) * (size_t)((NF == 5 ? 3 : 2) * (2 * K + 4)) + std::max(mat, red);
+}
+
 template <int NF, int MS, int W, int TL, int KS, bool TWO = (NF < 5)>
 hipError_t launch_synth_pair_as(const GroupView& g, SynthInput in, hipStream_t s) {
   constexpr int TW = TL * (W / KS);
   if (in.nsrc < 1 || in.nsrc > MS) return hipErrorInvalidValue;
   for (int i = in.nsrc; i < MS; ++i) in.src[i] = in.src[0];  // loaded, not used
   const int nsplit = ((g.nh + 15) / 16 + TW - 1) / TW;
-  const int K = pair_count(g.N, 0), len = pair_len(K, KS);
-  const size_t mat = sizeof(double) * (size_t)(4 * KS * len) * pair_row<NF>();
-  const size_t red = KS > 1 ? sizeof(double) * (size_t)(W / KS) * TL * NF * 64 : 0;
-  const size_t lds = sizeof(double2) * (size_t)((NF == 5 ? 3 : 2) * (2 * K + 4)) + std::max(mat, red);
+  const size_t lds = synth_pair_lds<NF, W, TL, KS>(g.N);
   const dim3 grid = pair_places(g, NF == 4 ? g.mb_synth : 0, nsplit);
   hipLaunchKernelGGL((k_synthesis_pair<NF, MS, W, TL, KS, TWO>), grid, dim3(64 * W), lds, s, g, in, nsplit);
   return hipGetLastError();
@@ -979,10 +984,15 @@ __global__ __launch_bounds__(64 * W) void k_analysis_pair(GroupView g, AnalOutpu
   }
 }
 
+template <int W>
+size_t anal_pair_lds(int N) {
+  const size_t len = pair_len(pair_count(N, 0), 1);
+  return PairRec<false>::kRow * len * 32 + len * pair_sums<1>() * 8 * W;
+}
+
 template <int W, int GW>
 hipError_t launch_anal_pair_as(const GroupView& g, const AnalOutput& out, hipStream_t s) {
-  const size_t len = pair_len(pair_count(g.N, 0), 1);
-  const size_t lds = PairRec<false>::kRow * len * 32 + len * pair_sums<1>() * 8 * W;
+  const size_t lds = anal_pair_lds<W>(g.N);
   const dim3 grid = pair_places(g, g.mb_anal, 1), block(64 * W);
   if (out.mode == ANAL_NDF)
     hipLaunchKernelGGL((k_analysis_pair<W, GW, -1>), grid, block, lds, s, g, out);
@@ -1203,15 +1213,19 @@ __global__ __launch_bounds__(64 * WL * (NFLD / FW), 4) void k_adjoint_pair(Group
   }
 }
 
+template <int NFLD, int FW, int WL, int KS>
+size_t adj_pair_lds(int N, int nh) {
+  constexpr int W = WL * (NFLD / FW);
+  const size_t len = pair_len(pair_count(N, 0), KS), rows = pair_edge<KS>() ? len + 2 : len;
+  return PairRec<pair_edge<KS>()>::kRow * len * 32 * KS +
+         std::max((size_t)NFLD * ((nh + 15) & ~15) * 32, rows * pair_sums<KS>() * 8 * W * FW);
+}
+
 template <int NFLD, int FW, int WL, int GW, int KS>
 hipError_t launch_adj_pair_as(const GroupView& g, double2* alpha_bar, const StepAdjointArgs* sa,
                               hipStream_t s) {
   constexpr int W = WL * (NFLD / FW);
-  const int nhp = (g.nh + 15) & ~15;
-  const size_t len = pair_len(pair_count(g.N, 0), KS);
-  const size_t rows = pair_edge<KS>() ? len + 2 : len;
-  const size_t lds = PairRec<pair_edge<KS>()>::kRow * len * 32 * KS +
-                     std::max((size_t)NFLD * nhp * 32, rows * pair_sums<KS>() * 8 * W * FW);
+  const size_t lds = adj_pair_lds<NFLD, FW, WL, KS>(g.N, g.nh);
   const dim3 grid = pair_places(g, 0, 1), block(64 * W);
   if constexpr (NFLD == 4) {
     if (sa && sa->depth <= 3) {
@@ -1254,6 +1268,15 @@ hipError_t launch_adjoint_pair(const GroupView& g, double2* alpha_bar, const Ste
                                bool projection, hipStream_t s) {
   return projection ? launch_adj_pair<2>(g, alpha_bar, nullptr, s)
                     : launch_adj_pair<4>(g, alpha_bar, sa, s);
+}
+
+// The most dynamic LDS that a launch for members of this truncation and grid asks for (the
+// adjoint has more fields than the projection, and the five-field synthesis than the others).
+size_t pair_lds_bytes(int N, int nh) {
+  size_t v = synth_pair_lds<4, 8, 3, 1>(N);
+  v = std::max(v, nh < 256 ? synth_pair_lds<5, 6, 2, 2>(N) : synth_pair_lds<5, 8, 3, 1>(N));
+  v = std::max(v, nh <= 96 ? anal_pair_lds<1>(N) : nh <= 192 ? anal_pair_lds<3>(N) : anal_pair_lds<4>(N));
+  return std::max(v, nh < 256 ? adj_pair_lds<4, 2, 4, 2>(N, nh) : adj_pair_lds<4, 1, 2, 1>(N, nh));
 }
 
 }  // namespace nse

@@ -29,6 +29,7 @@
 // products go through one forward transform, q_a + i q_b.
 // The plan (radices up to 16, three stages for most M, FftPlan) is chosen on the
 // host for the fewest stages and then for LDS accesses without bank conflicts.
+#include <algorithm>
 #include <type_traits>
 
 #include "nse_internal.h"
@@ -738,6 +739,20 @@ size_t ring_lds(const FftPlan& pl, int na) { return sizeof(double2) * (size_t)na
 // 480 rings: 11.3 against 12.6. Up to 256 rings half of the CUs would idle; above M = 1024 a
 // member alone has more than 256 pairs of rings, of which a CU holds one.
 inline bool two_rings(const GroupView& g) { return (int64_t)g.nlat * g.nb > 256; }
+
+// The most dynamic LDS that a ring kernel of this plan asks for.
+size_t ring_lds_bytes(int M, const FftPlan& pl) {
+  size_t v = 0;
+  (void)ring_dispatch(M, [&](auto maxm, auto, auto cm) {
+    constexpr int MAXM = decltype(maxm)::value, CM = decltype(cm)::value;
+    const FftPlan p = plan_of<CM>(pl);
+    v = ring_lds<1>(p, 3);
+    if (MAXM <= 1024) v = std::max(v, ring_lds<2>(p, 4));
+    if (MAXM <= 768) v = std::max(v, ring_lds<2>(p, 6));
+    return hipSuccess;
+  });
+  return v;
+}
 
 hipError_t launch_ring_adjoint(const GroupView& g, const FftPlan& pl, hipStream_t s) {
   return ring_dispatch(g.M, [&](auto maxm, auto nt, auto cm) {
