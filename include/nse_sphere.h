@@ -59,9 +59,10 @@ typedef enum {
 
 /* Precision of the Legendre contractions (the direct synthesis and analysis sums
  * of Section 4.2). The quadrature weights, FFTs, grid products and the viscous
- * update always run in FP64, and so do the Legendre values: FP64 and FP32
- * continue the recurrence in FP64 registers from FP64 seeds (FP64 mostly by pairs of
- * degrees); BF16X3 reads the FP64 table rounded once to FP32. */
+ * update always run in FP64, and so do the Legendre values, which every mode continues
+ * by the recurrence in FP64 registers from FP64 seeds (FP64 mostly by pairs of degrees);
+ * FP32 and BF16X3 round each value once to FP32. The adjoint and the projection run in FP64
+ * in every mode. */
 enum {
   NSE_PREC_FP64 = 0,  /* FP64 products, FP64 accumulation                      */
   NSE_PREC_FP32 = 1,  /* values and coefficients rounded to FP32, FP32 products
@@ -99,8 +100,9 @@ typedef struct {
 } nse_params;
 
 /* Creates a context: computes the Gauss-Legendre rule (eq. (quadrule)) on the
- * host, the normalised Legendre tables Pbar[l,m](mu_p), l <= N+1, in FP64 on
- * the GPU (eq. (sph_har)), FFT twiddles and workspaces. `hip_stream` is a
+ * host, the coefficients and seeds of the Legendre recurrences and, where a kernel starts
+ * from it, the table Pbar[l,m](mu_p), l <= N+1, in FP64 on the GPU (eq. (sph_har)),
+ * FFT twiddles and workspaces. `hip_stream` is a
  * hipStream_t (NULL = default stream). Returns NSE_ERR_ARG for n_members < 1,
  * N < 1, 2*nlat < 3N+2, nu < 0, order outside 1..5, newton_iters < 1, an
  * unknown precision or flag; NSE_ERR_UNSUPPORTED for a grid whose M has a prime
@@ -246,9 +248,11 @@ nse_status nse_synthesize(nse_ctx* ctx, const double* alpha, double* grid_out);
  * nse_synthesize exactly (up to rounding). */
 nse_status nse_analyze_velocity(nse_ctx* ctx, const double* u_grid, double* alpha_out);
 
-/* Normalised Legendre values of one member's table: writes Pbar[l,m](mu_p)
- * for l = m..N+1 and the nlat/2 northern nodes p as a device array
- * [l-m][p] of doubles. For testing the FP64 table. */
+/* Normalised Legendre values on one member's grid: writes Pbar[l,m](mu_p)
+ * for l = m..N+1 and the (nlat+1)/2 northern nodes p as a device array
+ * [l-m][p] of doubles, computed anew by the kernel of the FP64 table (which FP64
+ * members with (nlat+1)/2 >= 256 do not keep). For testing that recurrence; the seeds of the
+ * degree pairs are computed by another. */
 nse_status nse_legendre_values(nse_ctx* ctx, int32_t member, int32_t m,
                                double* out);
 

@@ -1029,7 +1029,7 @@ namespace {
 // (zero at l = 0, real at m = 0), stored or used in the adjoint of the NDF step. One
 // workgroup holds an order, so the degrees couple through LDS and no panel
 // cotangents go through memory. NFLD = 2: f0 and f1 only (the projection).
-// Waves: WL groups of latitudes for every FW fields. N = 511: 47 us against 111 for the
+// Waves: WL groups of latitudes for every FW fields. N = 511: 41.4 us against 111 for the
 // analysis from a table and 6.5 for the transpose (two fields 25); N = 255 with the step
 // adjoint 13.5 against 13.7 and 4.9. Bound by the FP64 issue with the row sums, 0.6 of the
 // time, then by the 25 MB of Fbar at its start.
@@ -1063,7 +1063,7 @@ __global__ __launch_bounds__(64 * WL * (NFLD / FW), 4) void k_adjoint_pair(Group
   const double2* seeds = KS == 2 ? g.seeds2 : g.seeds1;
   pin_arg(seeds);
   pin_arg(g.Fbar);
-  // as in the analysis: all loads of the prologue at once
+  // as in the analysis: the loads of the prologue at once (but see kLate)
   constexpr int FI = (NFLD * (KS == 2 ? 256 : 16 * WL * GW) + NT - 1) / NT;
   const int64_t fstride = (int64_t)(N + 1) * nlat;
   const double2* Gb = g.Fbar + (int64_t)b * 4 * fstride + (int64_t)m * nlat;
@@ -1091,12 +1091,21 @@ __global__ __launch_bounds__(64 * WL * (NFLD / FW), 4) void k_adjoint_pair(Group
   double x[GW], w[FW][GW];
   const int lo = (lane >> 4) + 4 * (((lane >> 2) & 3) / KS);
   const int segA = (lane & 3) + 4 * (((lane >> 2) & 3) % KS);
+  auto load_seeds = [&] {
 #pragma unroll
-  for (int i = 0; i < GW; ++i) {
-    const int p = min((wl * GW + i) * LG + lo, nh - 1);
-    seed[i] = seeds[(((int64_t)m * (nhp >> 4) + (p >> 4)) * NS + segA) * 16 + (p & 15)];
-    x[i] = g.mu[p];
-  }
+    for (int i = 0; i < GW; ++i) {
+      const int p = min((wl * GW + i) * LG + lo, nh - 1);
+      seed[i] = seeds[(((int64_t)m * (nhp >> 4) + (p >> 4)) * NS + segA) * 16 + (p & 15)];
+      x[i] = g.mu[p];
+    }
+  };
+  // With eight and twelve groups of latitudes the registers do not hold the folded
+  // cotangents beside the seeds, nor the first degree's coefficients and history beside the
+  // recurrence: 18 to 56 registers went through scratch memory. There the seeds are loaded
+  // behind the fold and the coefficients behind the sums. N = 511 47.6 -> 41.4 us, N = 300 with
+  // the step adjoint 26.0 -> 19.7 (order 5: 29.6 -> 21.1), without it 19.1 -> 18.5
+  constexpr bool kLate = GW >= 8;
+  if (!kLate) load_seeds();
 #pragma unroll
   for (int i = 0; i < FI; ++i) {
     pin(qn[i]);
@@ -1126,6 +1135,7 @@ __global__ __launch_bounds__(64 * WL * (NFLD / FW), 4) void k_adjoint_pair(Group
       PairRec<EDGE>::put(rec, len * NS, r, in ? rcv[i].x : 0.0, in ? rcv[i].y : 0.0, in ? -rce[i] : 0.0);
     }
   }
+  if (kLate) load_seeds();
   __syncthreads();
 #pragma unroll
   for (int i = 0; i < GW; ++i) {
@@ -1163,9 +1173,6 @@ __global__ __launch_bounds__(64 * WL * (NFLD / FW), 4) void k_adjoint_pair(Group
         hin[j] = sa.hin[(j < sa.depth ? j : 0) * sa.state_count + sbase + kk];
     }
   };
-  // (with twelve groups of latitudes they would take the recurrence's registers: 52 us
-  // against 46.5 at N = 511)
-  constexpr bool kLate = GW >= 12;
   if (!kLate && 64 * wave < La) load_inputs(min((int)threadIdx.x, La - 1));
   pair_rows<GW, KS, EDGE, FW>(seed, x, w, wl * GW * LG, lo, nh, len, rec, red + wave * FW * rows * RSUM,
                               lane);
@@ -1253,9 +1260,9 @@ hipError_t launch_adj_pair(const GroupView& g, double2* alpha_bar, const StepAdj
     if (g.nh <= 192) return launch_adj_pair_as<NFLD, 2, 4, 6, 2>(g, alpha_bar, sa, s);
     return launch_adj_pair_as<NFLD, 2, 4, 8, 2>(g, alpha_bar, sa, s);
   }
-  // nh > 192: with a wave per field 46.5 us for the four fields of N = 511 against 50.5 with
-  // two fields per wave, whose recurrence is shared but whose row sums are twice as many;
-  // for two fields 27.0 against 25.5 (with the two-operation step)
+  // nh >= 256: with a wave per field 46.5 us for the four fields of N = 511 against 50.5 with
+  // two fields per wave, whose recurrence is shared but whose row sums are twice as many
+  // (before the late loads); for two fields 27.0 against 25.5 (with the two-operation step)
   if constexpr (NFLD == 2)
     return launch_adj_pair_as<2, 2, 4, 6, 1>(g, alpha_bar, sa, s);
   else
