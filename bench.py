@@ -85,7 +85,7 @@ def algorithmic_bytes(N, nlat, order, nsrc):
     """HBM bytes each FP64 kernel must move per launch (one member). The synthesis
     by degree pairs reads two seed values per latitude and segment of its
     recurrence (eight segments per order below 256 northern latitudes, four above)
-    and ten coefficients per pair of degrees; the analysis the same seeds with two
+    and eleven coefficients per pair of degrees; the analysis the same seeds with three
     coefficients, or (below 256 northern latitudes) two table rows per 16-degree
     block of a wave with two coefficients per degree."""
     nh = (nlat + 1) // 2
@@ -94,9 +94,9 @@ def algorithmic_bytes(N, nlat, order, nsrc):
     W = nlat * (N + 1) * 16
     seeds = 16 * (8 if nh < 256 else 4) * nh * (N + 1)
     blocks = sum((N + 1 - m + 15) // 16 for m in range(N + 1))
-    anal_seeds = 8 * 2 * nh * blocks + slots * 16 if nh < 256 else seeds + slots * 8
+    anal_seeds = 8 * 2 * nh * blocks + slots * 16 if nh < 256 else seeds + slots * 12
     return {
-        "synthesis": seeds + nsrc * slots * 16 + F + slots * 40,
+        "synthesis": seeds + nsrc * slots * 16 + F + slots * 44,
         "ring": F + W,
         # seeds and coefficients, ring spectra, states
         "analysis": anal_seeds + W + (2 * (order + 1) + 1) * slots * 16,

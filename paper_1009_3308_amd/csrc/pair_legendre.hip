@@ -251,7 +251,7 @@ __device__ __forceinline__ int64_t member_offset(const GroupView& g, int b) {
 // unconditional (indices clamped, values masked afterwards): in one block the
 // scalar loads of the arguments and the vector loads go out together, where a branch per
 // load had put some twenty argument round trips in a row.
-// Bound: at N = 511 the FP64 issue (products, recurrence) for 0.7 of the time, the rest the
+// Bound: at N = 511 the FP64 issue (products, recurrence) for 0.77 of the cycles, the rest the
 // prologue and the stores: 27.5 us (25.6 with the two-operation step), 38 by single degrees on
 // the vector units; five fields 34 against 82, 16 members of N = 255 64 against 95. At N = 255
 // alone the chain of one workgroup: 11.2 against 11.4.
@@ -645,7 +645,7 @@ namespace {
 // its blocks of different latitudes are added (row rotations) and the sums go to
 // LDS, where the waves meet. The lane butterfly of the degree-by-degree form moved
 // every sum through six exchanges. N = 511: 18.6 us against 30 by single degrees, bound by
-// the FP64 issue and, for a third of the time, the load phase; 16 members of N = 255 38
+// the FP64 issue for 0.55 of the cycles (0.8 for 16 members of N = 255) and the load phase; 16 members of N = 255 38
 // against 38, 24 of N = 127 14.3 and of N = 63 7 against 9. (A conditional over whole
 // double2 values at the LDS stores had put the loaded values into scratch memory: 19.6, 41.8,
 // 19.3 and 9.8 us with the shorter step.)
@@ -1031,8 +1031,8 @@ namespace {
 // cotangents go through memory. NFLD = 2: f0 and f1 only (the projection).
 // Waves: WL groups of latitudes for every FW fields. N = 511: 41.4 us against 111 for the
 // analysis from a table and 6.5 for the transpose (two fields 25); N = 255 with the step
-// adjoint 13.5 against 13.7 and 4.9. Bound by the FP64 issue with the row sums, 0.6 of the
-// time, then by the 25 MB of Fbar at its start.
+// adjoint 13.5 against 13.7 and 4.9. Bound by the FP64 issue with the row sums, 0.8 of the
+// cycles, then by the 25 MB of Fbar at its start.
 // DEP: 0, or the step adjoint with that many history rows at most.
 template <int NFLD, int FW, int WL, int GW, int KS, int DEP>
 __global__ __launch_bounds__(64 * WL * (NFLD / FW), 4) void k_adjoint_pair(GroupView g,
